@@ -13,57 +13,62 @@ __constant__ StepTables kStepTables = make_step_tables();
 
 // ---------------------------------------------------------------------------
 // packing: FP32 master parameters (W1 [64][47], b1, W2 [64][64], b2, W3 [41][64],
-// b3) and the normalisation (x_mean[47], x_iscale[47], y_scale[41]) -> Packed
+// b3) and the normalisation (x_mean[47], x_iscale[47], y_scale[41]) -> Packed.  One element
+// of each table per thread: the time is a few dependent load latencies (one 256-thread block
+// walking the tables took 27 us).
 // ---------------------------------------------------------------------------
+constexpr int kPackBlocks = N_HID * N_HID / 256;      // the largest table
+
 __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ theta,
                                                    const float* __restrict__ norm,
                                                    Packed* __restrict__ P) {
+  const int tid = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
   const float* W1 = theta;
   const float* b1 = W1 + N_HID * N_IN;
   const float* W2 = b1 + N_HID;
   const float* b2 = W2 + N_HID * N_HID;
   const float* W3 = b2 + N_HID;
   const float* b3 = W3 + N_OUT * N_HID;
-  for (int t = threadIdx.x; t < N_HID * K_IN; t += blockDim.x) {
+  for (int t = tid; t < N_HID * K_IN; t += step) {
     const int r = t / K_IN, c = t % K_IN;
     P->w1[t] = c < N_IN ? bf16_bits(W1[r * N_IN + c]) : 0;
   }
-  for (int t = threadIdx.x; t < N_HID * N_HID; t += blockDim.x) {
+  for (int t = tid; t < N_HID * N_HID; t += step) {
     const int r = t / N_HID, c = t % N_HID;
     P->w2[t] = bf16_bits(W2[t]);
     P->w2t[t] = bf16_bits(W2[c * N_HID + r]);
   }
-  for (int t = threadIdx.x; t < M_OUT * N_HID; t += blockDim.x) {
+  for (int t = tid; t < M_OUT * N_HID; t += step) {
     const int r = t / N_HID, c = t % N_HID;               // w3: [output r][hidden c]
     P->w3[t] = r < N_OUT ? bf16_bits(W3[r * N_HID + c]) : 0;
     const int h = t / M_OUT, o = t % M_OUT;               // w3t: [hidden h][output o]
     P->w3t[t] = o < N_OUT ? bf16_bits(W3[o * N_HID + h]) : 0;
   }
-  for (int t = threadIdx.x; t < M_OUT; t += blockDim.x) {
+  for (int t = tid; t < M_OUT; t += step) {
     P->b1[t] = t < N_HID ? b1[t] : 0.f;
     P->b2[t] = t < N_HID ? b2[t] : 0.f;
     P->b3[t] = t < N_OUT ? b3[t] : 0.f;
     P->y_scale[t] = t < N_OUT ? norm[2 * N_IN + t] : 0.f;
     P->zero[t] = 0.f;
   }
-  for (int t = threadIdx.x; t < K_IN; t += blockDim.x) {
+  for (int t = tid; t < K_IN; t += step) {
     P->x_mean[t] = t < N_IN ? norm[t] : 0.f;
     P->x_iscale[t] = t < N_IN ? norm[N_IN + t] : 0.f;
   }
   // the fused step's copies: logical row k at physical row perm_row(k); the output
   // layer carries y_scale so that its result is the moment correction itself
-  for (int t = threadIdx.x; t < 64 * K_IN; t += blockDim.x) {
+  for (int t = tid; t < 64 * K_IN; t += step) {
     const int row = t / K_IN, c = t % K_IN, k = perm_row(row);
     P->w1p[t] = c < N_IN ? bf16_bits(W1[k * N_IN + c]) : 0;
     P->tab.feat[t] = kStepTables.feat[t];
     P->tab.minv[t] = kStepTables.minv[t];
   }
-  for (int t = threadIdx.x; t < 64 * N_HID; t += blockDim.x) {
+  for (int t = tid; t < 64 * N_HID; t += step) {
     const int row = t / N_HID, c = t % N_HID, k = perm_row(row);
     P->w2p[t] = bf16_bits(W2[k * N_HID + c]);
     P->w3p[t] = k < N_OUT ? bf16_bits(norm[2 * N_IN + k] * W3[k * N_HID + c]) : 0;
   }
-  for (int row = threadIdx.x; row < 64; row += blockDim.x) {
+  for (int row = tid; row < 64; row += step) {
     const int k = perm_row(row);
     P->b1p[row] = b1[k];
     P->b2p[row] = b2[k];
@@ -218,21 +223,42 @@ __global__ __launch_bounds__(64) void grad_kernel(const Packed* __restrict__ P,
   }
 }
 
-// Fixed-order sums of the per-block partials: the gradient and the batch loss.
-__global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restrict__ gpart,
-                                                          const double* __restrict__ lpart,
-                                                          int64_t nblocks, int64_t batch,
-                                                          float* __restrict__ grad,
-                                                          double* __restrict__ loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < N_PARAMS) {
-    double s = 0.0;
-    for (int64_t b = 0; b < nblocks; ++b) s += (double)gpart[b * N_PARAMS + p];
+// Fixed-order FP64 sums of the per-block partials: the gradient and the batch loss.  One
+// wavefront's lanes hold 64 neighbouring parameters (a partial row is read in 256-byte runs)
+// and the block's 16 wavefronts take every 16th row, eight loads in flight each; their sums
+// are added in wavefront order.  One more block sums the losses.  Bound by the latency of a
+// few loads and the 10 MB of partials at 16 384 rows (from L2): one thread per parameter
+// walking all 256 rows had 39 blocks in flight and took 76 us.
+constexpr int kReduceSlices = 16;
+constexpr int kReduceBlocks = (N_PARAMS + 63) / 64;
+
+__global__ __launch_bounds__(64 * kReduceSlices) void grad_reduce_kernel(const float* __restrict__ gpart,
+                                                                         const double* __restrict__ lpart,
+                                                                         int64_t nblocks, int64_t batch,
+                                                                         float* __restrict__ grad,
+                                                                         double* __restrict__ loss) {
+  __shared__ double part[kReduceSlices][64];
+  const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
+  double s = 0.0;
+  if (blockIdx.x < kReduceBlocks) {
+    const int p = blockIdx.x * 64 + lane;
+    if (p < N_PARAMS) {
+#pragma unroll 8
+      for (int64_t b = slice; b < nblocks; b += kReduceSlices) s += (double)gpart[b * N_PARAMS + p];
+    }
+    part[slice][lane] = s;
+    __syncthreads();
+    if (slice != 0 || p >= N_PARAMS) return;
+    for (int k = 1; k < kReduceSlices; ++k) s += part[k][lane];
     grad[p] = (float)s;
-  }
-  if (p == 0 && loss) {
-    double s = 0.0;
-    for (int64_t b = 0; b < nblocks; ++b) s += lpart[b];
+  } else {
+#pragma unroll 4
+    for (int64_t b = threadIdx.x; b < nblocks; b += 64 * kReduceSlices) s += lpart[b];
+    s = wave_sum(s);
+    if (lane == 0) part[slice][0] = s;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < kReduceSlices; ++k) s += part[k][0];
     *loss = s / ((double)batch * N_OUT);
   }
 }
@@ -412,7 +438,7 @@ __global__ __launch_bounds__(256) void pairs_kernel(const float* __restrict__ a,
 // host launchers
 // ---------------------------------------------------------------------------
 hipError_t mlp_launch_pack(const float* theta, const float* norm, void* packed, hipStream_t st) {
-  hipLaunchKernelGGL(mlp::pack_kernel, dim3(1), dim3(256), 0, st, theta, norm, (mlp::Packed*)packed);
+  hipLaunchKernelGGL(mlp::pack_kernel, dim3(mlp::kPackBlocks), dim3(256), 0, st, theta, norm, (mlp::Packed*)packed);
   return hipGetLastError();
 }
 
@@ -431,8 +457,8 @@ hipError_t mlp_launch_grad(const void* packed, const float* x, const float* y, c
                      (const mlp::Packed*)packed, x, y, idx, batch, gpart, lpart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mlp::grad_reduce_kernel, dim3((mlp::N_PARAMS + 255) / 256), dim3(256), 0, st,
-                     gpart, lpart, blocks, batch, grad, loss);
+  hipLaunchKernelGGL(mlp::grad_reduce_kernel, dim3(mlp::kReduceBlocks + (loss ? 1 : 0)),
+                     dim3(64 * mlp::kReduceSlices), 0, st, gpart, lpart, blocks, batch, grad, loss);
   return hipGetLastError();
 }
 
