@@ -14,8 +14,8 @@ __constant__ StepTables kStepTables = make_step_tables();
 // ---------------------------------------------------------------------------
 // packing: FP32 master parameters (W1 [64][47], b1, W2 [64][64], b2, W3 [41][64],
 // b3) and the normalisation (x_mean[47], x_iscale[47], y_scale[41]) -> Packed.  One element
-// of each table per thread: the time is a few dependent load latencies (one 256-thread block
-// walking the tables took 27 us).
+// of each table per thread: the time is a few dependent load latencies (27 -> 5 us against one
+// 256-thread block walking the tables).
 // ---------------------------------------------------------------------------
 constexpr int kPackBlocks = N_HID * N_HID / 256;      // the largest table
 
@@ -106,93 +106,211 @@ __global__ __launch_bounds__(64) void forward_kernel(const Packed* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// gradient of the mean squared error over a batch (rows idx[0..batch)), one
-// wavefront of 64 samples per block; per-block partial gradients in the
-// master-parameter order and a partial loss
+// Gradient of the mean squared error over a batch (rows idx[0..batch)): per-block partial
+// gradients in the master-parameter order and a partial loss.
+//
+// A block is 64 samples on four wavefronts; each 64 x 64 product of a layer is four 32 x 32
+// MFMA tiles, one per wavefront, with the operands in LDS: activations node-major (the next
+// layer's B operand, 16-byte reads) and, for the sums over the samples, also row-major
+// ([row][node], so that both operands of an outer product are 16-byte reads).  A wavefront
+// keeps its tile's hidden activations in registers for tanh' = 1 - h^2, and loads all its
+// weight operands before the first product.  The time is one block's chain (16 384 rows are
+// one block per CU), not bandwidth: loads 4.2 us, the two tanh layers 2.0 us each, the output
+// layer 1.3, back 0.9, outer products and stores 1.5-2.0.  52 -> 18 us at 16 384 rows (one
+// wavefront per block had read its rows per lane and its outer-product operands one 2-byte
+// value at a time).
 // ---------------------------------------------------------------------------
-// sum_n A[n][i] B[n][j] for i, j < 64 over the 64 nodes (rows) of two LDS buffers.
-template <typename Emit>
-__device__ __forceinline__ void outer_over_nodes(const uint16_t* A, const uint16_t* B, Emit emit) {
-  const int lane = threadIdx.x & 63;
-  const int half = lane >> 5, col = lane & 31;
+constexpr int kGradRows = 64, kGradThreads = 256;
+
+// Round to nearest even with gfx950's own conversion (bf16_bits without its integer steps).
+__device__ __forceinline__ uint16_t to_bf16_bits(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
+
+// A operand of a 32-row tile of W [rows][KW]: all k-steps of the lane's row.
+template <int KW>
+struct WeightTile {
+  bf16x8 v[KW / 16];
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ W, int mt, int col, int half) {
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
+    for (int ks = 0; ks < KW / 16; ++ks) v[ks] = load8(W + (32 * mt + col) * KW + 16 * ks + 8 * half);
+  }
+};
+
+// acc + W tile x the 32 nodes at `nt` of a node-major buffer
+template <int KW>
+__device__ __forceinline__ f32x16 tile_product(const WeightTile<KW>& w, const uint16_t* act, int nt, int col,
+                                               int half, f32x16 acc) {
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      f32x16 acc = {0};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        bf16x8 a, b;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int n = 16 * ks + 8 * half + q;
-          a[q] = __builtin_bit_cast(__bf16, A[n * LDS_PITCH + 32 * mt + col]);
-          b[q] = __builtin_bit_cast(__bf16, B[n * LDS_PITCH + 32 * nt + col]);
-        }
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) emit(32 * mt + d_row(r, lane), 32 * nt + col, acc[r]);
-    }
+  for (int ks = 0; ks < KW / 16; ++ks)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w.v[ks], load8(act + (32 * nt + col) * LDS_PITCH + 16 * ks + 8 * half),
+                                                  acc, 0, 0, 0);
+  return acc;
 }
 
-__global__ __launch_bounds__(64) void grad_kernel(const Packed* __restrict__ P,
-                                                  const float* __restrict__ x,
-                                                  const float* __restrict__ y,
-                                                  const int64_t* __restrict__ idx, int64_t batch,
-                                                  float* __restrict__ gpart,
-                                                  double* __restrict__ lpart) {
-  __shared__ __attribute__((aligned(16))) uint16_t X[64 * LDS_PITCH], H1[64 * LDS_PITCH],
-      H2[64 * LDS_PITCH], D0[64 * LDS_PITCH], D12[2 * 64 * LDS_PITCH];
+// The tile's 16 results of a lane (rows 32 mt + d_row(r), node 32 nt + col) into the
+// node-major buffer `act` and the row-major buffer `tr` (either may be null).
+__device__ __forceinline__ void put_tile(const uint16_t (&v)[16], uint16_t* act, uint16_t* tr, int mt, int nt,
+                                         int col, int half) {
+  const int node = 32 * nt + col;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int row = 32 * mt + 8 * j + 4 * half;
+    if (act) {
+      const uint2 q = {(uint32_t)v[4 * j] | ((uint32_t)v[4 * j + 1] << 16),
+                       (uint32_t)v[4 * j + 2] | ((uint32_t)v[4 * j + 3] << 16)};
+      *reinterpret_cast<uint2*>(act + node * LDS_PITCH + row) = q;
+    }
+    if (tr) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) tr[(row + q) * LDS_PITCH + node] = v[4 * j + q];
+    }
+  }
+}
+
+// One 32 x 32 tile of sum_n A[i][n] B[j][n] over the block's samples (row-major buffers).
+__device__ __forceinline__ f32x16 outer_tile(const uint16_t* A, const uint16_t* B, int mt, int nt, int col, int half) {
+  f32x16 acc = {0};
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load8(A + (32 * mt + col) * LDS_PITCH + 16 * ks + 8 * half),
+                                                  load8(B + (32 * nt + col) * LDS_PITCH + 16 * ks + 8 * half), acc, 0, 0, 0);
+  return acc;
+}
+
+// Sum over the block's samples of one row of a row-major buffer, in sample order.
+__device__ __forceinline__ float row_sum(const uint16_t* row) {
+  float s = 0.f;
+#pragma unroll
+  for (int n = 0; n < kGradRows; n += 8) {
+    const bf16x8 v = load8(row + n);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += (float)v[q];
+  }
+  return s;
+}
+
+__global__ __launch_bounds__(kGradThreads) void grad_kernel(const Packed* __restrict__ P,
+                                                            const float* __restrict__ x,
+                                                            const float* __restrict__ y,
+                                                            const int64_t* __restrict__ idx, int64_t batch,
+                                                            float* __restrict__ gpart,
+                                                            double* __restrict__ lpart) {
+  constexpr int BUF = 64 * LDS_PITCH;
+  // node-major: X then h2 then delta 1; h1 then delta 0 (and last, row-major, delta 2)
+  __shared__ __attribute__((aligned(16))) uint16_t A[BUF], B[BUF];
+  // row-major: the input, the hidden activations and the back-propagated deltas
+  __shared__ __attribute__((aligned(16))) uint16_t XT[BUF], H1T[BUF], H2T[BUF], D0T[BUF], D1T[BUF];
+  uint16_t* const D2T = B;
+  __shared__ float yn[kGradRows * N_OUT];       // normalised targets, then the residuals
   __shared__ float lsum[64];
-  uint16_t* D1 = D12;
-  uint16_t* D2 = D12 + 64 * LDS_PITCH;
-  // the normalised targets live in D1/D2 until the output layer has used them
-  float* yn = reinterpret_cast<float*>(D12);
-  static_assert(sizeof(D12) >= 64 * N_OUT * sizeof(float), "target staging does not fit");
-  const int lane = threadIdx.x;
-  const int64_t s = (int64_t)blockIdx.x * 64 + lane;
-  const bool live = s < batch;
-  const int64_t row = live ? idx[s] : 0;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int half = lane >> 5, col = lane & 31;
+  const int mt = wv >> 1, nt = wv & 1;          // this wavefront's tile of every product
+  const int64_t s0 = (int64_t)blockIdx.x * kGradRows;
+  const int live = (int)(batch - s0 < kGradRows ? batch - s0 : kGradRows);
   const float inv_count = 1.0f / (float)(batch * N_OUT);
-  {
-    float xr[N_IN];
-    for (int k = 0; k < N_IN; ++k) xr[k] = live ? x[row * N_IN + k] : 0.f;
-    put_features(P, xr, X + lane * LDS_PITCH);
-    for (int k = 0; k < N_OUT; ++k) yn[lane * N_OUT + k] = live ? y[row * N_OUT + k] / P->y_scale[k] : 0.f;
-    for (int k = 0; k < LDS_PITCH; ++k) D0[lane * LDS_PITCH + k] = 0;
+
+  // A wavefront reads 16 rows, a lane one column of each: the row's address is scalar and the
+  // column's normalisation constants are the lane's own.  Every load is unconditional (a
+  // padded sample or column reads a valid neighbour and is discarded below): behind a branch
+  // each one was waited for by itself (10.7 us for this phase; with per-lane row addresses 6.2).
+  constexpr int NR = kGradRows / 4;
+  const int r0 = NR * wv;
+  const int kx = min(lane, N_IN - 1), ky = min(lane, N_OUT - 1);
+  float xv[NR], yv[NR];
+#pragma unroll
+  for (int j = 0; j < NR; ++j) {
+    const int64_t row = idx[s0 + min(r0 + j, live - 1)];
+    xv[j] = (x + row * N_IN)[kx];
+    yv[j] = (y + row * N_OUT)[ky];
+  }
+  const float mean = P->x_mean[kx], iscale = P->x_iscale[kx], yscale = P->y_scale[ky];
+  WeightTile<K_IN> w1;
+  WeightTile<N_HID> w2, w3, w2t;
+  WeightTile<M_OUT> w3t;
+  w1.load(P->w1, mt, col, half);
+  w2.load(P->w2, mt, col, half);
+  w3.load(P->w3, mt, col, half);
+  w3t.load(P->w3t, mt, col, half);
+  w2t.load(P->w2t, mt, col, half);
+  f32x16 b1, b2, b3;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = 32 * mt + d_row(r, lane);
+    b1[r] = P->b1[row];
+    b2[r] = P->b2[row];
+    b3[r] = P->b3[row];
+  }
+  if (lane < K_IN) {
+#pragma unroll
+    for (int j = 0; j < NR; j += 2) {
+      uint32_t v[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const float xr = r0 + j + q < live ? xv[j + q] : 0.f;
+        v[q] = lane < N_IN ? to_bf16_bits((xr - mean) * iscale) : 0u;
+        A[(r0 + j + q) * LDS_PITCH + lane] = (uint16_t)v[q];
+      }
+      *reinterpret_cast<uint32_t*>(XT + lane * LDS_PITCH + r0 + j) = v[0] | (v[1] << 16);
+    }
+  }
+  if (lane < N_OUT) {
+#pragma unroll
+    for (int j = 0; j < NR; ++j) yn[(r0 + j) * N_OUT + lane] = r0 + j < live ? yv[j] / yscale : 0.f;
   }
   __syncthreads();
-  // forward
-  mfma_layer<N_HID, K_IN>(P->w1, P->b1, X, [&](int r, int n, float v) {
-    H1[n * LDS_PITCH + r] = bf16_bits(tanhf(v));
-  });
+
+  // forward; the hidden tiles stay in registers as the BF16 values the next layer sees
+  uint16_t h1[16], h2[16], d[16];
+  {
+    const f32x16 t = tile_product(w1, A, nt, col, half, b1);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) h1[r] = to_bf16_bits(tanhf(t[r]));
+    put_tile(h1, B, H1T, mt, nt, col, half);
+  }
   __syncthreads();
-  mfma_layer<N_HID, N_HID>(P->w2, P->b2, H1, [&](int r, int n, float v) {
-    H2[n * LDS_PITCH + r] = bf16_bits(tanhf(v));
-  });
+  {
+    const f32x16 t = tile_product(w2, B, nt, col, half, b2);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) h2[r] = to_bf16_bits(tanhf(t[r]));
+    put_tile(h2, A, H2T, mt, nt, col, half);
+  }
   __syncthreads();
-  float lacc = 0.f;
   // output layer and dL/do = 2 (o - y) / (batch * 41); padded samples contribute nothing
-  mfma_layer<M_OUT, N_HID>(P->w3, P->b3, H2, [&](int r, int n, float v) {
-    if (r < N_OUT && (int64_t)blockIdx.x * 64 + n < batch) {
-      const float d = v - yn[n * N_OUT + r];
-      lacc += d * d;
-      D0[n * LDS_PITCH + r] = bf16_bits(2.f * d * inv_count);
+  {
+    const f32x16 t = tile_product(w3, A, nt, col, half, b3);
+    const int node = 32 * nt + col;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = 32 * mt + d_row(r, lane);
+      const float res = t[r] - yn[node * N_OUT + min(row, N_OUT - 1)];
+      d[r] = row < N_OUT && node < live ? to_bf16_bits(2.f * res * inv_count) : (uint16_t)0;
+      if (row < N_OUT) yn[node * N_OUT + row] = res;
     }
-  });
-  lsum[lane] = lacc;
+    put_tile(d, B, D0T, mt, nt, col, half);
+  }
   __syncthreads();
   // back through the hidden layers (transposed weights), tanh' = 1 - h^2
-  mfma_layer<N_HID, M_OUT>(P->w3t, P->zero, D0, [&](int r, int n, float v) {
-    const float h = bf16_float(H2[n * LDS_PITCH + r]);
-    D1[n * LDS_PITCH + r] = bf16_bits(v * (1.f - h * h));
-  });
+  {
+    const f32x16 zero = {0};
+    const f32x16 t = tile_product(w3t, B, nt, col, half, zero);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float h = bf16_float(h2[r]);
+      d[r] = to_bf16_bits(t[r] * (1.f - h * h));
+    }
+    put_tile(d, A, D1T, mt, nt, col, half);
+  }
   __syncthreads();
-  mfma_layer<N_HID, N_HID>(P->w2t, P->zero, D1, [&](int r, int n, float v) {
-    const float h = bf16_float(H1[n * LDS_PITCH + r]);
-    D2[n * LDS_PITCH + r] = bf16_bits(v * (1.f - h * h));
-  });
+  {
+    const f32x16 zero = {0};
+    const f32x16 t = tile_product(w2t, A, nt, col, half, zero);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float h = bf16_float(h1[r]);
+      d[r] = to_bf16_bits(t[r] * (1.f - h * h));
+    }
+    put_tile(d, nullptr, D2T, mt, nt, col, half);
+  }
   __syncthreads();
   // weight gradients: sums over the block's samples of outer products
   float* g = gpart + (int64_t)blockIdx.x * N_PARAMS;
@@ -202,24 +320,44 @@ __global__ __launch_bounds__(64) void grad_kernel(const Packed* __restrict__ P,
   float* gb2 = gW2 + N_HID * N_HID;
   float* gW3 = gb2 + N_HID;
   float* gb3 = gW3 + N_OUT * N_HID;
-  outer_over_nodes(D2, X, [&](int i, int j, float v) { if (j < N_IN) gW1[i * N_IN + j] = v; });
-  outer_over_nodes(D1, H1, [&](int i, int j, float v) { gW2[i * N_HID + j] = v; });
-  outer_over_nodes(D0, H2, [&](int i, int j, float v) { if (i < N_OUT) gW3[i * N_HID + j] = v; });
-  {
-    float a = 0.f, b = 0.f, c = 0.f;
-    for (int n = 0; n < 64; ++n) {
-      a += bf16_float(D2[n * LDS_PITCH + lane]);
-      b += bf16_float(D1[n * LDS_PITCH + lane]);
-      c += bf16_float(D0[n * LDS_PITCH + lane]);
-    }
-    gb1[lane] = a;
-    gb2[lane] = b;
-    if (lane < N_OUT) gb3[lane] = c;
+  const int j = 32 * nt + col;
+  const f32x16 t1 = outer_tile(D2T, XT, mt, nt, col, half);
+  const f32x16 t2 = outer_tile(D1T, H1T, mt, nt, col, half);
+  const f32x16 t3 = outer_tile(D0T, H2T, mt, nt, col, half);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int i = 32 * mt + d_row(r, lane);
+    if (j < N_IN) gW1[i * N_IN + j] = t1[r];
+    gW2[i * N_HID + j] = t2[r];
+    if (i < N_OUT) gW3[i * N_HID + j] = t3[r];
   }
-  if (lane == 0) {
-    double t = 0.0;
-    for (int n = 0; n < 64; ++n) t += (double)lsum[n];
-    lpart[blockIdx.x] = t;
+  if (wv == 0) {
+    // the partial loss: each lane its residuals in tile order, then the lanes in order
+    float lacc = 0.f;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = 32 * a + d_row(r, lane), node = 32 * b + col;
+          const float res = yn[node * N_OUT + min(row, N_OUT - 1)];
+          lacc = row < N_OUT && node < live ? fma_c(res, res, lacc) : lacc;
+        }
+    lsum[lane] = lacc;
+    if (lane == 0) {
+      double t = 0.0;
+#pragma unroll
+      for (int n = 0; n < 64; ++n) t += (double)lsum[n];
+      lpart[blockIdx.x] = t;
+    }
+  } else if (wv == 1) {
+    gb1[lane] = row_sum(D2T + lane * LDS_PITCH);
+  } else if (wv == 2) {
+    gb2[lane] = row_sum(D1T + lane * LDS_PITCH);
+  } else {
+    const float c = row_sum(D0T + lane * LDS_PITCH);
+    if (lane < N_OUT) gb3[lane] = c;
   }
 }
 
@@ -228,7 +366,7 @@ __global__ __launch_bounds__(64) void grad_kernel(const Packed* __restrict__ P,
 // and the block's 16 wavefronts take every 16th row, eight loads in flight each; their sums
 // are added in wavefront order.  One more block sums the losses.  Bound by the latency of a
 // few loads and the 10 MB of partials at 16 384 rows (from L2): one thread per parameter
-// walking all 256 rows had 39 blocks in flight and took 76 us.
+// walking all 256 rows had 39 blocks in flight; 76 -> 4.1 us at 16 384 rows.
 constexpr int kReduceSlices = 16;
 constexpr int kReduceBlocks = (N_PARAMS + 63) / 64;
 
@@ -453,7 +591,7 @@ hipError_t mlp_launch_grad(const void* packed, const float* x, const float* y, c
                            int64_t batch, float* gpart, double* lpart, float* grad, double* loss,
                            hipStream_t st) {
   const int64_t blocks = (batch + 63) / 64;
-  hipLaunchKernelGGL(mlp::grad_kernel, dim3((unsigned)blocks), dim3(64), 0, st,
+  hipLaunchKernelGGL(mlp::grad_kernel, dim3((unsigned)blocks), dim3(mlp::kGradThreads), 0, st,
                      (const mlp::Packed*)packed, x, y, idx, batch, gpart, lpart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
