@@ -225,6 +225,50 @@ def test_normalisation_matches_oracle():
     np.testing.assert_allclose(got[94:], ref[2], rtol=1e-6)
 
 
+@pytest.mark.parametrize("start", [0, 1])                 # rows starting on a 16-byte boundary, and not
+@pytest.mark.parametrize("rows", [1, 3, 4, 1027, 40001])
+def test_normalisation_edges_match_oracle(rows, start):
+    # row counts around the runs of four rows a block reads, and fewer rows than blocks
+    rng = np.random.default_rng(100 * rows + start)
+    x = rng.standard_normal((rows + start, 47)) * rng.uniform(0.1, 3, 47) + rng.uniform(-1, 1, 47)
+    y = rng.standard_normal((rows + start, 41)) * 1e-4
+    xd, yd = t32(x)[start:], t32(y)[start:]
+    norm = torch.empty(135, dtype=torch.float32, device=DEV)
+    work = torch.empty(stgv.lbm_mlp_norm_work_bytes(), dtype=torch.uint8, device=DEV)
+    stgv.lbm_mlp_norm(xd, yd, rows, norm, work, stream())
+    ref = L.norm_from_data(x[start:].astype(np.float32), y[start:].astype(np.float32))
+    got = norm.cpu().numpy().astype(np.float64)
+    np.testing.assert_allclose(got[:47], ref[0], rtol=1e-6, atol=1e-7)
+    np.testing.assert_allclose(got[47:94], ref[1], rtol=1e-4)
+    np.testing.assert_allclose(got[94:], ref[2], rtol=1e-6)
+
+
+@pytest.mark.parametrize("batch", [1, 63, 64, 65, 1100])
+def test_gradient_edges_match_oracle(batch):
+    # batches around the 64 samples of a block, and more blocks than a reduction slice
+    rng = np.random.default_rng(batch)
+    theta = L.init_params(4) + 0.01 * rng.standard_normal(L.N_PARAMS)
+    norm = random_norm(rng)
+    n = 700
+    x = rng.standard_normal((n, 47)) * 0.7 + norm[0]
+    y = rng.standard_normal((n, 41)) * norm[2]
+    idx = rng.integers(0, n, batch)
+    packed = packed_net(theta, norm)
+    grad = torch.empty(L.N_PARAMS, dtype=torch.float32, device=DEV)
+    loss = torch.empty(1, dtype=torch.float64, device=DEV)
+    work = torch.empty(stgv.lbm_mlp_grad_work_bytes(batch), dtype=torch.uint8, device=DEV)
+    stgv.lbm_mlp_grad(packed, t32(x), t32(y), torch.tensor(idx, dtype=torch.int64, device=DEV), batch,
+                      grad, loss, work, stream())
+    th32 = theta.astype(np.float32).astype(np.float64)
+    nrm32 = tuple(np.asarray(v, np.float64).astype(np.float32).astype(np.float64) for v in norm)
+    xf, yf = (a.astype(np.float32).astype(np.float64)[idx] for a in (x, y))
+    bgrad, bound, bloss = bf16_bounds(th32, xf, nrm32, yf)
+    err = np.abs(grad.cpu().numpy().astype(np.float64) - bgrad)
+    print(f"\nbatch {batch}: error / bound max {np.max(err / bound):.3f}")
+    assert np.all(err <= bound), (int(np.argmax(err / bound)), float(np.max(err / bound)))
+    assert abs(loss.item() - bloss) < 0.02 * bloss
+
+
 @pytest.mark.parametrize("forcing", ["guo", "shift"])
 def test_restriction_matches_oracle(forcing):
     kwf = dict(n=32, forcing=forcing, u0=0.05, re=200.0, fr=0.5, sc=0.7, g_over_n=0.5,
