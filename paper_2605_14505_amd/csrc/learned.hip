@@ -2,6 +2,9 @@
 // pairs, the network's forward / backward / Adam kernels on BF16 MFMA.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "learned.hpp"
 #include "lbm_device.hpp"
 #include "mlp_device.hpp"
@@ -78,31 +81,150 @@ __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ the
   }
 }
 
-// Normalised features of one row into an LDS activation row (BF16, zero padded to 64).
-__device__ __forceinline__ void put_features(const Packed* P, const float* x, uint16_t* row) {
-  for (int k = 0; k < 64; ++k)
-    row[k] = k < N_IN ? bf16_bits((x[k] - P->x_mean[k]) * P->x_iscale[k]) : (uint16_t)0;
-}
+// V floats read or written at once.
+template <int V> struct FloatPiece { typedef float type __attribute__((ext_vector_type(V))); };
+template <> struct FloatPiece<1> { typedef float type; };
+
+// A operand of a 32-row tile of W [rows][KW]: all k-steps of the lane's row.
+template <int KW>
+struct WeightTile {
+  bf16x8 v[KW / 16];
+  __device__ __forceinline__ void load(const uint16_t* W, int mt, int col, int half) {
+#pragma unroll
+    for (int ks = 0; ks < KW / 16; ++ks) v[ks] = load8(W + (32 * mt + col) * KW + 16 * ks + 8 * half);
+  }
+};
 
 // ---------------------------------------------------------------------------
-// batch inference: rows of raw features -> de-normalised moment corrections
-// one wavefront (64 rows) per block
+// Batch inference: rows of raw features -> de-normalised moment corrections.
+//
+// A wavefront takes tiles of 32 rows.  A tile's 6 KB of features are contiguous: they come
+// in by 16-byte pieces and go through the wavefront's LDS buffer to the lanes that hold each
+// row's MFMA operand; the same buffer then carries the hidden activations from a layer's
+// result layout to the next one's operand layout, and last the outputs, stored contiguously
+// again.  The weights sit in LDS, once per block.  Bound by VALU issue, most of it the 128
+// tanh per row: 262 144 rows 113 -> 31.5 us (one 64-row wavefront per block had read its rows
+// one lane per row and run tanhf's two branches per value).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void forward_kernel(const Packed* __restrict__ P,
-                                                     const float* __restrict__ x, int64_t rows,
-                                                     float* __restrict__ y) {
-  __shared__ __attribute__((aligned(16))) uint16_t xs[64 * LDS_PITCH];
-  __shared__ __attribute__((aligned(16))) uint16_t hs[64 * LDS_PITCH];
-  __shared__ float os[64 * N_OUT];
-  const int lane = threadIdx.x;
-  const int64_t row = (int64_t)blockIdx.x * 64 + lane;
-  float xr[N_IN];
-  for (int k = 0; k < N_IN; ++k) xr[k] = row < rows ? x[row * N_IN + k] : 0.f;
-  put_features(P, xr, xs + lane * LDS_PITCH);
+constexpr int kInferThreads = 256, kInferRows = 32;
+constexpr int kInferBlocks = 3 * 256;                  // three resident blocks per CU
+constexpr int kInferBuf = kInferRows * N_IN;          // floats per wavefront: 6016 B
+static_assert(kInferRows * LDS_PITCH * 2 <= kInferBuf * 4 && kInferRows * N_OUT <= kInferBuf,
+              "activations and outputs share the feature buffer");
+
+// Orders the wavefront's own LDS writes before its later reads of other lanes' values.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// `count` (at most MAX) contiguous floats from src to dst, every load ahead of the first
+// store, in pieces of V floats; V = 4 wants count = MAX and 16-byte alignment of both ends.
+template <int V, int MAX>
+__device__ __forceinline__ void wave_copy(float* dst, const float* src, int lane, int count) {
+  using Piece = typename FloatPiece<V>::type;
+  constexpr int iters = (MAX / V + 63) / 64;
+  Piece p[iters];
+#pragma unroll
+  for (int j = 0; j < iters; ++j) p[j] = *reinterpret_cast<const Piece*>(src + min(V * (lane + 64 * j), count - V));
+#pragma unroll
+  for (int j = 0; j < iters; ++j) {
+    const int e = V * (lane + 64 * j);
+    if (e < count) *reinterpret_cast<Piece*>(dst + e) = p[j];
+  }
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kInferThreads) void forward_kernel(const Packed* __restrict__ P,
+                                                                const float* __restrict__ x, int64_t rows,
+                                                                float* __restrict__ y) {
+  __shared__ __attribute__((aligned(16))) float buf_all[kInferThreads / 64][kInferBuf];
+  __shared__ __attribute__((aligned(16))) uint16_t w1[N_HID * K_IN], w2[N_HID * N_HID], w3[M_OUT * N_HID];
+  __shared__ float mean[K_IN], iscale[K_IN], b1[N_HID], b2[N_HID], b3[M_OUT], y_scale[M_OUT];
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int e = 8 * tid; e < N_HID * K_IN; e += 8 * kInferThreads) *reinterpret_cast<bf16x8*>(w1 + e) = load8(P->w1 + e);
+  for (int e = 8 * tid; e < N_HID * N_HID; e += 8 * kInferThreads) {
+    *reinterpret_cast<bf16x8*>(w2 + e) = load8(P->w2 + e);
+    *reinterpret_cast<bf16x8*>(w3 + e) = load8(P->w3 + e);
+  }
+  if (tid < K_IN) { mean[tid] = P->x_mean[tid]; iscale[tid] = P->x_iscale[tid]; }
+  if (tid < N_HID) { b1[tid] = P->b1[tid]; b2[tid] = P->b2[tid]; b3[tid] = P->b3[tid]; y_scale[tid] = P->y_scale[tid]; }
   __syncthreads();
-  mlp_forward_wave(P, xs, hs, os);
-  if (row < rows)
-    for (int k = 0; k < N_OUT; ++k) y[row * N_OUT + k] = os[lane * N_OUT + k];
+
+  float* const buf = buf_all[wv];
+  uint16_t* const act = reinterpret_cast<uint16_t*>(buf);
+  const int64_t tiles = (rows + kInferRows - 1) / kInferRows, step = (int64_t)gridDim.x * (kInferThreads / 64);
+  for (int64_t t = (int64_t)blockIdx.x * (kInferThreads / 64) + wv; t < tiles; t += step) {
+    const int live = (int)(rows - t * kInferRows < kInferRows ? rows - t * kInferRows : kInferRows);
+    const bool vec = VEC && live == kInferRows;       // a partial tile goes by single floats
+    if (vec) wave_copy<4, kInferBuf>(buf, x + t * kInferBuf, lane, kInferBuf);
+    else wave_copy<1, kInferBuf>(buf, x + t * kInferBuf, lane, live * N_IN);
+    wave_lds_sync();
+    bf16x8 op[4];
+    {
+      const int r = min(col, live - 1);
+#pragma unroll
+      for (int ks = 0; ks < K_IN / 16; ++ks) {
+        uint4 q;
+        uint32_t* w = reinterpret_cast<uint32_t*>(&q);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const int k = 16 * ks + 8 * half + 2 * p;
+          const float v0 = (buf[r * N_IN + k] - mean[k]) * iscale[k];
+          const float v1 = k + 1 < N_IN ? (buf[r * N_IN + min(k + 1, N_IN - 1)] - mean[k + 1]) * iscale[k + 1] : 0.f;
+          w[p] = to_bf16_pair(v0, v1);
+        }
+        op[ks] = __builtin_bit_cast(bf16x8, q);
+      }
+    }
+    wave_lds_sync();
+    // one layer: both 32-row tiles from the operand registers, results handed to emit(mt, j, 4 values)
+    auto layer = [&](const uint16_t* W, const float* bias, auto kw, auto emit) {
+      constexpr int KW = decltype(kw)::value;
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = bias[32 * mt + d_row(r, lane)];
+        WeightTile<KW> w;
+        w.load(W, mt, col, half);
+#pragma unroll
+        for (int ks = 0; ks < KW / 16; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w.v[ks], op[ks], acc, 0, 0, 0);
+        emit(mt, acc);
+      }
+    };
+    auto to_act = [&](int mt, const f32x16& acc) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint2 q = {tanh_bf16_pair(acc[4 * j], acc[4 * j + 1]), tanh_bf16_pair(acc[4 * j + 2], acc[4 * j + 3])};
+        *reinterpret_cast<uint2*>(act + col * LDS_PITCH + 32 * mt + 8 * j + 4 * half) = q;
+      }
+    };
+    auto from_act = [&] {
+      wave_lds_sync();
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) op[ks] = load8(act + col * LDS_PITCH + 16 * ks + 8 * half);
+      wave_lds_sync();
+    };
+    layer(w1, b1, std::integral_constant<int, K_IN>{}, to_act);
+    from_act();
+    layer(w2, b2, std::integral_constant<int, N_HID>{}, to_act);
+    from_act();
+    layer(w3, b3, std::integral_constant<int, N_HID>{}, [&](int mt, const f32x16& acc) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = 32 * mt + d_row(r, lane);
+        if (row < N_OUT) buf[col * N_OUT + row] = acc[r] * y_scale[row];
+      }
+    });
+    wave_lds_sync();
+    float* dst = y + t * (kInferRows * N_OUT);
+    if (vec) wave_copy<4, kInferRows * N_OUT>(dst, buf, lane, kInferRows * N_OUT);
+    else wave_copy<1, kInferRows * N_OUT>(dst, buf, lane, live * N_OUT);
+    wave_lds_sync();
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -121,19 +243,6 @@ __global__ __launch_bounds__(64) void forward_kernel(const Packed* __restrict__ 
 // value at a time).
 // ---------------------------------------------------------------------------
 constexpr int kGradRows = 64, kGradThreads = 256;
-
-// Round to nearest even with gfx950's own conversion (bf16_bits without its integer steps).
-__device__ __forceinline__ uint16_t to_bf16_bits(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
-
-// A operand of a 32-row tile of W [rows][KW]: all k-steps of the lane's row.
-template <int KW>
-struct WeightTile {
-  bf16x8 v[KW / 16];
-  __device__ __forceinline__ void load(const uint16_t* __restrict__ W, int mt, int col, int half) {
-#pragma unroll
-    for (int ks = 0; ks < KW / 16; ++ks) v[ks] = load8(W + (32 * mt + col) * KW + 16 * ks + 8 * half);
-  }
-};
 
 // acc + W tile x the 32 nodes at `nt` of a node-major buffer
 template <int KW>
@@ -264,14 +373,22 @@ __global__ __launch_bounds__(kGradThreads) void grad_kernel(const Packed* __rest
   {
     const f32x16 t = tile_product(w1, A, nt, col, half, b1);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) h1[r] = to_bf16_bits(tanhf(t[r]));
+    for (int r = 0; r < 16; r += 2) {
+      const uint32_t q = tanh_bf16_pair(t[r], t[r + 1]);
+      h1[r] = (uint16_t)q;
+      h1[r + 1] = (uint16_t)(q >> 16);
+    }
     put_tile(h1, B, H1T, mt, nt, col, half);
   }
   __syncthreads();
   {
     const f32x16 t = tile_product(w2, B, nt, col, half, b2);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) h2[r] = to_bf16_bits(tanhf(t[r]));
+    for (int r = 0; r < 16; r += 2) {
+      const uint32_t q = tanh_bf16_pair(t[r], t[r + 1]);
+      h2[r] = (uint16_t)q;
+      h2[r + 1] = (uint16_t)(q >> 16);
+    }
     put_tile(h2, A, H2T, mt, nt, col, half);
   }
   __syncthreads();
@@ -428,8 +545,6 @@ __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, fl
 constexpr int NSTAT = 2 * N_IN + N_OUT;    // sum x, sum x^2, sum y^2
 constexpr int kStatsThreads = 1024;
 
-template <int V> struct FloatPiece { typedef float type __attribute__((ext_vector_type(V))); };
-template <> struct FloatPiece<1> { typedef float type; };
 template <int V>
 __device__ __forceinline__ float piece_at(const typename FloatPiece<V>::type& p, int j) {
   if constexpr (V == 1) return p;
@@ -650,9 +765,14 @@ hipError_t mlp_launch_pack(const float* theta, const float* norm, void* packed, 
 }
 
 hipError_t mlp_launch_forward(const void* packed, const float* x, int64_t rows, float* y, hipStream_t st) {
-  const int64_t blocks = (rows + 63) / 64;
-  hipLaunchKernelGGL(mlp::forward_kernel, dim3((unsigned)blocks), dim3(64), 0, st,
-                     (const mlp::Packed*)packed, x, rows, y);
+  const int64_t tiles = (rows + mlp::kInferRows - 1) / mlp::kInferRows, waves = mlp::kInferThreads / 64;
+  const int64_t blocks = std::min<int64_t>((tiles + waves - 1) / waves, mlp::kInferBlocks);
+  if (((uintptr_t)x | (uintptr_t)y) % 16 == 0)        // a whole tile of either starts on 16 bytes
+    hipLaunchKernelGGL(mlp::forward_kernel<true>, dim3((unsigned)blocks), dim3(mlp::kInferThreads), 0, st,
+                       (const mlp::Packed*)packed, x, rows, y);
+  else
+    hipLaunchKernelGGL(mlp::forward_kernel<false>, dim3((unsigned)blocks), dim3(mlp::kInferThreads), 0, st,
+                       (const mlp::Packed*)packed, x, rows, y);
   return hipGetLastError();
 }
 

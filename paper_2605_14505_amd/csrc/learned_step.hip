@@ -79,13 +79,6 @@ __device__ __forceinline__ void split_bf16(float v, __bf16& hi, __bf16& lo) {
   lo = to_bf16(v - (float)hi);
 }
 
-// tanh x = 1 - 2 / (1 + e^(2x)) with the hardware exp2 and reciprocal: absolute error
-// ~1e-7, far below the BF16 rounding (2^-9 relative) the activation goes through next.
-// Saturates to +-1 for large |x| (e^(2x) -> inf or 0).
-__device__ __forceinline__ float fast_tanh(float x) {
-  return 1.f - 2.f * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(2.8853900817779268f * x));
-}
-
 // direction data of population p (global index: f_i = i, g_j = 27 + j; -1: none)
 struct Dir {
   int ex, ey, ez, opp;
@@ -132,7 +125,8 @@ __device__ __forceinline__ float analytic_feature(int k, const NodeMacro<float>&
 }
 constexpr bool is_analytic(int k) { return k < NCF || k == 27 || k == N_IN - 1; }
 
-// tanh of the 16 results of a tile into two 8-wide B operands
+// tanh of the 16 results of a tile into two 8-wide B operands (the fast form's error, ~2e-7,
+// is far below the BF16 rounding, 2^-9 relative, the activation goes through next)
 __device__ __forceinline__ void tanh_to_b(const f32x16& t, bf16x8& lo8, bf16x8& hi8) {
 #pragma unroll
   for (int q = 0; q < 8; ++q) {

@@ -274,7 +274,7 @@ __device__ __forceinline__ uint16_t bf16_bits(float v) {   // round to nearest e
 }
 __device__ __forceinline__ float bf16_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
-// Activation buffers in LDS hold 64 nodes (one wavefront) x up to 64 values,
+// Activation buffers in LDS hold a wavefront's or block's nodes x up to 64 values,
 // node-major, rows padded to 72 entries to spread the 16-byte operand reads
 // over the LDS banks.
 constexpr int LDS_PITCH = 72;
@@ -288,51 +288,31 @@ __device__ __forceinline__ bf16x8 load8(const uint16_t* p) {   // 16-byte aligne
   return *reinterpret_cast<const bf16x8*>(p);
 }
 
-// out^T = W act^T for the 64 nodes of this wavefront: W is [MROWS][KW] row-major
-// in global memory, act is LDS [node][LDS_PITCH] (k < KW used); the result for
-// (row, node) is handed to emit(row, node, value) with the bias added.
-template <int MROWS, int KW, typename Emit>
-__device__ __forceinline__ void mfma_layer(const uint16_t* __restrict__ W, const float* __restrict__ bias,
-                                           const uint16_t* act, Emit emit) {
-  const int lane = threadIdx.x & 63;
-  const int half = lane >> 5, col = lane & 31;
-#pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-#pragma unroll
-    for (int mt = 0; mt < MROWS / 32; ++mt) {
-      f32x16 acc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = bias[32 * mt + d_row(r, lane)];
-#pragma unroll
-      for (int ks = 0; ks < KW / 16; ++ks) {
-        const bf16x8 a = load8(W + (32 * mt + col) * KW + 16 * ks + 8 * half);
-        const bf16x8 b = load8(act + (32 * nt + col) * LDS_PITCH + 16 * ks + 8 * half);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) emit(32 * mt + d_row(r, lane), 32 * nt + col, acc[r]);
-    }
-  }
+// Round to nearest even with gfx950's own conversion (bf16_bits without its integer steps).
+__device__ __forceinline__ uint16_t to_bf16_bits(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
+__device__ __forceinline__ uint32_t to_bf16_pair(float a, float b) {
+  return (uint32_t)to_bf16_bits(a) | ((uint32_t)to_bf16_bits(b) << 16);
 }
 
-// The network on the 64 node feature rows in LDS buffer x (normalised, BF16,
-// columns 47.. zero).  h is a second LDS buffer; the de-normalised outputs
-// go to o[node * N_OUT + k] (LDS, FP32).  Every wavefront of the block must call
-// it (it synchronises the block between layers).
-__device__ __forceinline__ void mlp_forward_wave(const Packed* __restrict__ P, uint16_t* x, uint16_t* h,
-                                                 float* o) {
-  mfma_layer<N_HID, K_IN>(P->w1, P->b1, x, [&](int row, int node, float v) {
-    h[node * LDS_PITCH + row] = bf16_bits(tanhf(v));
-  });
-  __syncthreads();
-  mfma_layer<N_HID, N_HID>(P->w2, P->b2, h, [&](int row, int node, float v) {
-    x[node * LDS_PITCH + row] = bf16_bits(tanhf(v));
-  });
-  __syncthreads();
-  mfma_layer<M_OUT, N_HID>(P->w3, P->b3, x, [&](int row, int node, float v) {
-    if (row < N_OUT) o[node * N_OUT + row] = v * P->y_scale[row];
-  });
-  __syncthreads();
+// tanh x = 1 - 2 / (1 + e^(2x)) with the hardware exp2 and reciprocal: absolute error
+// ~2e-7 (2.4e-7 from tanhf, the largest over every FP32 argument).  Saturates to +-1 for
+// large |x| (e^(2x) -> inf or 0).
+__device__ __forceinline__ float fast_tanh(float x) {
+  return 1.f - 2.f * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(2.8853900817779268f * x));
+}
+
+// tanhf of two values, rounded to BF16 and packed.  The fast form is within kTanhBound of
+// tanhf, so unless a BF16 rounding boundary lies within that distance of it both round to
+// the same value; the few lanes where one does (about 6e-4 of them for activations of order
+// one) take tanhf itself.  The result is tanhf's, bit for bit, over every FP32 argument; the
+// fast form costs a third of tanhf's two-branch code.
+constexpr float kTanhBound = 3.6e-7f;
+__device__ __forceinline__ uint32_t tanh_bf16_pair(float a, float b) {
+  const float ta = fast_tanh(a), tb = fast_tanh(b);
+  const uint32_t lo = to_bf16_pair(ta - kTanhBound, tb - kTanhBound);
+  const uint32_t hi = to_bf16_pair(ta + kTanhBound, tb + kTanhBound);
+  if (__builtin_expect(lo != hi, 0)) return to_bf16_pair(tanhf(a), tanhf(b));
+  return lo;
 }
 
 }  // namespace mlp

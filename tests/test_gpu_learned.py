@@ -160,6 +160,29 @@ def test_forward_matches_oracle(rows):
     assert np.all(err <= bound), np.unravel_index(np.argmax(err / bound), err.shape)
 
 
+@pytest.mark.parametrize("rows,start", [(32, 0), (33, 0), (31, 1), (64, 1), (98400, 0), (98337, 3)])
+def test_forward_edges_match_oracle(rows, start):
+    # whole and partial tiles of 32 rows, rows starting off a 16-byte boundary, and more tiles
+    # than the launch has wavefronts; small and large pre-activations (zero, saturated)
+    rng = np.random.default_rng(rows)
+    theta = L.init_params(1) + 0.01 * rng.standard_normal(L.N_PARAMS)
+    norm = random_norm(rng)
+    x = rng.standard_normal((rows + start, 47)) * 0.5 * 10.0 ** rng.uniform(-4, 1.5, (rows + start, 1)) + norm[0]
+    packed = packed_net(theta, norm)
+    y = torch.full((rows + start + 1, 41), 7.0, dtype=torch.float32, device=DEV)
+    stgv.lbm_mlp_forward(packed, t32(x)[start:], rows, y[start:], stream())
+    th32 = theta.astype(np.float32).astype(np.float64)
+    nrm32 = tuple(np.asarray(v, np.float64).astype(np.float32).astype(np.float64) for v in norm)
+    keep = np.unique(np.concatenate([np.arange(min(rows, 70)), np.arange(max(0, rows - 70), rows),
+                                     rng.integers(0, rows, 400)]))
+    bref, bound = bf16_bounds(th32, x.astype(np.float32).astype(np.float64)[start:][keep], nrm32)
+    got = y.cpu().numpy().astype(np.float64)
+    assert np.all(got[:start] == 7.0) and np.all(got[start + rows:] == 7.0)      # nothing else written
+    err = np.abs(got[start:start + rows][keep] - bref)
+    print(f"\nforward rows={rows}: error / bound max {np.max(err / bound):.3f}")
+    assert np.all(err <= bound), np.unravel_index(np.argmax(err / bound), err.shape)
+
+
 def test_gradient_and_loss_match_oracle():
     rng = np.random.default_rng(5)
     theta = L.init_params(2) + 0.01 * rng.standard_normal(L.N_PARAMS)
