@@ -652,24 +652,64 @@ __global__ __launch_bounds__(64) void norm_kernel(const double* __restrict__ par
 
 // ---------------------------------------------------------------------------
 // restriction of a fine D3Q27 x D3Q19 state to the coarse grid (ratio 4)
+//
+// The filter is separable.  A lane holds one fine x and sums its 5 x 5 rows of a coarse
+// (Y, Z) over y and z (the 46 populations and their 46 non-equilibrium parts, in registers);
+// the five x of a coarse node are then added through LDS.  Every row is read in whole lines
+// and each fine node's equilibria are formed 25 / 16 times, against 125 / 64 strided reads
+// and evaluations when a thread walked its coarse node's whole 5^3 stencil.
+//
+// A block is 256 lanes: with n <= 256 whole fine rows of 256 / n neighbouring Y (the x sums
+// wrap around in LDS), else the row segment of kRestrictX coarse nodes and the halo of two
+// fine nodes on its left and right.
 // ---------------------------------------------------------------------------
+constexpr int kRestrictThreads = 256, kRestrictChunk = 23;     // 92 sums go through LDS in four chunks
+constexpr int kRestrictX = (kRestrictThreads - 1) / 4;         // 63 coarse nodes need 4 x 63 + 1 fine ones
+
+struct RestrictShape {
+  int rows;     // coarse rows (Y) of a block
+  int xseg;     // coarse nodes of a block's row segment
+  int segs;     // segments of a row
+};
+__host__ __device__ inline RestrictShape restrict_shape(int nc) {
+  const int n = 4 * nc;
+  if (n <= kRestrictThreads) return {kRestrictThreads / n, nc, 1};
+  return {1, kRestrictX, (nc + kRestrictX - 1) / kRestrictX};
+}
+
 template <typename T, int MODE>
-__global__ __launch_bounds__(256) void restrict_kernel(const T* __restrict__ fine, Geometry gf,
-                                                       PhysConsts cf, int nc, float sf, float sg,
-                                                       float* __restrict__ out) {
-  const int64_t nc3 = (int64_t)nc * nc * nc;
-  const int64_t J = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (J >= nc3) return;
-  const int X = (int)(J % nc), Y = (int)((J / nc) % nc), Z = (int)(J / ((int64_t)nc * nc));
-  const int n = gf.n;
+__global__ __launch_bounds__(kRestrictThreads) void restrict_kernel(const T* __restrict__ fine, Geometry gf,
+                                                                    PhysConsts cf, int nc, float sf, float sg,
+                                                                    float* __restrict__ out) {
+  constexpr int NV = 2 * (27 + 19);
+  static_assert(NV % kRestrictChunk == 0, "chunks of equal size");
+  __shared__ float xs[kRestrictChunk][kRestrictThreads];
+  const int n = gf.n, t = threadIdx.x;
+  const RestrictShape sh = restrict_shape(nc);
+  const bool ring = sh.segs == 1;
+  const int Z = blockIdx.z, Y0 = blockIdx.y * sh.rows, X0 = blockIdx.x * sh.xseg;
+  const int width = ring ? n : kRestrictThreads;
+  const int yy = t / width, l = t % width;
+  const int Y = Y0 + yy;
+  int x = ring ? l : 4 * X0 - 2 + l;
+  x += x < 0 ? n : 0;
+  x -= x >= n ? n : 0;
   auto wf = [](int d) { return (d == -2 || d == 2) ? 0.125f : 0.25f; };   // [1,2,2,2,1] / 8
-  float fb[27] = {0}, gb[19] = {0}, fn[27] = {0}, gn[19] = {0};
-  for (int dz = -2; dz <= 2; ++dz)
-    for (int dy = -2; dy <= 2; ++dy)
-      for (int dx = -2; dx <= 2; ++dx) {
-        const int x = (4 * X + dx + n) % n, y = (4 * Y + dy + n) % n, z = (4 * Z + dz + n) % n;
-        const float w = wf(dx) * wf(dy) * wf(dz);
-        const NodeIndex ix = make_index(x, y, z, n);
+  auto wrap = [n](int v) { return v < 0 ? v + n : (v >= n ? v - n : v); };
+  float a[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) a[k] = 0.f;
+  if (yy < sh.rows && Y < nc && (ring || x < n)) {
+    // neighbouring Y sweep in opposite directions, so that the row they share is read by
+    // both at the same time
+    const int dir = (Y & 1) ? -1 : 1;
+#pragma unroll 1
+    for (int dz = -2; dz <= 2; ++dz)
+#pragma unroll 1
+      for (int dyi = -2; dyi <= 2; ++dyi) {
+        const int dy = dir * dyi;
+        const float w = wf(dy) * wf(dz);
+        const NodeIndex ix = make_index(x, wrap(4 * Y + dy), wrap(4 * Z + dz), n);
         float f[27], g[19];
         gather<27, T, MODE>(f, fine, 0, ix, gf.stride);
         gather<19, T, MODE>(g, fine, 27, ix, gf.stride);
@@ -678,10 +718,36 @@ __global__ __launch_bounds__(256) void restrict_kernel(const T* __restrict__ fin
         m.vx = m.ux; m.vy = m.uy; m.vz = m.uz;           // equilibria at the physical velocity
         const Collision<27, 19, FORCE_GUO, float> col(cf, m);
 #pragma unroll
-        for (int i = 0; i < 27; ++i) { fb[i] += w * f[i]; fn[i] += w * (f[i] - col.feq(i)); }
+        for (int i = 0; i < 27; ++i) { a[i] += w * f[i]; a[46 + i] += w * (f[i] - col.feq(i)); }
 #pragma unroll
-        for (int j = 0; j < 19; ++j) { gb[j] += w * g[j]; gn[j] += w * (g[j] - col.geq(j)); }
+        for (int j = 0; j < 19; ++j) { a[27 + j] += w * g[j]; a[73 + j] += w * (g[j] - col.geq(j)); }
       }
+  }
+  // the five fine x of this thread's coarse node (threads q < rows * xseg)
+  const int cy = t / sh.xseg, cx = t % sh.xseg;
+  const bool coarse = cy < sh.rows && Y0 + cy < nc && X0 + cx < nc;
+  int at[5];
+#pragma unroll
+  for (int d = 0; d < 5; ++d) {
+    const int p = ring ? wrap(4 * cx + d - 2) : 4 * cx + d;
+    at[d] = coarse ? cy * width + p : 0;
+  }
+  float b[NV];
+#pragma unroll
+  for (int k0 = 0; k0 < NV; k0 += kRestrictChunk) {
+    if (k0) __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRestrictChunk; ++k) xs[k][t] = a[k0 + k];
+    __syncthreads();
+    if (coarse) {
+#pragma unroll
+      for (int k = 0; k < kRestrictChunk; ++k)
+        b[k0 + k] = 0.125f * (xs[k][at[0]] + xs[k][at[4]]) + 0.25f * (xs[k][at[1]] + xs[k][at[2]] + xs[k][at[3]]);
+    }
+  }
+  if (!coarse) return;
+  const int64_t nc3 = (int64_t)nc * nc * nc, J = X0 + cx + (int64_t)nc * (Y0 + cy + (int64_t)nc * Z);
+  const float *fb = b, *gb = b + 27, *fn = b + 46, *gn = b + 73;
   // non-conserved moments of the filtered non-equilibrium part, rescaled by (s - 1)
   float mf[27], mg[19];
 #pragma unroll
@@ -690,19 +756,19 @@ __global__ __launch_bounds__(256) void restrict_kernel(const T* __restrict__ fin
   for (int k = 0; k < 19; ++k) mg[k] = k < NCG ? 0.f : (sg - 1.f) * moment<19>(k, gn);
 #pragma unroll
   for (int i = 0; i < 27; ++i) {
-    float a = fb[i];
+    float v = fb[i];
 #pragma unroll
     for (int k = NCF; k < 27; ++k)
-      if (MINV_F.v[i][k] != 0.f) a += MINV_F.v[i][k] * mf[k];
-    out[i * nc3 + J] = a;
+      if (MINV_F.v[i][k] != 0.f) v += MINV_F.v[i][k] * mf[k];
+    out[i * nc3 + J] = v;
   }
 #pragma unroll
   for (int j = 0; j < 19; ++j) {
-    float a = gb[j];
+    float v = gb[j];
 #pragma unroll
     for (int k = NCG; k < 19; ++k)
-      if (MINV_G.v[j][k] != 0.f) a += MINV_G.v[j][k] * mg[k];
-    out[(27 + j) * nc3 + J] = a;
+      if (MINV_G.v[j][k] != 0.f) v += MINV_G.v[j][k] * mg[k];
+    out[(27 + j) * nc3 + J] = v;
   }
 }
 
@@ -813,12 +879,12 @@ hipError_t mlp_launch_norm(const float* x, const float* y, int64_t rows, double*
 template <typename T>
 static hipError_t restrict_t(const void* fine, int mode, Geometry gf, PhysConsts cf, int nc, float sf,
                              float sg, float* out, hipStream_t st) {
-  const int64_t nc3 = (int64_t)nc * nc * nc;
-  const dim3 grid((unsigned)((nc3 + 255) / 256));
+  const mlp::RestrictShape sh = mlp::restrict_shape(nc);
+  const dim3 grid((unsigned)sh.segs, (unsigned)((nc + sh.rows - 1) / sh.rows), (unsigned)nc), block(mlp::kRestrictThreads);
   if (mode == MODE_ODD)
-    hipLaunchKernelGGL((mlp::restrict_kernel<T, MODE_ODD>), grid, dim3(256), 0, st, (const T*)fine, gf, cf, nc, sf, sg, out);
+    hipLaunchKernelGGL((mlp::restrict_kernel<T, MODE_ODD>), grid, block, 0, st, (const T*)fine, gf, cf, nc, sf, sg, out);
   else
-    hipLaunchKernelGGL((mlp::restrict_kernel<T, MODE_EVEN>), grid, dim3(256), 0, st, (const T*)fine, gf, cf, nc, sf, sg, out);
+    hipLaunchKernelGGL((mlp::restrict_kernel<T, MODE_EVEN>), grid, block, 0, st, (const T*)fine, gf, cf, nc, sf, sg, out);
   return hipGetLastError();
 }
 
