@@ -165,27 +165,28 @@ __device__ __forceinline__ T* at_node(T* array, uint32_t node) {
 // Gather the pre-collision populations of one lattice (Q directions starting at
 // array `first`) in the layout given by MODE.  The direction is a compile-time index, so
 // the choice of load (cached or non-temporal) is fixed per direction.
-template <int Q, typename T, int MODE, bool NTX, int I, typename C>
+template <int Q, typename T, int MODE, bool NTX, bool CACHED, int I, typename C>
 __device__ __forceinline__ void gather_one(C* v, const T* pop, int first, const NodeIndex& ix,
                                            int64_t stride) {
   using S = Stencil<Q>;
   constexpr bool odd = MODE == MODE_ODD;   // post-collision value of x - e_i sits in slot opp(i)
-  constexpr bool nt = ((STGV_NT_LOAD_MODES >> MODE) & 1) != 0 ||
-                      (odd && NTX && STGV_NT_LOAD_ODD_XALIGNED && S::ex[I] == 0);
+  constexpr bool nt = !CACHED && (((STGV_NT_LOAD_MODES >> MODE) & 1) != 0 ||
+                                  (odd && NTX && STGV_NT_LOAD_ODD_XALIGNED && S::ex[I] == 0));
   const uint32_t off = odd ? ix.at(-S::ex[I], -S::ey[I], -S::ez[I]) : ix.base;
   const int slot = odd ? opp(I) : I;
   v[I] = load_as<C, nt>(at_node(pop + (int64_t)(first + slot) * stride, off));
 }
-template <int Q, typename T, int MODE, bool NTX, typename C, int... I>
+template <int Q, typename T, int MODE, bool NTX, bool CACHED, typename C, int... I>
 __device__ __forceinline__ void gather_seq(C* v, const T* pop, int first, const NodeIndex& ix,
                                            int64_t stride, std::integer_sequence<int, I...>) {
-  (gather_one<Q, T, MODE, NTX, I>(v, pop, first, ix, stride), ...);
+  (gather_one<Q, T, MODE, NTX, CACHED, I>(v, pop, first, ix, stride), ...);
 }
-// NTX: non-temporal loads for the odd step's x-aligned directions.
-template <int Q, typename T, int MODE, bool NTX = false, typename C>
+// NTX: non-temporal loads for the odd step's x-aligned directions.  CACHED: no
+// non-temporal loads, for kernels that read a node more than once.
+template <int Q, typename T, int MODE, bool NTX = false, bool CACHED = false, typename C>
 __device__ __forceinline__ void gather(C* v, const T* pop, int first, const NodeIndex& ix,
                                        int64_t stride) {
-  gather_seq<Q, T, MODE, NTX>(v, pop, first, ix, stride, std::make_integer_sequence<int, Q>{});
+  gather_seq<Q, T, MODE, NTX, CACHED>(v, pop, first, ix, stride, std::make_integer_sequence<int, Q>{});
 }
 
 // Scatter post-collision populations for MODE (AB writes into `dst`), one compile-time
