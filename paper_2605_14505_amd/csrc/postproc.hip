@@ -5,6 +5,8 @@
 // the blocks in a fixed order.
 #include "postproc.hpp"
 
+#include "lbm_device.hpp"
+
 #include <rocfft/rocfft.h>
 
 #include <cmath>
@@ -21,39 +23,52 @@ constexpr int kShellThreads = 256;
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 // One component's half spectrum c[(n/2 + 1) n n] (kx fastest): the Hermitian twins of
-// 0 < kx < n/2 are counted twice.  scale = 1 / (2 n^6 u0^2).
-__global__ __launch_bounds__(kShellThreads) void shell_kernel(const float2* __restrict__ c, int n,
-                                                              int nshell, double scale,
-                                                              double* __restrict__ partial) {
+// 0 < kx < n/2 are counted twice.  scale = 1 / (2 n^6 u0^2).  The grid-stride walk carries
+// (kx, ky, kz) along by adding the stride's own digits, so no element needs a division, and
+// the shell is taken in FP32: |k|^2 is an integer below 2^20, and the values next to a shell's
+// edge, (s - 1/2)^2 -+ 1/4 and 3/4, are 1e-4 or more away from it in |k|, twice the rounding.
+// Bound by reading c: 256^3 30 -> 20 us a component.  partial is [shell][block], so that
+// the reduction reads a shell's partials contiguously.
+struct Digits {
+  int kx, ky, kz;
+};
+
+__global__ __launch_bounds__(kShellThreads) void shell_kernel(const float2* __restrict__ c, int n, int nshell,
+                                                              double scale, double* __restrict__ partial,
+                                                              int parts, int part0) {
   extern __shared__ double hist[];
   for (int s = threadIdx.x; s < nshell; s += blockDim.x) hist[s] = 0.0;
   __syncthreads();
-  const int nh = n / 2 + 1;
-  const int64_t total = (int64_t)nh * n * n;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int kx = (int)(i % nh);
-    const int64_t r = i / nh;
-    const int ky0 = (int)(r % n), kz0 = (int)(r / n);
-    const int ky = ky0 <= n / 2 ? ky0 : ky0 - n;
-    const int kz = kz0 <= n / 2 ? kz0 : kz0 - n;
-    const double k = sqrt((double)kx * kx + (double)ky * ky + (double)kz * kz);
-    const int s = (int)floor(k + 0.5);
+  const int nh = n / 2 + 1, total = nh * n * n, step = gridDim.x * blockDim.x;
+  auto digits = [=](int i) { return Digits{i % nh, (i / nh) % n, i / nh / n}; };
+  const Digits d = digits(step);
+  int i = blockIdx.x * blockDim.x + threadIdx.x;
+  Digits k = digits(i);
+  for (; i < total; i += step) {
     const float2 v = c[i];
-    const double w = (kx == 0 || 2 * kx == n) ? 1.0 : 2.0;
-    atomicAdd(&hist[s], w * ((double)v.x * v.x + (double)v.y * v.y) * scale);
+    const int ky = k.ky <= n / 2 ? k.ky : k.ky - n, kz = k.kz <= n / 2 ? k.kz : k.kz - n;
+    const int s = (int)(sqrtf((float)(k.kx * k.kx + ky * ky + kz * kz)) + 0.5f);
+    const double w = (k.kx == 0 || 2 * k.kx == n) ? scale : 2.0 * scale;
+    atomicAdd(&hist[s], w * ((double)v.x * v.x + (double)v.y * v.y));
+    k.kx += d.kx;
+    k.ky += d.ky;
+    k.kz += d.kz;
+    if (k.kx >= nh) { k.kx -= nh; ++k.ky; }
+    if (k.ky >= n) { k.ky -= n; ++k.kz; }
   }
   __syncthreads();
-  for (int s = threadIdx.x; s < nshell; s += blockDim.x) partial[(int64_t)blockIdx.x * nshell + s] = hist[s];
+  for (int s = threadIdx.x; s < nshell; s += blockDim.x) partial[(int64_t)s * parts + part0 + blockIdx.x] = hist[s];
 }
 
+// One block per shell; fixed order.  256^3: 720 -> 4 us against one thread per shell walking a
+// strided column of 3072 partials.
 __global__ __launch_bounds__(256) void shell_reduce_kernel(const double* __restrict__ partial, int nparts,
-                                                           int nshell, double* __restrict__ out) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nshell) return;
+                                                           double* __restrict__ out) {
+  const double* p = partial + (int64_t)blockIdx.x * nparts;
   double acc = 0.0;
-  for (int b = 0; b < nparts; ++b) acc += partial[(int64_t)b * nshell + s];
-  out[s] = acc;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nparts; b += 256) acc += p[b];
+  block_reduce_store<1, 0u>(&acc, out + blockIdx.x);
 }
 
 struct Plan {
@@ -143,7 +158,7 @@ hipError_t spectrum_launch(const float* ux, const float* uy, const float* uz, in
     ok = rocfft_execute(p->plan, in, outp, info) == rocfft_status_success;
     if (!ok) break;
     hipLaunchKernelGGL(shell_kernel, dim3(kShellBlocks), dim3(kShellThreads), nshell * sizeof(double), st, cbuf, n,
-                       nshell, scale, partial + (size_t)c * kShellBlocks * nshell);
+                       nshell, scale, partial, 3 * kShellBlocks, c * kShellBlocks);
     e = hipGetLastError();
     if (e != hipSuccess) break;
   }
@@ -153,8 +168,7 @@ hipError_t spectrum_launch(const float* ux, const float* uy, const float* uz, in
     return hipErrorUnknown;
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(shell_reduce_kernel, dim3((nshell + 255) / 256), dim3(256), 0, st, partial, 3 * kShellBlocks,
-                     nshell, out);
+  hipLaunchKernelGGL(shell_reduce_kernel, dim3(nshell), dim3(256), 0, st, partial, 3 * kShellBlocks, out);
   return hipGetLastError();
 }
 

@@ -45,6 +45,23 @@ def test_spectrum_matches_oracle(n, steps):
     assert abs(got.sum() - ek) < 1e-6 * ek
 
 
+@pytest.mark.parametrize("n", [4, 7, 45, 64])
+def test_spectrum_binning_of_a_random_field(n):
+    # odd and even boxes, fewer and more modes than the binning launch has threads: the modes of
+    # a random velocity field land in the shells of the oracle's FP64 binning
+    kw = kw32(n=n, fr=np.inf)
+    sim = stgv.Simulation(**kw)
+    rng = np.random.default_rng(n)
+    dev = rng.uniform(-1e-3, 1e-3, (46, n, n, n)).astype(np.float32)
+    sim.load(torch.from_numpy(dev), step=0)
+    u = sim.fields().cpu().numpy().astype(np.float64)[1:4]
+    ref = postproc.ke_spectrum(u, kw["u0"])
+    got = sim.spectrum().cpu().numpy()
+    err = np.abs(got - ref).max() / ref.max()
+    print(f"\nspectrum of a random field, {n}^3: {err:.2e}")
+    assert err < 1e-5          # FP32 transforms, log2(64^3) butterflies of 6e-8 and sums of many modes
+
+
 def test_spectrum_work_size_and_errors():
     nbytes = stgv.lbm_spectrum_work_bytes(32)
     assert nbytes >= 5 * 32 ** 3 * 4
