@@ -25,6 +25,8 @@
 
 namespace stgv {
 
+constexpr int kNodeBlock = 256;   // threads (and nodes) of a node kernel's block
+
 enum Mode : int { MODE_EVEN = 0, MODE_ODD = 1, MODE_AB = 2 };
 // Guo source term, Shan-Chen velocity shift (Eq. (10)), exact difference method
 // (Kupershtokh), He-Shan-Doolen source term: the four schemes of the forcing comparison.
@@ -66,7 +68,30 @@ struct PhysConsts {
 struct Geometry {
   int n;             // box edge
   int64_t stride;    // elements between population arrays
+  uint32_t n3;       // nodes
+  uint32_t div_mul;  // i / n = (i div_mul) >> (32 + div_shift) for i < 2^30
+  int div_shift;
+  int xcd_group;     // consecutive blocks that the x-shifted steps keep on one XCD
 };
+
+// Division by n as a multiplication: with 2^(s-1) < n <= 2^s and m = floor(2^(31 + s) / n) + 1
+// (< 2^32), m n exceeds 2^(31 + s) by at most n <= 2^s, so i m / 2^(31 + s) exceeds i / n by less
+// than 1 / n for every i < 2^31 (n^3 <= 2^30).
+inline Geometry make_geometry(int n, int64_t stride) {
+  Geometry g{};
+  g.n = n;
+  g.stride = stride;
+  g.n3 = (uint32_t)n * n * n;
+  int s = 0;
+  while ((1 << s) < n) ++s;
+  g.div_mul = (uint32_t)((1ull << (31 + s)) / (unsigned)n + 1);
+  g.div_shift = s - 1;
+  // blocks of kNodeBlock nodes that make up whole rows (at most 8 of them)
+  int rows = n, blk = kNodeBlock;
+  while (blk > 1 && rows % 2 == 0) { rows /= 2; blk /= 2; }
+  g.xcd_group = rows < 8 ? rows : 8;
+  return g;
+}
 
 // ---------------------------------------------------------------------------
 // storage <-> compute conversion (compute type C is float or double)

@@ -13,27 +13,37 @@ namespace stgv {
 namespace {
 
 template <int QF, int QG, int FORCE, typename T, int MODE, int FLAGS>
-hipError_t go_step(const LaunchShape& sh, hipStream_t st, T* pop, T* dst, Geometry geo,
+hipError_t go_step(hipStream_t st, T* pop, T* dst, Geometry geo,
                    PhysConsts c, float* fields, double* partials) {
   const size_t lds = (MODE == MODE_EVEN && FLAGS == K_COLLIDE) ? even_step_lds(sizeof(T), geo.n) : 0;
-  hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS>), sh.grid, sh.block,
-                     lds, st, pop, dst, geo, c, fields, partials);
+  const dim3 grid(node_blocks(geo.n)), block(kNodeBlock);
+  if constexpr (MODE != MODE_EVEN) {
+    if (geo.n % 64 == 0) {
+      hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS, true>), grid, block, lds, st, pop, dst,
+                         geo, c, fields, partials);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS, false>), grid, block, lds, st, pop, dst, geo,
+                     c, fields, partials);
   return hipGetLastError();
 }
 
 template <int QF, int QG, int FORCE, typename T>
-hipError_t step_force(int mode, bool diag, const LaunchShape& sh, hipStream_t st, T* pop, T* dst,
+hipError_t step_force(int mode, bool diag, hipStream_t st, T* pop, T* dst,
                       Geometry geo, PhysConsts c, float* fields, double* partials) {
   constexpr int STEP = K_COLLIDE;
   constexpr int STEP_DIAG = K_COLLIDE | K_FIELDS | K_PARTIALS;
 #define STGV_GO(M) \
-  return diag ? go_step<QF, QG, FORCE, T, M, STEP_DIAG>(sh, st, pop, dst, geo, c, fields, partials) \
-              : go_step<QF, QG, FORCE, T, M, STEP>(sh, st, pop, dst, geo, c, fields, partials)
+  return diag ? go_step<QF, QG, FORCE, T, M, STEP_DIAG>(st, pop, dst, geo, c, fields, partials) \
+              : go_step<QF, QG, FORCE, T, M, STEP>(st, pop, dst, geo, c, fields, partials)
   if (mode == MODE_EVEN) STGV_GO(MODE_EVEN);
   if constexpr (sizeof(STGV_C) == 4 && ring_pair<QF, QG>(sizeof(T))) {
-    if (mode == MODE_ODD && !diag && ring_shape(sh, geo.n, sizeof(T))) {
+    const bool whole = ring_whole(geo.n, sizeof(T));
+    if (mode == MODE_ODD && !diag && (whole || ring_part(geo.n))) {
+      const LaunchShape sh = ring_launch(geo.n);
       const size_t lds = ring_step_lds(sizeof(T), (size_t)(x_moving<QF>() + x_moving<QG>()) * 256 * sizeof(T));
-      if (ring_whole_shape(sh, geo.n, sizeof(T)))
+      if (whole)
         hipLaunchKernelGGL((lbm_step_ring_kernel<QF, QG, FORCE, T, STGV_C, false>), sh.grid, sh.block, lds,
                            st, pop, geo, c);
       else
@@ -49,7 +59,7 @@ hipError_t step_force(int mode, bool diag, const LaunchShape& sh, hipStream_t st
 }
 
 template <int QF, int QG, typename T>
-hipError_t step_pair(int force, int mode, int flags, const LaunchShape& sh, hipStream_t st, T* pop,
+hipError_t step_pair(int force, int mode, int flags, hipStream_t st, T* pop,
                      T* dst, Geometry geo, PhysConsts c, float* fields, double* partials) {
   constexpr int STEP = K_COLLIDE;
   constexpr int STEP_DIAG = K_COLLIDE | K_FIELDS | K_PARTIALS;
@@ -58,16 +68,16 @@ hipError_t step_pair(int force, int mode, int flags, const LaunchShape& sh, hipS
   if (flags == STEP || flags == STEP_DIAG) {
     const bool d = flags == STEP_DIAG;
     switch (force) {
-      case FORCE_GUO: return step_force<QF, QG, FORCE_GUO, T>(mode, d, sh, st, pop, dst, geo, c, fields, partials);
-      case FORCE_SHIFT: return step_force<QF, QG, FORCE_SHIFT, T>(mode, d, sh, st, pop, dst, geo, c, fields, partials);
-      case FORCE_EDM: return step_force<QF, QG, FORCE_EDM, T>(mode, d, sh, st, pop, dst, geo, c, fields, partials);
-      case FORCE_HCZ: return step_force<QF, QG, FORCE_HCZ, T>(mode, d, sh, st, pop, dst, geo, c, fields, partials);
+      case FORCE_GUO: return step_force<QF, QG, FORCE_GUO, T>(mode, d, st, pop, dst, geo, c, fields, partials);
+      case FORCE_SHIFT: return step_force<QF, QG, FORCE_SHIFT, T>(mode, d, st, pop, dst, geo, c, fields, partials);
+      case FORCE_EDM: return step_force<QF, QG, FORCE_EDM, T>(mode, d, st, pop, dst, geo, c, fields, partials);
+      case FORCE_HCZ: return step_force<QF, QG, FORCE_HCZ, T>(mode, d, st, pop, dst, geo, c, fields, partials);
       default: return hipErrorInvalidValue;
     }
   }
   // Moment-only passes read the natural layout (MODE_EVEN, also the AB lattice)
   // or the odd AA layout; the physical velocity does not depend on the forcing.
-#define STGV_GO(M, FL) return go_step<QF, QG, FORCE_GUO, T, M, FL>(sh, st, pop, dst, geo, c, fields, partials)
+#define STGV_GO(M, FL) return go_step<QF, QG, FORCE_GUO, T, M, FL>(st, pop, dst, geo, c, fields, partials)
   const int gm = (mode == MODE_ODD) ? MODE_ODD : MODE_EVEN;
   if (flags == SAMPLE) {
     if (gm == MODE_EVEN) STGV_GO(MODE_EVEN, SAMPLE);
@@ -85,10 +95,10 @@ hipError_t step_pair(int force, int mode, int flags, const LaunchShape& sh, hipS
 
 template <>
 hipError_t launch_step<STGV_T, STGV_C>(int qf, int qg, int force, int mode, int flags,
-                               const LaunchShape& sh, hipStream_t st, STGV_T* pop, STGV_T* dst,
+                               hipStream_t st, STGV_T* pop, STGV_T* dst,
                                Geometry geo, PhysConsts c, float* fields, double* partials) {
 #define STGV_STEP_PAIR(A, B) \
-  if (qf == A && qg == B) return step_pair<A, B, STGV_T>(force, mode, flags, sh, st, pop, dst, geo, c, fields, partials);
+  if (qf == A && qg == B) return step_pair<A, B, STGV_T>(force, mode, flags, st, pop, dst, geo, c, fields, partials);
   STGV_FOR_EACH_PAIR(STGV_STEP_PAIR)
 #undef STGV_STEP_PAIR
   return hipErrorInvalidValue;
@@ -96,11 +106,11 @@ hipError_t launch_step<STGV_T, STGV_C>(int qf, int qg, int force, int mode, int 
 
 #ifdef STGV_LAYOUT_KERNELS
 template <>
-hipError_t launch_init<STGV_T>(int qf, int qg, const LaunchShape& sh, hipStream_t st, STGV_T* pop,
+hipError_t launch_init<STGV_T>(int qf, int qg, hipStream_t st, STGV_T* pop,
                                Geometry geo, double u0, double noise_amp, uint64_t seed) {
 #define STGV_INIT(A, B) \
   if (qf == A && qg == B) { \
-    hipLaunchKernelGGL((lbm_init_tgv_kernel<A, B, STGV_T>), sh.grid, sh.block, 0, st, pop, geo, u0, noise_amp, seed); \
+    hipLaunchKernelGGL((lbm_init_tgv_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, u0, noise_amp, seed); \
     return hipGetLastError(); }
   STGV_FOR_EACH_PAIR(STGV_INIT)
 #undef STGV_INIT
@@ -108,23 +118,27 @@ hipError_t launch_init<STGV_T>(int qf, int qg, const LaunchShape& sh, hipStream_
 }
 
 template <>
-hipError_t launch_stream<STGV_T>(int qf, int qg, int mode, const LaunchShape& sh, hipStream_t st,
+hipError_t launch_stream<STGV_T>(int qf, int qg, int mode, hipStream_t st,
                                  STGV_T* pop, STGV_T* dst, Geometry geo) {
-  const bool ring = mode == MODE_ODD && ring_shape(sh, geo.n, sizeof(STGV_T));
-  const bool whole = ring_whole_shape(sh, geo.n, sizeof(STGV_T));
+  const bool whole = ring_whole(geo.n, sizeof(STGV_T)), ring = mode == MODE_ODD && (whole || ring_part(geo.n));
+  const bool rows = geo.n % 64 == 0;
+  const dim3 grid(node_blocks(geo.n)), block(kNodeBlock);
 #define STGV_STREAM(A, B) \
   if (qf == A && qg == B) { \
     if constexpr (ring_pair<A, B>(sizeof(STGV_T))) { \
       if (ring) { \
+        const LaunchShape sh = ring_launch(geo.n); \
         const size_t lds = ring_step_lds(sizeof(STGV_T), (size_t)(x_moving<A>() + x_moving<B>()) * 256 * sizeof(STGV_T)); \
         if (whole) hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, false>), sh.grid, sh.block, lds, st, pop, geo); \
         else hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, true>), sh.grid, sh.block, lds, st, pop, geo); \
         return hipGetLastError(); \
       } \
     } \
-    if (mode == MODE_EVEN) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN>), sh.grid, sh.block, even_step_lds(sizeof(STGV_T), geo.n), st, pop, dst, geo); \
-    else if (mode == MODE_ODD) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD>), sh.grid, sh.block, 0, st, pop, dst, geo); \
-    else if (mode == MODE_AB) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB>), sh.grid, sh.block, 0, st, pop, dst, geo); \
+    if (mode == MODE_EVEN) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN, false>), grid, block, even_step_lds(sizeof(STGV_T), geo.n), st, pop, dst, geo); \
+    else if (mode == MODE_ODD && rows) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, true>), grid, block, 0, st, pop, dst, geo); \
+    else if (mode == MODE_ODD) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, false>), grid, block, 0, st, pop, dst, geo); \
+    else if (mode == MODE_AB && rows) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, true>), grid, block, 0, st, pop, dst, geo); \
+    else if (mode == MODE_AB) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, false>), grid, block, 0, st, pop, dst, geo); \
     else return hipErrorInvalidValue; \
     return hipGetLastError(); }
   STGV_FOR_EACH_PAIR(STGV_STREAM)
@@ -133,12 +147,12 @@ hipError_t launch_stream<STGV_T>(int qf, int qg, int mode, const LaunchShape& sh
 }
 
 template <>
-hipError_t launch_canon<STGV_T>(int qf, int qg, int mode, const LaunchShape& sh, hipStream_t st,
+hipError_t launch_canon<STGV_T>(int qf, int qg, int mode, hipStream_t st,
                                 const STGV_T* pop, Geometry geo, float* out) {
 #define STGV_CANON(A, B) \
   if (qf == A && qg == B) { \
-    if (mode == MODE_ODD) hipLaunchKernelGGL((lbm_canon_kernel<A, B, STGV_T, MODE_ODD>), sh.grid, sh.block, 0, st, pop, geo, out); \
-    else hipLaunchKernelGGL((lbm_canon_kernel<A, B, STGV_T, MODE_EVEN>), sh.grid, sh.block, 0, st, pop, geo, out); \
+    if (mode == MODE_ODD) hipLaunchKernelGGL((lbm_canon_kernel<A, B, STGV_T, MODE_ODD>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, out); \
+    else hipLaunchKernelGGL((lbm_canon_kernel<A, B, STGV_T, MODE_EVEN>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, out); \
     return hipGetLastError(); }
   STGV_FOR_EACH_PAIR(STGV_CANON)
 #undef STGV_CANON
@@ -146,11 +160,11 @@ hipError_t launch_canon<STGV_T>(int qf, int qg, int mode, const LaunchShape& sh,
 }
 
 template <>
-hipError_t launch_load<STGV_T>(int qf, int qg, const LaunchShape& sh, hipStream_t st, STGV_T* pop,
+hipError_t launch_load<STGV_T>(int qf, int qg, hipStream_t st, STGV_T* pop,
                                Geometry geo, const float* in) {
 #define STGV_LOAD(A, B) \
   if (qf == A && qg == B) { \
-    hipLaunchKernelGGL((lbm_load_kernel<A, B, STGV_T>), sh.grid, sh.block, 0, st, pop, geo, in); \
+    hipLaunchKernelGGL((lbm_load_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, in); \
     return hipGetLastError(); }
   STGV_FOR_EACH_PAIR(STGV_LOAD)
 #undef STGV_LOAD

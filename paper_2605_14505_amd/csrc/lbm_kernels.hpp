@@ -7,9 +7,8 @@ namespace stgv {
 // ---------------------------------------------------------------------------
 // Fused stream-collide-force step (optionally with the diagnostic moments)
 //
-// Block (bx, by) threads over x and y; grid (ceil(n/bx), ceil(n/by), n).
-// `pop` is the population array (AA) or the source lattice (AB); `dst` is the
-// AB destination and equals `pop` otherwise.
+// `pop` is the population array (AA) or the source lattice (AB); `dst` is the AB
+// destination and equals `pop` otherwise.
 // ---------------------------------------------------------------------------
 // Minimum resident 256-thread blocks per CU requested from the register allocator
 // (0 = compiler's choice): STGV_EVEN_MIN_BLOCKS for the plain even step with 4-byte
@@ -30,21 +29,61 @@ constexpr int step_min_blocks() {
 #define STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) __launch_bounds__(256, (step_min_blocks<MODE, FLAGS, T, C>()))
 #define STGV_STEP_BOUNDS STGV_STEP_BOUNDS_FOR(MODE_ODD, K_COLLIDE, T, C)
 
-// Block coordinates of a node kernel.  The hardware hands consecutive workgroups to the
-// 8 XCDs in turn, each with its own L2, so the blocks that split one row along x sit on
-// different XCDs; the steps whose loads or stores are shifted along x (odd AA, A-B) share
-// a line at every block seam, and then fetch it from HBM twice (at 512^3 FP16, 15 % more
-// than the algorithmic bytes).  For those steps, when rows are split, the workgroups are
-// renumbered so that the blocks of one row group are 8 apart in dispatch order, i.e. on
-// one XCD: workgroup L = 8 (nbx q + h) + k holds x-block h of row group 8 q + k.  A
-// bijection whenever the row groups (gridDim.y gridDim.z) are a multiple of 8.
+// Nodes of the plain node kernels: block b holds the kNodeBlock consecutive nodes from
+// kNodeBlock b of the linear order x + n (y + n z), whatever the box, so that no lane is idle
+// and every wavefront's access is one contiguous run.  Against x-y block shapes (128 x 2 for
+// 90^3 and 100^3, 32 x 8 for 96^3 and 160^3), mean step in us: 90^3 FP16 27 x 7 35.6 -> 23.8,
+// FP32 27 x 19 72.2 -> 50.1; 100^3 FP32 91.7 -> 67.5; 160^3 FP16 215 -> 145; 96^3 FP32
+// 60.2 -> 58.5; boxes whose rows are whole wavefronts are unchanged within 1 %.
+//
+// The hardware hands consecutive workgroups to the 8 XCDs in turn, each with its own L2, so
+// neighbouring blocks sit on different XCDs; the steps whose loads or stores are shifted
+// along x (odd AA, A-B) share a line at every block seam inside a row, and then fetch it from
+// HBM twice (at 512^3 FP16, 15 % more than the algorithmic bytes).  For those steps the
+// workgroups are renumbered so that the `xcd_group` consecutive blocks that make up whole
+// rows are 8 apart in dispatch order, i.e. on one XCD: workgroup L = 8 (G q + h) + k holds
+// block G (8 q + k) + h; the blocks past the last multiple of 8 G keep their places.
+template <int MODE>
+__device__ __forceinline__ uint32_t node_block(const Geometry& geo) {
+  uint32_t b = blockIdx.x;
+  if (MODE != MODE_EVEN && geo.xcd_group > 1) {
+    const uint32_t G = (uint32_t)geo.xcd_group, whole = gridDim.x / (8 * G) * (8 * G);
+    if (b < whole) {
+      const uint32_t k = b & 7, rest = b >> 3;
+      b = G * (8 * (rest / G) + k) + rest % G;
+    }
+  }
+  return b;
+}
+template <int MODE>
+__device__ __forceinline__ uint32_t node_of(const Geometry& geo) {
+  return node_block<MODE>(geo) * kNodeBlock + threadIdx.x;
+}
+
+// Neighbour offsets of node i.  ROWS: n is a multiple of 64, so a wavefront's nodes lie in one
+// row and its y and z are scalar.  Even steps address their own node only.
+template <int MODE, bool ROWS>
+__device__ __forceinline__ NodeIndex index_of(uint32_t i, const Geometry& geo) {
+  NodeIndex ix{};
+  ix.base = i;
+  if constexpr (MODE != MODE_EVEN) {
+    uint32_t r = __umulhi(i, geo.div_mul) >> geo.div_shift;
+    const uint32_t x = i - r * (uint32_t)geo.n;
+    if constexpr (ROWS) r = (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
+    const uint32_t z = __umulhi(r, geo.div_mul) >> geo.div_shift;
+    ix = make_index((int)x, (int)(r - z * (uint32_t)geo.n), (int)z, geo.n);
+  }
+  return ix;
+}
+
+// Block coordinates of the row-aligned kernels, whose blocks are (bx, by) nodes of whole or
+// part rows; renumbered as above where rows are split.
 struct BlockXYZ { int bx, by, bz; };
 
-template <int MODE>
-__device__ __forceinline__ BlockXYZ node_block() {
+__device__ __forceinline__ BlockXYZ ring_block() {
   BlockXYZ b{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z};
   const int gx = (int)gridDim.x, gy = (int)gridDim.y;
-  if (MODE != MODE_EVEN && gx > 1 && ((gy * (int)gridDim.z) & 7) == 0) {
+  if (gx > 1 && ((gy * (int)gridDim.z) & 7) == 0) {
     const int L = b.bx + gx * (b.by + gy * b.bz);
     const int k = L & 7, rest = L >> 3;
     const int rg = (rest / gx) * 8 + k;
@@ -65,16 +104,12 @@ template <int MODE, int FLAGS, typename T, int QF>
 constexpr bool kBatchBf16 = MODE == MODE_EVEN && FLAGS == K_COLLIDE && std::is_same<T, bf16_t>::value && QF == 27;
 #define STGV_OPERANDS_27(a) "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15]), "+v"(a[16]), "+v"(a[17]), "+v"(a[18]), "+v"(a[19]), "+v"(a[20]), "+v"(a[21]), "+v"(a[22]), "+v"(a[23]), "+v"(a[24]), "+v"(a[25]), "+v"(a[26])
 
-template <int QF, int QG, int FORCE, typename T, typename C, int MODE, int FLAGS>
+template <int QF, int QG, int FORCE, typename T, typename C, int MODE, int FLAGS, bool ROWS>
 __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, T* dst, Geometry geo,
                                                        PhysConsts c, float* __restrict__ fields,
                                                        double* __restrict__ partials) {
-  const int n = geo.n;
-  const BlockXYZ blk = node_block<MODE>();
-  const int x = blk.bx * blockDim.x + threadIdx.x;
-  const int y = blk.by * blockDim.y + threadIdx.y;
-  const int z = blk.bz;
-  const bool active = (x < n) && (y < n);
+  const uint32_t node = node_of<MODE>(geo);
+  const bool active = node < geo.n3;
   constexpr bool kPart = (FLAGS & K_PARTIALS) != 0;
   if (!kPart && !active) return;
 
@@ -83,7 +118,7 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
   for (int k = 0; k < NPART; ++k) acc[k] = 0.0;
 
   if (active) {
-    const NodeIndex ix = make_index(x, y, z, n);
+    const NodeIndex ix = index_of<MODE, ROWS>(node, geo);
     C f[QF], g[QG];
     gather<QF, T, MODE, true>(f, pop, 0, ix, geo.stride);
     if constexpr (kBatchBf16<MODE, FLAGS, T, QF>) asm volatile("" : STGV_OPERANDS_27(f) :: "memory");
@@ -92,7 +127,7 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
     step_macro<QF, QG, FORCE, sizeof(T) == 4>(f, g, c, m);
     if (FLAGS & (K_FIELDS | K_PARTIALS)) {
       const NodeMacro<C> dm = diag_macro(m);
-      if (FLAGS & K_FIELDS) write_fields(dm, fields, ix.base, (int64_t)n * n * n);
+      if (FLAGS & K_FIELDS) write_fields(dm, fields, node, (int64_t)geo.n3);
       if (kPart) node_partials(dm, c, acc);
     }
     if (FLAGS & K_COLLIDE) {
@@ -102,8 +137,7 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
     }
   }
   if (kPart) {
-    const int64_t b = blk.bx + (int64_t)gridDim.x * (blk.by + (int64_t)gridDim.y * blk.bz);
-    block_reduce_store<NPART, (1u << P_UMAX2)>(acc, partials + b * NPART);
+    block_reduce_store<NPART, (1u << P_UMAX2)>(acc, partials + (int64_t)node_block<MODE>(geo) * NPART);
   }
 }
 
@@ -130,7 +164,7 @@ __global__ STGV_STEP_BOUNDS void lbm_step_ring_kernel(T* pop, Geometry geo, Phys
   constexpr int KF = x_moving<QF>(), KG = x_moving<QG>();
   __shared__ T xs[KF + KG][256];
   const int n = geo.n;
-  const BlockXYZ blk = node_block<MODE_ODD>();
+  const BlockXYZ blk = ring_block();
   const int x = blk.bx * blockDim.x + threadIdx.x;
   const int y = blk.by * blockDim.y + threadIdx.y;
   const NodeIndex ix = make_index(x, y, blk.bz, n);
@@ -159,14 +193,11 @@ __global__ STGV_STEP_BOUNDS void lbm_step_ring_kernel(T* pop, Geometry geo, Phys
 // through FP32, which holds every FP16 / BF16 value exactly, so a stream is exact in
 // every storage type.  It is the ceiling of the step's own access pattern.
 // ---------------------------------------------------------------------------
-template <int QF, int QG, typename T, int MODE>
-__global__ __launch_bounds__(256) void lbm_stream_kernel(T* pop, T* dst, Geometry geo) {
-  const int n = geo.n;
-  const BlockXYZ blk = node_block<MODE>();
-  const int x = blk.bx * blockDim.x + threadIdx.x;
-  const int y = blk.by * blockDim.y + threadIdx.y;
-  if (x >= n || y >= n) return;
-  const NodeIndex ix = make_index(x, y, blk.bz, n);
+template <int QF, int QG, typename T, int MODE, bool ROWS>
+__global__ __launch_bounds__(kNodeBlock) void lbm_stream_kernel(T* pop, T* dst, Geometry geo) {
+  const uint32_t node = node_of<MODE>(geo);
+  if (node >= geo.n3) return;
+  const NodeIndex ix = index_of<MODE, ROWS>(node, geo);
   float f[QF], g[QG];
   gather<QF, T, MODE, true>(f, pop, 0, ix, geo.stride);
   gather<QG, T, MODE, true>(g, pop, QF, ix, geo.stride);
@@ -182,7 +213,7 @@ __global__ __launch_bounds__(256) void lbm_stream_ring_kernel(T* pop, Geometry g
   constexpr int KF = x_moving<QF>(), KG = x_moving<QG>();
   __shared__ T xs[KF + KG][256];
   const int n = geo.n;
-  const BlockXYZ blk = node_block<MODE_ODD>();
+  const BlockXYZ blk = ring_block();
   const int x = blk.bx * blockDim.x + threadIdx.x;
   const int y = blk.by * blockDim.y + threadIdx.y;
   const NodeIndex ix = make_index(x, y, blk.bz, n);
@@ -231,16 +262,14 @@ __device__ __forceinline__ void store_once(_Float16* p, double d) { store_as(p, 
 __device__ __forceinline__ void store_once(bf16_t* p, double d) { store_as(p, round_to_odd_f32(d)); }
 
 template <int QF, int QG, typename T>
-__global__ __launch_bounds__(256) void lbm_init_tgv_kernel(T* pop, Geometry geo, double u0,
+__global__ __launch_bounds__(kNodeBlock) void lbm_init_tgv_kernel(T* pop, Geometry geo, double u0,
                                                            double noise_amp, uint64_t seed) {
   using SF = Stencil<QF>;
   using SG = Stencil<QG>;
   const int n = geo.n;
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= n || y >= n) return;
-  const int64_t node = (int64_t)x + (int64_t)n * (y + (int64_t)n * z);
+  const uint32_t node = node_of<MODE_EVEN>(geo);
+  if (node >= geo.n3) return;
+  const int r = (int)(node / (uint32_t)n), x = (int)node - r * n, z = r / n, y = r - z * n;
   const double h = 2.0 * M_PI / n;
   const double X = h * x, Y = h * y, Z = h * z;
   const double vx = u0 * sin(X) * cos(Y) * cos(Z);
@@ -273,15 +302,12 @@ __global__ __launch_bounds__(256) void lbm_init_tgv_kernel(T* pop, Geometry geo,
 // Layout conversion: current layout -> natural FP32 deviations, and back.
 // ---------------------------------------------------------------------------
 template <int QF, int QG, typename T, int MODE>
-__global__ __launch_bounds__(256) void lbm_canon_kernel(const T* pop, Geometry geo,
+__global__ __launch_bounds__(kNodeBlock) void lbm_canon_kernel(const T* pop, Geometry geo,
                                                         float* __restrict__ out) {
-  const int n = geo.n;
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= n || y >= n) return;
-  const NodeIndex ix = make_index(x, y, z, n);
-  const int64_t n3 = (int64_t)n * n * n;
+  const uint32_t node = node_of<MODE_EVEN>(geo);
+  if (node >= geo.n3) return;
+  const NodeIndex ix = index_of<MODE, false>(node, geo);
+  const int64_t n3 = geo.n3;
   float f[QF], g[QG];
   gather<QF, T, MODE>(f, pop, 0, ix, geo.stride);
   gather<QG, T, MODE>(g, pop, QF, ix, geo.stride);
@@ -292,15 +318,11 @@ __global__ __launch_bounds__(256) void lbm_canon_kernel(const T* pop, Geometry g
 }
 
 template <int QF, int QG, typename T>
-__global__ __launch_bounds__(256) void lbm_load_kernel(T* pop, Geometry geo,
+__global__ __launch_bounds__(kNodeBlock) void lbm_load_kernel(T* pop, Geometry geo,
                                                        const float* __restrict__ in) {
-  const int n = geo.n;
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= n || y >= n) return;
-  const int64_t n3 = (int64_t)n * n * n;
-  const int64_t node = (int64_t)x + (int64_t)n * (y + (int64_t)n * z);
+  const uint32_t node = node_of<MODE_EVEN>(geo);
+  if (node >= geo.n3) return;
+  const int64_t n3 = geo.n3;
 #pragma unroll
   for (int i = 0; i < QF + QG; ++i)
     store_as(pop + (int64_t)i * geo.stride + node, in[i * n3 + node]);

@@ -16,32 +16,9 @@ struct LaunchShape {
 // to each.
 #define STGV_FOR_EACH_PAIR(X) X(27, 19) X(27, 7) X(19, 7) X(27, 27) X(19, 19) X(19, 15) X(15, 7) X(7, 27)
 
-// Launch shape of the node kernels: block (bx, by) over x and y, grid over
-// (x, y, z).  Blocks are 256 threads except when a row is shorter than a
-// wavefront; every block is a whole number of 64-wide wavefronts.
-#ifndef STGV_BLOCK_X
-#define STGV_BLOCK_X 256
-#endif
-inline LaunchShape node_shape(int n) {
-  int bx, by;
-  if (n <= 64 && 64 % n == 0) {
-    bx = n;
-    by = 256 / n;
-  } else if (n % 64 != 0 && n % 32 == 0) {
-    bx = 32;                      // whole 128-byte lines per row, no idle lanes (n = 96, 160, ...)
-    by = 8;
-  } else if (n % 64 == 0) {
-    bx = n % 256 == 0 ? 256 : (n % 128 == 0 ? 128 : 64);   // rows split evenly (n = 320, 384, 448)
-    by = 256 / bx;
-  } else {
-    bx = ((n + 63) / 64) * 64;
-    if (bx > STGV_BLOCK_X) bx = STGV_BLOCK_X;
-    by = 256 / bx;
-  }
-  LaunchShape s;
-  s.block = dim3(bx, by, 1);
-  s.grid = dim3((n + bx - 1) / bx, (n + by - 1) / by, n);
-  return s;
+// Blocks of the plain node kernels (kNodeBlock consecutive nodes each).
+inline unsigned node_blocks(int n) {
+  return (unsigned)(((int64_t)n * n * n + kNodeBlock - 1) / kNodeBlock);
 }
 
 // Whether the plain odd step runs row-aligned through an LDS ring (lbm_step_ring_kernel):
@@ -59,15 +36,14 @@ constexpr bool ring_pair(size_t elem) {
   return elem == 4 ? ((QF == 27 && QG == 19) || (QF == 19 && QG == 19) || (QF == 7 && QG == 27))
                    : ((QF == 27 && QG == 19) || (QF == 27 && QG == 7));
 }
-inline bool ring_whole_shape(const LaunchShape& sh, int n, size_t elem) {
-  const int bx = (int)sh.block.x, by = (int)sh.block.y;
-  return n >= (elem == 4 ? 256 : 128) && bx == n && sh.grid.x == 1 && bx * by == 256 && n % by == 0;
-}
-inline bool ring_part_shape(const LaunchShape& sh, int n) {
-  return n >= 512 && sh.block.x == 256 && sh.block.y == 1 && n % 256 == 0;
-}
-inline bool ring_shape(const LaunchShape& sh, int n, size_t elem) {
-  return ring_whole_shape(sh, n, elem) || ring_part_shape(sh, n);
+inline bool ring_whole(int n, size_t elem) { return n == 256 || (n == 128 && elem != 4); }
+inline bool ring_part(int n) { return n >= 512 && n % 256 == 0; }
+// Blocks of n x 256 / n nodes (whole rows) or of 256 nodes of one row.
+inline LaunchShape ring_launch(int n) {
+  LaunchShape s;
+  s.block = n < 256 ? dim3(n, 256 / n, 1) : dim3(256, 1, 1);
+  s.grid = dim3(n / s.block.x, n / s.block.y, n);
+  return s;
 }
 
 // Blocks resident per CU for the plain even step (0 = as many as the registers allow), set
@@ -116,25 +92,24 @@ inline size_t ring_step_lds(size_t elem, size_t static_lds) {
 
 // Every function returns the launch error (hipSuccess when queued).
 template <typename T, typename C>
-hipError_t launch_step(int qf, int qg, int force, int mode, int flags, const LaunchShape& sh,
-                       hipStream_t st, T* pop, T* dst, Geometry geo, PhysConsts c,
+hipError_t launch_step(int qf, int qg, int force, int mode, int flags, hipStream_t st, T* pop, T* dst, Geometry geo, PhysConsts c,
                        float* fields, double* partials);
 
 template <typename T>
-hipError_t launch_init(int qf, int qg, const LaunchShape& sh, hipStream_t st, T* pop, Geometry geo,
+hipError_t launch_init(int qf, int qg, hipStream_t st, T* pop, Geometry geo,
                        double u0, double noise_amp, uint64_t seed);
 
 // Free streaming (lbm_stream_kernel) in layout MODE, from pop into dst.
 template <typename T>
-hipError_t launch_stream(int qf, int qg, int mode, const LaunchShape& sh, hipStream_t st, T* pop,
+hipError_t launch_stream(int qf, int qg, int mode, hipStream_t st, T* pop,
                          T* dst, Geometry geo);
 
 template <typename T>
-hipError_t launch_canon(int qf, int qg, int mode, const LaunchShape& sh, hipStream_t st,
+hipError_t launch_canon(int qf, int qg, int mode, hipStream_t st,
                         const T* pop, Geometry geo, float* out);
 
 template <typename T>
-hipError_t launch_load(int qf, int qg, const LaunchShape& sh, hipStream_t st, T* pop,
+hipError_t launch_load(int qf, int qg, hipStream_t st, T* pop,
                        Geometry geo, const float* in);
 
 }  // namespace stgv

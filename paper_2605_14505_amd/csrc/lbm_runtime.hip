@@ -365,8 +365,7 @@ Sizes sizes_of(const lbm_params* p) {
   s.stride = ((s.n3 + pad + per_line - 1) / per_line) * per_line;
   const int64_t arrays = (int64_t)(p->q_f + p->q_g) * (p->layout == LBM_LAYOUT_AB ? 2 : 1);
   s.pop_bytes = (size_t)(arrays * s.stride) * s.elem;
-  const LaunchShape sh = node_shape(p->n);
-  s.nsp = (int64_t)sh.grid.x * sh.grid.y * sh.grid.z;
+  s.nsp = node_blocks(p->n);
   // the learned step runs 256-thread blocks of 128 nodes
   s.nsp_learned = (p->n % 64 == 0) ? (int64_t)p->n * p->n * p->n / 128 : 0;
   const int64_t nsp_max = s.nsp > s.nsp_learned ? s.nsp : s.nsp_learned;
@@ -387,7 +386,6 @@ struct lbm_ctx {
   lbm_params p;
   Derived d;
   Sizes sz;
-  LaunchShape sh;
   PhysConsts c;
   Geometry geo;
   char* pop;           // AA array, or the first AB lattice
@@ -467,15 +465,15 @@ hipError_t launch_node(lbm_ctx* c, int mode, int flags, char* src, char* dst, fl
   switch (c->p.storage) {
     case LBM_FP32:
       if (c->p.compute == LBM_COMPUTE_FP64)
-        return launch_step<float, double>(qf, qg, fo, mode, flags, c->sh, c->stream, (float*)src,
+        return launch_step<float, double>(qf, qg, fo, mode, flags, c->stream, (float*)src,
                                           (float*)dst, c->geo, c->c, fields, partials);
-      return launch_step<float, float>(qf, qg, fo, mode, flags, c->sh, c->stream, (float*)src,
+      return launch_step<float, float>(qf, qg, fo, mode, flags, c->stream, (float*)src,
                                        (float*)dst, c->geo, c->c, fields, partials);
     case LBM_FP16:
-      return launch_step<_Float16, float>(qf, qg, fo, mode, flags, c->sh, c->stream, (_Float16*)src,
+      return launch_step<_Float16, float>(qf, qg, fo, mode, flags, c->stream, (_Float16*)src,
                                           (_Float16*)dst, c->geo, c->c, fields, partials);
     default:
-      return launch_step<bf16_t, float>(qf, qg, fo, mode, flags, c->sh, c->stream, (bf16_t*)src,
+      return launch_step<bf16_t, float>(qf, qg, fo, mode, flags, c->stream, (bf16_t*)src,
                                         (bf16_t*)dst, c->geo, c->c, fields, partials);
   }
 }
@@ -530,15 +528,13 @@ int lbm_init_tgv(const lbm_params* p, void* pop_dev, size_t pop_bytes, void* wor
   c->p = *p;
   c->d = d;
   c->sz = s;
-  c->sh = node_shape(p->n);
   c->c.omega_f = 1.0 / d.tau_f;
   c->c.omega_g = 1.0 / d.tau_g;
   c->c.tau_f = d.tau_f;
   c->c.G = d.G;
   c->c.beta = d.beta;
   c->c.g_over_n = p->g_over_n;
-  c->geo.n = p->n;
-  c->geo.stride = s.stride;
+  c->geo = make_geometry(p->n, s.stride);
   c->pop = (char*)pop_dev;
   c->pop_b = p->layout == LBM_LAYOUT_AB
                  ? (char*)pop_dev + (size_t)(p->q_f + p->q_g) * s.stride * s.elem
@@ -552,7 +548,7 @@ int lbm_init_tgv(const lbm_params* p, void* pop_dev, size_t pop_bytes, void* wor
   c->err[0] = 0;
   hipError_t e = by_storage(p->storage, [&](auto* tag) {
     using T = std::remove_pointer_t<decltype(tag)>;
-    return launch_init<T>(p->q_f, p->q_g, c->sh, c->stream, (T*)c->pop, c->geo, p->u0,
+    return launch_init<T>(p->q_f, p->q_g, c->stream, (T*)c->pop, c->geo, p->u0,
                           p->noise_amp, p->seed);
   });
   if (e != hipSuccess) {
@@ -622,7 +618,7 @@ int lbm_stream(lbm_ctx* c, int64_t nsteps) {
     }
     hipError_t e = by_storage(c->p.storage, [&](auto* tag) {
       using T = std::remove_pointer_t<decltype(tag)>;
-      return launch_stream<T>(c->p.q_f, c->p.q_g, mode, c->sh, c->stream, (T*)src, (T*)dst, c->geo);
+      return launch_stream<T>(c->p.q_f, c->p.q_g, mode, c->stream, (T*)src, (T*)dst, c->geo);
     });
     if (e != hipSuccess) return hip_fail(c, e, "free-streaming kernel");
     c->step++;
@@ -709,7 +705,7 @@ int lbm_read_populations(lbm_ctx* c, float* dev_out) {
   char* src = current_array(c);
   hipError_t e = by_storage(c->p.storage, [&](auto* tag) {
     using T = std::remove_pointer_t<decltype(tag)>;
-    return launch_canon<T>(c->p.q_f, c->p.q_g, mode, c->sh, c->stream, (const T*)src, c->geo, dev_out);
+    return launch_canon<T>(c->p.q_f, c->p.q_g, mode, c->stream, (const T*)src, c->geo, dev_out);
   });
   if (e != hipSuccess) return hip_fail(c, e, "canonicalise kernel");
   e = hipStreamSynchronize(c->stream);
@@ -723,7 +719,7 @@ int lbm_load_populations(lbm_ctx* c, const float* dev_in, int64_t step) {
   if (step < 0) { set_err(c->err, "step = %lld < 0", (long long)step); return LBM_EINVAL; }
   hipError_t e = by_storage(c->p.storage, [&](auto* tag) {
     using T = std::remove_pointer_t<decltype(tag)>;
-    return launch_load<T>(c->p.q_f, c->p.q_g, c->sh, c->stream, (T*)c->pop, c->geo, dev_in);
+    return launch_load<T>(c->p.q_f, c->p.q_g, c->stream, (T*)c->pop, c->geo, dev_in);
   });
   if (e != hipSuccess) return hip_fail(c, e, "load kernel");
   e = hipStreamSynchronize(c->stream);
