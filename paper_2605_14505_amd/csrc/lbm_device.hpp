@@ -314,16 +314,22 @@ __device__ __forceinline__ RowLane make_rowlane(int x, int n) {
   return l;
 }
 
-template <int Q, typename T, bool NTX, int I, typename C>
-__device__ __forceinline__ void row_load_one(C* v, T (*xs)[256], int k0, const T* pop, int first,
-                                             const NodeIndex& ix, int64_t stride, const RowLane& l) {
+// The loads go to registers first (row_load_one) and are written to the ring or converted
+// afterwards (row_stage_one), so that a kernel can issue all of them before its first wait.
+template <int Q, typename T, bool NTX, int I>
+__device__ __forceinline__ void row_load_one(T* raw, const T* pop, int first, const NodeIndex& ix, int64_t stride,
+                                             const RowLane& l) {
   using S = Stencil<Q>;
   constexpr int ex = S::ex[I];
   // the ring's seam lane for e_x = +1 is the last, for e_x = -1 the first
   const uint32_t xl = ex > 0 ? l.x_b : (ex < 0 ? l.x_a : l.x_own);
   const T* p = at_node(pop + (int64_t)(first + opp(I)) * stride, xl + ix.yo[1 - S::ey[I]] + ix.zo[1 - S::ez[I]]);
-  if constexpr (ex == 0) v[I] = load_as<C, true>(p);
-  else xs[k0 + x_slot<Q>(I)][l.lid] = raw_load<NTX>(p);
+  raw[I] = raw_load<ex == 0 || NTX>(p);
+}
+template <int Q, typename T, int I, typename C>
+__device__ __forceinline__ void row_stage_one(C* v, const T* raw, T (*xs)[256], int k0, const RowLane& l) {
+  if constexpr (Stencil<Q>::ex[I] == 0) v[I] = load_as<C>(&raw[I]);
+  else xs[k0 + x_slot<Q>(I)][l.lid] = raw[I];
 }
 template <int Q, typename T, int I, typename C>
 __device__ __forceinline__ void row_pick_one(C* v, const T (*xs)[256], int k0, const RowLane& l) {
@@ -349,11 +355,15 @@ __device__ __forceinline__ void row_store_one(const C* v, const T (*xs)[256], in
   else raw_store<NTX>(p, xs[k0 + x_slot<Q>(I)][l.lid]);
 }
 
-template <int Q, typename T, bool NTX, typename C, int... I>
-__device__ __forceinline__ void row_load(C* v, T (*xs)[256], int k0, const T* pop, int first,
-                                         const NodeIndex& ix, int64_t stride, const RowLane& l,
-                                         std::integer_sequence<int, I...>) {
-  (row_load_one<Q, T, NTX, I>(v, xs, k0, pop, first, ix, stride, l), ...);
+template <int Q, typename T, bool NTX, int... I>
+__device__ __forceinline__ void row_load(T* raw, const T* pop, int first, const NodeIndex& ix, int64_t stride,
+                                         const RowLane& l, std::integer_sequence<int, I...>) {
+  (row_load_one<Q, T, NTX, I>(raw, pop, first, ix, stride, l), ...);
+}
+template <int Q, typename T, typename C, int... I>
+__device__ __forceinline__ void row_stage(C* v, const T* raw, T (*xs)[256], int k0, const RowLane& l,
+                                          std::integer_sequence<int, I...>) {
+  (row_stage_one<Q, T, I>(v, raw, xs, k0, l), ...);
 }
 template <int Q, typename T, typename C, int... I>
 __device__ __forceinline__ void row_pick(C* v, const T (*xs)[256], int k0, const RowLane& l,
