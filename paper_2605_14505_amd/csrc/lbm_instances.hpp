@@ -146,13 +146,26 @@ hipError_t launch_stream<STGV_T>(int qf, int qg, int mode, hipStream_t st,
   return hipErrorInvalidValue;
 }
 
+// Conversion in natural order: four values at a time where every array of both sides starts on
+// four of them and holds a whole number (n even makes n^3 a multiple of 8; the natural side is
+// the caller's buffer), else single values.
+template <bool LOAD>
+static hipError_t convert(int arrays, hipStream_t st, STGV_T* pop, Geometry geo, float* natural) {
+  constexpr int V = 4;
+  const bool wide = geo.n % 2 == 0 && (uintptr_t)natural % 16 == 0;
+  const unsigned chunk = kNodeBlock * kConvertUnroll * (wide ? V : 1);
+  const dim3 grid((geo.n3 + chunk - 1) / chunk, (unsigned)arrays), block(kNodeBlock);
+  if (wide) hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, V, LOAD>), grid, block, 0, st, pop, geo, natural);
+  else hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, 1, LOAD>), grid, block, 0, st, pop, geo, natural);
+  return hipGetLastError();
+}
+
 template <>
-hipError_t launch_canon<STGV_T>(int qf, int qg, int mode, hipStream_t st,
-                                const STGV_T* pop, Geometry geo, float* out) {
+hipError_t launch_canon<STGV_T>(int qf, int qg, int mode, hipStream_t st, const STGV_T* pop, Geometry geo, float* out) {
+  if (mode != MODE_ODD) return convert<false>(qf + qg, st, const_cast<STGV_T*>(pop), geo, out);
 #define STGV_CANON(A, B) \
   if (qf == A && qg == B) { \
-    if (mode == MODE_ODD) hipLaunchKernelGGL((lbm_canon_kernel<A, B, STGV_T, MODE_ODD>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, out); \
-    else hipLaunchKernelGGL((lbm_canon_kernel<A, B, STGV_T, MODE_EVEN>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, out); \
+    hipLaunchKernelGGL((lbm_canon_odd_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, out); \
     return hipGetLastError(); }
   STGV_FOR_EACH_PAIR(STGV_CANON)
 #undef STGV_CANON
@@ -160,15 +173,8 @@ hipError_t launch_canon<STGV_T>(int qf, int qg, int mode, hipStream_t st,
 }
 
 template <>
-hipError_t launch_load<STGV_T>(int qf, int qg, hipStream_t st, STGV_T* pop,
-                               Geometry geo, const float* in) {
-#define STGV_LOAD(A, B) \
-  if (qf == A && qg == B) { \
-    hipLaunchKernelGGL((lbm_load_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, in); \
-    return hipGetLastError(); }
-  STGV_FOR_EACH_PAIR(STGV_LOAD)
-#undef STGV_LOAD
-  return hipErrorInvalidValue;
+hipError_t launch_load<STGV_T>(int qf, int qg, hipStream_t st, STGV_T* pop, Geometry geo, const float* in) {
+  return convert<true>(qf + qg, st, pop, geo, const_cast<float*>(in));
 }
 #endif  // STGV_LAYOUT_KERNELS
 

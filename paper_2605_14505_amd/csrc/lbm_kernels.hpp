@@ -313,31 +313,75 @@ __global__ __launch_bounds__(kNodeBlock) void lbm_init_tgv_kernel(T* pop, Geomet
 // ---------------------------------------------------------------------------
 // Layout conversion: current layout -> natural FP32 deviations, and back.
 // ---------------------------------------------------------------------------
-template <int QF, int QG, typename T, int MODE>
-__global__ __launch_bounds__(kNodeBlock) void lbm_canon_kernel(const T* pop, Geometry geo,
-                                                        float* __restrict__ out) {
-  const uint32_t node = node_of<MODE_EVEN>(geo);
-  if (node >= geo.n3) return;
-  const NodeIndex ix = index_of<MODE, false>(node, geo);
-  const int64_t n3 = geo.n3;
-  float f[QF], g[QG];
-  gather<QF, T, MODE>(f, pop, 0, ix, geo.stride);
-  gather<QG, T, MODE>(g, pop, QF, ix, geo.stride);
-#pragma unroll
-  for (int i = 0; i < QF; ++i) out[i * n3 + ix.base] = f[i];
-#pragma unroll
-  for (int j = 0; j < QG; ++j) out[(QF + j) * n3 + ix.base] = g[j];
+// Where the array is in natural order (an even number of steps, A-B, a load) a conversion is a
+// copy of each population array by itself: block (b, q) converts a contiguous chunk of array
+// q, four values at a time (contiguous over a wavefront on both sides: eight of a 2-byte type
+// left gaps between the 16-byte stores, 512^3 FP16 read-back 8.81 ms) or one at a time, all
+// loads ahead of the stores.  HBM-bound, 5.7-5.9 TB/s: 512^3 FP16 read-back 7.86 -> 6.26 ms and
+// load 7.33 -> 6.26, 256^3 FP32 1171 -> 1081 us and 1144 -> 1088, against one thread per node with
+// 46 streams open.
+constexpr int kConvertUnroll = 4;
+
+template <typename T, int V> struct Packet { T v[V]; };
+template <int BYTES> struct PacketWord { typedef uint32_t type __attribute__((ext_vector_type(BYTES / 4))); };
+template <int V, typename T>
+__device__ __forceinline__ Packet<T, V> load_packet(const T* p) {
+  if constexpr (V == 1) return Packet<T, V>{{raw_load<true>(p)}};
+  else return __builtin_bit_cast(Packet<T, V>, __builtin_nontemporal_load((const typename PacketWord<sizeof(T) * V>::type*)p));
+}
+template <int V, typename T>
+__device__ __forceinline__ void store_packet(T* p, const Packet<T, V>& v) {
+  if constexpr (V == 1) {
+    put_rounded(p, v.v[0]);
+  } else {
+    using Word = typename PacketWord<sizeof(T) * V>::type;
+    __builtin_nontemporal_store(__builtin_bit_cast(Word, v), (Word*)p);
+  }
 }
 
+template <typename T, int V, bool LOAD>
+__global__ __launch_bounds__(kNodeBlock) void lbm_convert_kernel(T* pop, Geometry geo, float* natural) {
+  T* const a = pop + (int64_t)blockIdx.y * geo.stride;
+  float* const b = natural + (int64_t)blockIdx.y * geo.n3;
+  const uint32_t e0 = (blockIdx.x * (kNodeBlock * kConvertUnroll) + threadIdx.x) * V;
+  Packet<T, V> t[kConvertUnroll];
+  Packet<float, V> f[kConvertUnroll];
+#pragma unroll
+  for (int k = 0; k < kConvertUnroll; ++k) {
+    const uint32_t e = e0 + k * (kNodeBlock * V);
+    if (e >= geo.n3) continue;
+    if constexpr (LOAD) f[k] = load_packet<V>(b + e);
+    else t[k] = load_packet<V>(a + e);
+  }
+#pragma unroll
+  for (int k = 0; k < kConvertUnroll; ++k) {
+    const uint32_t e = e0 + k * (kNodeBlock * V);
+    if (e >= geo.n3) continue;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      if constexpr (LOAD) t[k].v[j] = rounded((const T*)nullptr, f[k].v[j]);
+      else f[k].v[j] = load_as<float>(&t[k].v[j]);
+    }
+    if constexpr (LOAD) store_packet<V>(a + e, t[k]);
+    else store_packet<V>(b + e, f[k]);
+  }
+}
+
+// Read-back of the odd AA layout: one thread per node, x-shifted loads.
 template <int QF, int QG, typename T>
-__global__ __launch_bounds__(kNodeBlock) void lbm_load_kernel(T* pop, Geometry geo,
-                                                       const float* __restrict__ in) {
+__global__ __launch_bounds__(kNodeBlock) void lbm_canon_odd_kernel(const T* pop, Geometry geo,
+                                                                   float* __restrict__ out) {
   const uint32_t node = node_of<MODE_EVEN>(geo);
   if (node >= geo.n3) return;
+  const NodeIndex ix = index_of<MODE_ODD, false>(node, geo);
   const int64_t n3 = geo.n3;
+  float f[QF], g[QG];
+  gather<QF, T, MODE_ODD>(f, pop, 0, ix, geo.stride);
+  gather<QG, T, MODE_ODD>(g, pop, QF, ix, geo.stride);
 #pragma unroll
-  for (int i = 0; i < QF + QG; ++i)
-    store_as(pop + (int64_t)i * geo.stride + node, in[i * n3 + node]);
+  for (int i = 0; i < QF; ++i) put(out + i * n3 + node, f[i]);
+#pragma unroll
+  for (int j = 0; j < QG; ++j) put(out + (QF + j) * n3 + node, g[j]);
 }
 
 }  // namespace stgv

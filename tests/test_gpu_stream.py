@@ -112,3 +112,26 @@ def test_free_streaming_rejects_a_negative_count():
     sim.free_stream(0)
     assert sim.step_count == 0
     sim.close()
+
+
+@pytest.mark.parametrize("storage", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("n,start", [(4, 0), (7, 0), (20, 0), (20, 1), (34, 0), (34, 3)])
+def test_load_and_read_back_round_trip(n, start, storage):
+    # odd boxes and caller buffers off a 16-byte boundary (one value at a time), even ones (four),
+    # a last chunk that is not full; nothing outside the caller's range is written
+    dev = uniform_deviations(46, n, 1e-2, seed=n + start)
+    ref = model.round_storage(dev.astype(np.float64), storage)
+    sim = make_sim(n, 27, 19, storage)
+    src = torch.zeros(start + dev.size, dtype=torch.float32, device="cuda:0")
+    src[start:] = torch.from_numpy(dev).reshape(-1).to(src.device)
+    out = torch.full((start + dev.size + 5,), 7.0, dtype=torch.float32, device="cuda:0")
+    stgv.lbm_load_populations(sim.ctx, src[start:], 0)
+    for steps in (0, 1):
+        if steps:
+            sim.free_stream(1)
+            ref = oracle_streamed(ref, 27, 19, 1)
+        stgv.lbm_read_populations(sim.ctx, out[start:])
+        got = out.cpu().numpy().astype(np.float64)
+        assert np.array_equal(got[start:start + dev.size].reshape(ref.shape), ref)
+        assert np.all(got[:start] == 7.0) and np.all(got[start + dev.size:] == 7.0)
+    sim.close()
