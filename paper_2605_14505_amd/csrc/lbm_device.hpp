@@ -900,41 +900,48 @@ __device__ __forceinline__ void node_partials(const NodeMacro<C>& m, const PhysC
 // ---------------------------------------------------------------------------
 // block reductions (fixed order: deterministic)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// v of the lane that the DPP control names, 0 where there is none (or its row is masked out)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+// Sum (or, of non-negative values, maximum) over the wavefront in lane 63: shifts within rows of
+// 16 lanes, then the row totals passed on by broadcasts.  Register moves only: six shuffles
+// through LDS per value put ~1 us of latency behind every diagnostic block.
+template <bool MAX>
+__device__ __forceinline__ double wave_reduce(double v) {
+  auto step = [&](double o) { v = MAX ? fmax(v, o) : v + o; };
+  step(dpp_move<0x111, 0xf>(v));      // row_shr:1
+  step(dpp_move<0x112, 0xf>(v));      // row_shr:2
+  step(dpp_move<0x114, 0xf>(v));      // row_shr:4
+  step(dpp_move<0x118, 0xf>(v));      // row_shr:8
+  step(dpp_move<0x142, 0xa>(v));      // row_bcast:15 into rows 1 and 3
+  step(dpp_move<0x143, 0xc>(v));      // row_bcast:31 into rows 2 and 3
   return v;
 }
 
-// Reduce NV per-thread values over the block and write them to out[0..NV).
-// Bit k of MAXMASK selects a maximum instead of a sum for entry k.  Every
-// thread of the block must call this (masked-out threads pass neutral values);
-// the block size must be a multiple of 64 and at most 1024.
+// Reduce NV per-thread values over the block; value k goes to out[k * stride].  Bit k of MAXMASK
+// selects a maximum (of non-negative values) instead of a sum.  Every thread of the block must
+// call this (masked-out threads pass zeros); one-dimensional blocks of a multiple of 64 and at
+// most 1024 threads.
 template <int NV, unsigned MAXMASK>
-__device__ __forceinline__ void block_reduce_store(const double* vals, double* __restrict__ out) {
-  __shared__ double lds[16][NV];
-  const int tid = threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z);
-  const int nthreads = blockDim.x * blockDim.y * blockDim.z;
-  const int lane = tid & 63, wid = tid >> 6, nw = nthreads >> 6;
+__device__ __forceinline__ void block_reduce_store(const double* vals, double* __restrict__ out, int64_t stride = 1) {
+  __shared__ double lds[NV][16];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    const double r = ((MAXMASK >> k) & 1u) ? wave_max(vals[k]) : wave_sum(vals[k]);
-    if (lane == 0) lds[wid][k] = r;
+    const double r = ((MAXMASK >> k) & 1u) ? wave_reduce<true>(vals[k]) : wave_reduce<false>(vals[k]);
+    if (lane == 63) lds[k][wid] = r;
   }
   __syncthreads();
-  if (tid == 0) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      double acc = lds[0][k];
-      for (int w = 1; w < nw; ++w)
-        acc = ((MAXMASK >> k) & 1u) ? fmax(acc, lds[w][k]) : acc + lds[w][k];
-      out[k] = acc;
-    }
+  const int k = threadIdx.x;
+  if (k < NV) {
+    double acc = lds[k][0];
+    for (int w = 1; w < nw; ++w) acc = ((MAXMASK >> k) & 1u) ? fmax(acc, lds[k][w]) : acc + lds[k][w];
+    out[k * stride] = acc;
   }
 }
 

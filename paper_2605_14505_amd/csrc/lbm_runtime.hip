@@ -13,185 +13,194 @@
 #include "../../include/stgv.h"
 #include "learned.hpp"
 #include "postproc.hpp"
-#include "lbm_device.hpp"
+#include "lbm_kernels.hpp"
 #include "lbm_launch.hpp"
 #include "mlp_device.hpp"
 
 namespace stgv {
 
 // ---------------------------------------------------------------------------
-// Dissipation stencil: eps_k needs |curl u|^2 and eps_p needs |grad rho'|^2 by
-// second-order central differences (periodic).  A 64 x 4 tile of x-y columns
-// marches up a chunk of z.  Each z-plane of the tile plus a one-node halo is
-// staged in LDS (double-buffered, one barrier per plane) for the in-plane
-// derivatives while the next plane is already on its way into registers; the
-// z-derivatives of a plane are taken one plane later, when the plane above has
-// arrived, from the column's values kept in registers.  Node by node, the
-// arithmetic and the order of each thread's sum (planes z0, z0 + 1, ...) are
-// those of the plain definition.
+// Dissipation stencil and first stage of a record's reduction: eps_k needs |curl u|^2 and
+// eps_p needs |grad rho'|^2 by second-order central differences (periodic).
 //
-// The hardware hands consecutive blocks to the 8 XCDs in turn, each with its own
-// L2; left so, a tile's halo rows belong to tiles on other XCDs and are fetched
-// from HBM again.  The tiles of a z-chunk are therefore remapped so that every
-// XCD owns a contiguous band of rows, whose inner halos its own L2 then serves.
+// Block b of nb takes a share of the nodes, and reduces the same share of the step's per-block
+// partials beside them into one row of NPART + NFD values, rows[k nb + b].  The hardware hands
+// consecutive blocks to the 8 XCDs in turn, each with its own L2, so the blocks are renumbered
+// to give each XCD a contiguous slab of the box, whose inner neighbours its own L2 then serves.
+//
+// COLUMNS (fd_shape): a 64 x 4 tile of x-y columns marches up a chunk of z.  Each z-plane of the
+// tile plus a one-node halo is staged in LDS (double-buffered, one barrier per plane) for the
+// in-plane derivatives while the next plane is already on its way into registers; the
+// z-derivatives of a plane are taken one plane later, when the plane above has arrived, from
+// the column's values kept in registers.  Otherwise a block takes consecutive nodes of the
+// linear order, with no serial chain but a thread's few nodes and no idle lanes, and all 18
+// neighbour values through L1 and L2.
+//
+// The columns read each field once and are bound by the misses a CU keeps in flight (3.1 TB/s);
+// below kFdColumnsFrom the march's latency is what counts.  A whole record (moments kernel,
+// stencil, reduction) in us, columns and two further reduction launches before / now: 64^3
+// 44.0 / 18.6, 96^3 67 / 47, 128^3 111 / 93, 192^3 295 / 281, 256^3 720 / 722.  Linear order
+// at 256^3 732 and at 512^3 FP16 3530 against 3407; columns through L1 alone, without LDS,
+// 717 and 3581.
 // ---------------------------------------------------------------------------
-#ifndef STGV_FD_ZC
-#define STGV_FD_ZC 32
+constexpr int kXcds = 8;
+constexpr int kNV = NPART + NFD;
+constexpr unsigned kMaxMask = 1u << P_UMAX2;
+constexpr int kFdBlocks = 2048;              // about: 8 resident blocks on each CU
+#ifndef STGV_FD_COLUMNS_FROM
+#define STGV_FD_COLUMNS_FROM 192
 #endif
-constexpr int FD_TX = 64, FD_TY = 4, FD_ZC = STGV_FD_ZC;
+constexpr int kFdColumnsFrom = STGV_FD_COLUMNS_FROM;
+constexpr int FD_TX = 64, FD_TY = kNodeBlock / FD_TX, FD_ZC = 32;
 constexpr int FD_W = FD_TX + 2, FD_H = FD_TY + 2;
 constexpr int FD_CELLS = FD_W * FD_H;
-constexpr int FD_SLOTS = (FD_CELLS + FD_TX * FD_TY - 1) / (FD_TX * FD_TY);
-constexpr int kXcds = 8;
+constexpr int FD_SLOTS = (FD_CELLS + kNodeBlock - 1) / kNodeBlock;
 
-__global__ __launch_bounds__(256) void lbm_fd_kernel(const float* __restrict__ fields, int n,
-                                                     double* __restrict__ partials) {
-  __shared__ float plane[2][4][FD_H][FD_W];     // u_x, u_y, u_z, rho'
-  const int64_t n2 = (int64_t)n * n, n3 = n2 * n;
+struct FdShape {
+  bool columns;
+  int tx, ty, chunks;      // tiles in x and y, chunks in z
+  int64_t blocks;
+};
+inline FdShape fd_shape(int n) {
+  FdShape f{n >= kFdColumnsFrom, (n + FD_TX - 1) / FD_TX, (n + FD_TY - 1) / FD_TY, 1, 0};
+  if (f.columns) {
+    f.chunks = (n + FD_ZC - 1) / FD_ZC < 8 ? (n + FD_ZC - 1) / FD_ZC : 8;
+    f.blocks = (int64_t)f.tx * f.ty * f.chunks;
+  } else {
+    f.blocks = ((int64_t)n * n * n + kNodeBlock - 1) / kNodeBlock;
+    if (f.blocks > kFdBlocks) f.blocks = kFdBlocks;
+  }
+  return f;
+}
+
+template <bool COLUMNS>
+__global__ __launch_bounds__(kNodeBlock) void lbm_fd_kernel(const float* __restrict__ fields, Geometry geo, int tiles_x,
+                                                            int tiles_y, const double* __restrict__ sp, int64_t nsp,
+                                                            double* __restrict__ rows) {
+  const int64_t n3 = geo.n3, nb = gridDim.x;
   const float* ux = fields + n3;
   const float* uy = fields + 2 * n3;
   const float* uz = fields + 3 * n3;
   const float* rp = fields + 4 * n3;
-  int bx = blockIdx.x, by = blockIdx.y;
-  if (gridDim.y % kXcds == 0) {            // the chunk's tiles, in dispatch order, by XCD
-    const int lin = blockIdx.x + gridDim.x * blockIdx.y;
-    const int xcd = lin % kXcds, j = lin / kXcds;
-    by = xcd * (gridDim.y / kXcds) + j / gridDim.x;
-    bx = j % gridDim.x;
-  }
-  const int tx = threadIdx.x, ty = threadIdx.y;
-  const int tid = tx + FD_TX * ty;
-  const int x0 = bx * FD_TX, y0 = by * FD_TY;
-  const bool active = (x0 + tx < n) && (y0 + ty < n);
-  const int z0 = blockIdx.z * FD_ZC;
-  const int z1 = min(z0 + FD_ZC, n);
-  auto zwrap = [n](int z) { return z < 0 ? z + n : (z >= n ? z - n : z); };
-
-  // this thread's cells of the staged tile and their in-plane offsets, wrapped once
-  int64_t off[FD_SLOTS];
-  int cell[FD_SLOTS];
-#pragma unroll
-  for (int s = 0; s < FD_SLOTS; ++s) {
-    const int c = tid + FD_TX * FD_TY * s;
-    cell[s] = c < FD_CELLS ? c : -1;
-    const int ly = c / FD_W, lx = c % FD_W;
-    const int gx = ((x0 + lx - 1) % n + n) % n, gy = ((y0 + ly - 1) % n + n) % n;
-    off[s] = c < FD_CELLS ? gx + (int64_t)n * gy : 0;
-  }
-  float r[FD_SLOTS][4];
-  auto fetch = [&](int z) {
-    const int64_t zo = n2 * zwrap(z);
-#pragma unroll
-    for (int s = 0; s < FD_SLOTS; ++s) {
-      if (cell[s] < 0) continue;
-      r[s][0] = ux[zo + off[s]];
-      r[s][1] = uy[zo + off[s]];
-      r[s][2] = uz[zo + off[s]];
-      r[s][3] = rp[zo + off[s]];
-    }
-  };
-
-  // per column: centres of the two planes below, in-plane terms of the plane below
-  float cx_2 = 0.f, cy_2 = 0.f, cr_2 = 0.f, cx_1 = 0.f, cy_1 = 0.f, cr_1 = 0.f;
-  float duz_dy = 0.f, duz_dx = 0.f, duy_dx = 0.f, dux_dy = 0.f, gx = 0.f, gy = 0.f;
-  double curl2 = 0.0, grad2 = 0.0;
-  const int lx = tx + 1, ly = ty + 1;
-
-  fetch(z0 - 1);
-  for (int z = z0 - 1; z <= z1; ++z) {
-    const int b = (z - z0 + 1) & 1;
-#pragma unroll
-    for (int s = 0; s < FD_SLOTS; ++s) {
-      if (cell[s] < 0) continue;
-#pragma unroll
-      for (int f = 0; f < 4; ++f) (&plane[b][f][0][0])[cell[s]] = r[s][f];
-    }
-    if (z < z1) fetch(z + 1);
-    __syncthreads();
-    const float cx_0 = plane[b][0][ly][lx], cy_0 = plane[b][1][ly][lx], cr_0 = plane[b][3][ly][lx];
-    if (active && z >= z0 + 1) {          // plane z - 1 is complete
-      const float dux_dz = 0.5f * (cx_0 - cx_2);
-      const float duy_dz = 0.5f * (cy_0 - cy_2);
-      const float wx = duz_dy - duy_dz, wy = dux_dz - duz_dx, wz = duy_dx - dux_dy;
-      curl2 += (double)(wx * wx + wy * wy + wz * wz);
-      const float gz = 0.5f * (cr_0 - cr_2);
-      grad2 += (double)(gx * gx + gy * gy + gz * gz);
-    }
-    // in-plane terms of plane z, used when plane z + 1 arrives
-    duz_dx = 0.5f * (plane[b][2][ly][lx + 1] - plane[b][2][ly][lx - 1]);
-    duz_dy = 0.5f * (plane[b][2][ly + 1][lx] - plane[b][2][ly - 1][lx]);
-    duy_dx = 0.5f * (plane[b][1][ly][lx + 1] - plane[b][1][ly][lx - 1]);
-    dux_dy = 0.5f * (plane[b][0][ly + 1][lx] - plane[b][0][ly - 1][lx]);
-    gx = 0.5f * (plane[b][3][ly][lx + 1] - plane[b][3][ly][lx - 1]);
-    gy = 0.5f * (plane[b][3][ly + 1][lx] - plane[b][3][ly - 1][lx]);
-    cx_2 = cx_1; cy_2 = cy_1; cr_2 = cr_1;
-    cx_1 = cx_0; cy_1 = cy_0; cr_1 = cr_0;
-  }
-  // partials in dispatch order, so the reduction order does not depend on the remap
-  const double v[NFD] = {curl2, grad2};
-  const int64_t blk = blockIdx.x + (int64_t)gridDim.x * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z);
-  block_reduce_store<NFD, 0u>(v, partials + blk * NFD);
-}
-
-// ---------------------------------------------------------------------------
-// Fixed-order FP64 reduction of the per-block partials into one record, in two
-// launches: kMidBlocks blocks each reduce an even share of the step and stencil
-// partials into one row of NPART + NFD values, then one block reduces the rows
-// and writes the record.  Both orders depend only on the box size, so records
-// are bitwise reproducible.
-// ---------------------------------------------------------------------------
-constexpr int kMidBlocks = 256;
-constexpr int kNV = NPART + NFD;
-constexpr unsigned kMaxMask = 1u << P_UMAX2;
-
-__global__ __launch_bounds__(256) void lbm_mid_kernel(const double* __restrict__ sp, int64_t nsp,
-                                                      const double* __restrict__ fp, int64_t nfp,
-                                                      double* __restrict__ mid) {
-  const int64_t b = blockIdx.x, nb = gridDim.x;
+  int64_t b = blockIdx.x;
+  if (nb % kXcds == 0) b = (b % kXcds) * (nb / kXcds) + b / kXcds;
   double v[kNV];
 #pragma unroll
   for (int k = 0; k < kNV; ++k) v[k] = 0.0;
-  for (int64_t i = nsp * b / nb + threadIdx.x; i < nsp * (b + 1) / nb; i += blockDim.x) {
+  for (int64_t i = nsp * b / nb + threadIdx.x; i < nsp * (b + 1) / nb; i += kNodeBlock) {
 #pragma unroll
     for (int k = 0; k < NPART; ++k)
       v[k] = ((kMaxMask >> k) & 1u) ? fmax(v[k], sp[i * NPART + k]) : v[k] + sp[i * NPART + k];
   }
-  for (int64_t i = nfp * b / nb + threadIdx.x; i < nfp * (b + 1) / nb; i += blockDim.x) {
+  if constexpr (COLUMNS) {
+    __shared__ float plane[2][4][FD_H][FD_W];     // u_x, u_y, u_z, rho'
+    const int n = geo.n, tiles = tiles_x * tiles_y, chunks = (int)(nb / tiles);
+    const int chunk = (int)(b / tiles), tile = (int)(b % tiles);
+    const int x0 = FD_TX * (tile % tiles_x), y0 = FD_TY * (tile / tiles_x);
+    const int tx = threadIdx.x % FD_TX, ty = threadIdx.x / FD_TX;
+    const bool active = (x0 + tx < n) && (y0 + ty < n);
+    const int z0 = (int)((int64_t)n * chunk / chunks), z1 = (int)((int64_t)n * (chunk + 1) / chunks);
+    const int64_t n2 = (int64_t)n * n;
+    auto zwrap = [n](int z) { return z < 0 ? z + n : (z >= n ? z - n : z); };
+
+    // this thread's cells of the staged tile and their in-plane offsets, wrapped once
+    int64_t off[FD_SLOTS];
+    int cell[FD_SLOTS];
 #pragma unroll
-    for (int k = 0; k < NFD; ++k) v[NPART + k] += fp[i * NFD + k];
+    for (int s = 0; s < FD_SLOTS; ++s) {
+      const int c = (int)threadIdx.x + kNodeBlock * s;
+      cell[s] = c < FD_CELLS ? c : -1;
+      const int ly = c / FD_W, lx = c % FD_W;
+      const int gx = ((x0 + lx - 1) % n + n) % n, gy = ((y0 + ly - 1) % n + n) % n;
+      off[s] = c < FD_CELLS ? gx + (int64_t)n * gy : 0;
+    }
+    float r[FD_SLOTS][4];
+    auto fetch = [&](int z) {
+      const int64_t zo = n2 * zwrap(z);
+#pragma unroll
+      for (int s = 0; s < FD_SLOTS; ++s) {
+        if (cell[s] < 0) continue;
+        r[s][0] = ux[zo + off[s]];
+        r[s][1] = uy[zo + off[s]];
+        r[s][2] = uz[zo + off[s]];
+        r[s][3] = rp[zo + off[s]];
+      }
+    };
+
+    // per column: centres of the two planes below, in-plane terms of the plane below
+    float cx_2 = 0.f, cy_2 = 0.f, cr_2 = 0.f, cx_1 = 0.f, cy_1 = 0.f, cr_1 = 0.f;
+    float duz_dy = 0.f, duz_dx = 0.f, duy_dx = 0.f, dux_dy = 0.f, gx = 0.f, gy = 0.f;
+    const int lx = tx + 1, ly = ty + 1;
+
+    fetch(z0 - 1);
+    for (int z = z0 - 1; z <= z1; ++z) {
+      const int b = (z - z0 + 1) & 1;
+#pragma unroll
+      for (int s = 0; s < FD_SLOTS; ++s) {
+        if (cell[s] < 0) continue;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) (&plane[b][f][0][0])[cell[s]] = r[s][f];
+      }
+      if (z < z1) fetch(z + 1);
+      __syncthreads();
+      const float cx_0 = plane[b][0][ly][lx], cy_0 = plane[b][1][ly][lx], cr_0 = plane[b][3][ly][lx];
+      if (active && z >= z0 + 1) {          // plane z - 1 is complete
+        const float dux_dz = 0.5f * (cx_0 - cx_2);
+        const float duy_dz = 0.5f * (cy_0 - cy_2);
+        const float wx = duz_dy - duy_dz, wy = dux_dz - duz_dx, wz = duy_dx - dux_dy;
+        v[NPART + FD_CURL2] += (double)(wx * wx + wy * wy + wz * wz);
+        const float gz = 0.5f * (cr_0 - cr_2);
+        v[NPART + FD_GRAD2] += (double)(gx * gx + gy * gy + gz * gz);
+      }
+      // in-plane terms of plane z, used when plane z + 1 arrives
+      duz_dx = 0.5f * (plane[b][2][ly][lx + 1] - plane[b][2][ly][lx - 1]);
+      duz_dy = 0.5f * (plane[b][2][ly + 1][lx] - plane[b][2][ly - 1][lx]);
+      duy_dx = 0.5f * (plane[b][1][ly][lx + 1] - plane[b][1][ly][lx - 1]);
+      dux_dy = 0.5f * (plane[b][0][ly + 1][lx] - plane[b][0][ly - 1][lx]);
+      gx = 0.5f * (plane[b][3][ly][lx + 1] - plane[b][3][ly][lx - 1]);
+      gy = 0.5f * (plane[b][3][ly + 1][lx] - plane[b][3][ly - 1][lx]);
+      cx_2 = cx_1; cy_2 = cy_1; cr_2 = cr_1;
+      cx_1 = cx_0; cy_1 = cy_0; cr_1 = cr_0;
+    }
+  } else {
+    const uint32_t hi = (uint32_t)(n3 * (b + 1) / nb);
+    for (uint32_t i = (uint32_t)(n3 * b / nb) + threadIdx.x; i < hi; i += kNodeBlock) {
+      const NodeIndex ix = index_of<MODE_ODD, false>(i, geo);
+      const uint32_t xm = ix.at(-1, 0, 0), xp = ix.at(1, 0, 0), ym = ix.at(0, -1, 0), yp = ix.at(0, 1, 0),
+                     zm = ix.at(0, 0, -1), zp = ix.at(0, 0, 1);
+      const float duz_dx = 0.5f * (uz[xp] - uz[xm]), duz_dy = 0.5f * (uz[yp] - uz[ym]);
+      const float duy_dx = 0.5f * (uy[xp] - uy[xm]), duy_dz = 0.5f * (uy[zp] - uy[zm]);
+      const float dux_dy = 0.5f * (ux[yp] - ux[ym]), dux_dz = 0.5f * (ux[zp] - ux[zm]);
+      const float gx = 0.5f * (rp[xp] - rp[xm]), gy = 0.5f * (rp[yp] - rp[ym]), gz = 0.5f * (rp[zp] - rp[zm]);
+      const float wx = duz_dy - duy_dz, wy = dux_dz - duz_dx, wz = duy_dx - dux_dy;
+      v[NPART + FD_CURL2] += (double)(wx * wx + wy * wy + wz * wz);
+      v[NPART + FD_GRAD2] += (double)(gx * gx + gy * gy + gz * gz);
+    }
   }
-  block_reduce_store<kNV, kMaxMask>(v, mid + b * kNV);
+  block_reduce_store<kNV, kMaxMask>(v, rows + b, nb);
 }
 
-__global__ __launch_bounds__(256) void lbm_final_kernel(const double* __restrict__ mid, int64_t rows,
-                                                        double* __restrict__ rec, int64_t step) {
-  constexpr int NV = kNV;
-  double v[NV];
-#pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = 0.0;
-  for (int64_t b = threadIdx.x; b < rows; b += blockDim.x) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k)
-      v[k] = ((kMaxMask >> k) & 1u) ? fmax(v[k], mid[b * NV + k]) : v[k] + mid[b * NV + k];
+// Second stage: one wavefront per value sums the blocks' rows, fixed order, and the record is
+// written.  Both stages' orders depend only on the box size, so records are bitwise
+// reproducible.
+__global__ __launch_bounds__(64 * kNV) void lbm_final_kernel(const double* __restrict__ rows, int64_t nb,
+                                                             double* __restrict__ rec, int64_t step) {
+  const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
+  const bool is_max = ((kMaxMask >> k) & 1u) != 0;
+  double s = 0.0;
+#pragma unroll 8
+  for (int64_t i = lane; i < nb; i += 64) {
+    const double r = rows[k * nb + i];
+    s = is_max ? fmax(s, r) : s + r;
   }
-  __shared__ double out[NV];
-  block_reduce_store<NV, kMaxMask>(v, out);
-  __syncthreads();
+  s = is_max ? wave_reduce<true>(s) : wave_reduce<false>(s);
+  constexpr int slot[kNV] = {R_EK, R_EP, R_DRHO, R_DSIG, R_MX, R_MY, R_MZ, R_UMAX2, R_NONFINITE, R_CURL2, R_GRAD2};
+  static_assert(P_EK == 0 && P_EP == 1 && P_DRHO == 2 && P_DSIG == 3 && P_MX == 4 && P_MY == 5 && P_MZ == 6 &&
+                P_UMAX2 == 7 && P_NONFINITE == 8 && NPART == 9 && FD_CURL2 == 0 && FD_GRAD2 == 1, "record slots");
+  if (lane == 63) rec[slot[k]] = s;
   if (threadIdx.x == 0) {
-    double r[NREC] = {0};
-    r[R_STEP] = (double)step;
-    r[R_EK] = out[P_EK];
-    r[R_EP] = out[P_EP];
-    r[R_CURL2] = out[NPART + FD_CURL2];
-    r[R_GRAD2] = out[NPART + FD_GRAD2];
-    r[R_DRHO] = out[P_DRHO];
-    r[R_DSIG] = out[P_DSIG];
-    r[R_MX] = out[P_MX];
-    r[R_MY] = out[P_MY];
-    r[R_MZ] = out[P_MZ];
-    r[R_UMAX2] = out[P_UMAX2];
-    r[R_NONFINITE] = out[P_NONFINITE];
-    for (int k = 0; k < NREC; ++k) rec[k] = r[k];
+    rec[R_STEP] = (double)step;
+    for (int q = R_NONFINITE + 1; q < NREC; ++q) rec[q] = 0.0;
   }
 }
 
@@ -347,8 +356,9 @@ int derive(const lbm_params* p, Derived* d, char* err) {
 struct Sizes {
   int64_t n3, stride;
   size_t elem, pop_bytes;
-  size_t off_fields, off_sp, off_fp, off_mid, off_ring, work_bytes;
-  int64_t nsp, nfp, nsp_learned;
+  size_t off_fields, off_sp, off_rows, off_ring, work_bytes;
+  int64_t nsp, nsp_learned;
+  FdShape fd;
 };
 
 size_t elem_size(int storage) { return storage == LBM_FP32 ? 4 : 2; }
@@ -369,12 +379,11 @@ Sizes sizes_of(const lbm_params* p) {
   // the learned step runs 256-thread blocks of 128 nodes
   s.nsp_learned = (p->n % 64 == 0) ? (int64_t)p->n * p->n * p->n / 128 : 0;
   const int64_t nsp_max = s.nsp > s.nsp_learned ? s.nsp : s.nsp_learned;
-  s.nfp = (int64_t)((p->n + FD_TX - 1) / FD_TX) * ((p->n + FD_TY - 1) / FD_TY) * ((p->n + FD_ZC - 1) / FD_ZC);
+  s.fd = fd_shape(p->n);
   size_t off = 0;
   s.off_fields = off; off = align_up(off + (size_t)(5 * s.n3) * sizeof(float), kAlign);
   s.off_sp = off;     off = align_up(off + (size_t)(nsp_max * NPART) * sizeof(double), kAlign);
-  s.off_fp = off;     off = align_up(off + (size_t)(s.nfp * NFD) * sizeof(double), kAlign);
-  s.off_mid = off;    off = align_up(off + (size_t)kMidBlocks * kNV * sizeof(double), kAlign);
+  s.off_rows = off;   off = align_up(off + (size_t)(s.fd.blocks * kNV) * sizeof(double), kAlign);
   s.off_ring = off;   off = align_up(off + (size_t)kRingCap * NREC * sizeof(double), kAlign);
   s.work_bytes = off;
   return s;
@@ -423,8 +432,7 @@ hipError_t launch_node(lbm_ctx* c, int mode, int flags, char* src, char* dst, fl
 
 float* fields_buf(lbm_ctx* c) { return (float*)(c->work + c->sz.off_fields); }
 double* sp_buf(lbm_ctx* c) { return (double*)(c->work + c->sz.off_sp); }
-double* fp_buf(lbm_ctx* c) { return (double*)(c->work + c->sz.off_fp); }
-double* mid_buf(lbm_ctx* c) { return (double*)(c->work + c->sz.off_mid); }
+double* rows_buf(lbm_ctx* c) { return (double*)(c->work + c->sz.off_rows); }
 double* ring_buf(lbm_ctx* c) { return (double*)(c->work + c->sz.off_ring); }
 
 // Layout of the current state for the gather of a moment-only pass.
@@ -436,21 +444,20 @@ char* current_array(const lbm_ctx* c) {
   return (c->p.layout == LBM_LAYOUT_AB && c->odd) ? c->pop_b : c->pop;
 }
 
-// Queue the dissipation stencil and the final reduction into the next ring slot.
+// Queue the dissipation stencil and the reduction into the next ring slot.
 hipError_t queue_record(lbm_ctx* c, int64_t step, bool learned) {
-  const dim3 fblock(FD_TX, FD_TY, 1);
-  const dim3 fgrid((c->p.n + FD_TX - 1) / FD_TX, (c->p.n + FD_TY - 1) / FD_TY,
-                   (c->p.n + FD_ZC - 1) / FD_ZC);
-  hipLaunchKernelGGL(lbm_fd_kernel, fgrid, fblock, 0, c->stream, fields_buf(c), c->p.n, fp_buf(c));
+  const FdShape& fd = c->sz.fd;
+  const int64_t nsp = learned ? c->sz.nsp_learned : c->sz.nsp;
+  if (fd.columns)
+    hipLaunchKernelGGL(lbm_fd_kernel<true>, dim3((unsigned)fd.blocks), dim3(kNodeBlock), 0, c->stream, fields_buf(c),
+                       c->geo, fd.tx, fd.ty, sp_buf(c), nsp, rows_buf(c));
+  else
+    hipLaunchKernelGGL(lbm_fd_kernel<false>, dim3((unsigned)fd.blocks), dim3(kNodeBlock), 0, c->stream, fields_buf(c),
+                       c->geo, fd.tx, fd.ty, sp_buf(c), nsp, rows_buf(c));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   double* slot = ring_buf(c) + (c->ring_head % kRingCap) * NREC;
-  hipLaunchKernelGGL(lbm_mid_kernel, dim3(kMidBlocks), dim3(256), 0, c->stream, sp_buf(c),
-                     learned ? c->sz.nsp_learned : c->sz.nsp, fp_buf(c), c->sz.nfp, mid_buf(c));
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lbm_final_kernel, dim3(1), dim3(256), 0, c->stream, mid_buf(c),
-                     (int64_t)kMidBlocks, slot, step);
+  hipLaunchKernelGGL(lbm_final_kernel, dim3(1), dim3(64 * kNV), 0, c->stream, rows_buf(c), fd.blocks, slot, step);
   e = hipGetLastError();
   if (e == hipSuccess) c->ring_head++;
   return e;

@@ -509,10 +509,11 @@ __global__ __launch_bounds__(64 * kReduceSlices) void grad_reduce_kernel(const f
   } else {
 #pragma unroll 4
     for (int64_t b = threadIdx.x; b < nblocks; b += 64 * kReduceSlices) s += lpart[b];
-    s = wave_sum(s);
-    if (lane == 0) part[slice][0] = s;
+    s = wave_reduce<false>(s);
+    if (lane == 63) part[slice][0] = s;
     __syncthreads();
     if (threadIdx.x != 0) return;
+    s = part[0][0];
     for (int k = 1; k < kReduceSlices; ++k) s += part[k][0];
     *loss = s / ((double)batch * N_OUT);
   }
@@ -634,19 +635,19 @@ __global__ __launch_bounds__(64) void norm_kernel(const double* __restrict__ par
     double s = 0.0;
 #pragma unroll 4
     for (int b = lane; b < nblocks; b += 64) s += part[stat * nblocks + b];
-    return wave_sum(s);
+    return wave_reduce<false>(s);      // in lane 63
   };
   if (c < N_IN) {
     const double s = total(c), s2 = total(N_IN + c);
     const double mean = s / rows;
     const double var = s2 / rows - mean * mean;
-    if (lane == 0) {
+    if (lane == 63) {
       norm[c] = (float)mean;
       norm[N_IN + c] = var > 1e-300 ? (float)(1.0 / sqrt(var)) : 0.f;
     }
   } else {
     const double ms = total(N_IN + c) / rows;       // statistic 2 N_IN + (c - N_IN)
-    if (lane == 0) norm[N_IN + c] = ms > 1e-300 ? (float)sqrt(ms) : 1.f;
+    if (lane == 63) norm[N_IN + c] = ms > 1e-300 ? (float)sqrt(ms) : 1.f;
   }
 }
 

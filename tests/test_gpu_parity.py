@@ -618,3 +618,35 @@ def test_zero_steps_change_nothing(layout):
     assert stgv.lbm_get_step(sim.ctx) == 1
     assert [r["step"] for r in sim.diagnostics()] == [0]
     sim.close()
+
+
+# ----------------------------------------------------------------------------
+# the record's stencil and reductions over box shapes
+# ----------------------------------------------------------------------------
+@pytest.mark.parametrize("n", [4, 5, 20, 65, 100, 191, 192, 193, 260])
+def test_record_of_a_random_state_matches_fp64_of_its_fields(n):
+    # linear-order blocks below 192^3, tiles of columns from there (partial tiles in x and y at 193
+    # and 260, uneven z chunks); fewer and more step blocks than stencil blocks
+    kw = dict(n=n, q_f=19, q_g=7, forcing="shift", u0=0.05, re=100.0, fr=0.5, sc=0.7, g_over_n=0.5)
+    sim = stgv.Simulation(**kw)
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    sim.load((torch.rand((26, n, n, n), generator=gen, device="cuda:0") - 0.5) * 2e-3, step=0)
+    sim.sample()
+    rec = sim.diagnostics(raise_unstable=False)[0]
+    rho1, ux, uy, uz, rp = (v.double() for v in sim.fields())
+    U = model.units(model.Params(**kw))
+
+    def diff(a, axis):
+        return 0.5 * (torch.roll(a, -1, axis) - torch.roll(a, 1, axis))
+    curl = (diff(uz, 1) - diff(uy, 0), diff(ux, 0) - diff(uz, 2), diff(uy, 2) - diff(ux, 1))
+    usq = ux * ux + uy * uy + uz * uz
+    ref = dict(ek=0.5 * usq.mean() / 0.05 ** 2, ep=0.5 * (0.5 * rp).square().mean() / 0.05 ** 2,
+               eps_k=U.nu * sum(w.square().mean() for w in curl) * U.L / 0.05 ** 3,
+               eps_p=U.D * 0.25 * sum(diff(rp, a).square().mean() for a in (0, 1, 2)) * U.L / 0.05 ** 3,
+               umax=usq.max().sqrt(), mass=n ** 3 + rho1.sum())
+    for k, v in ref.items():
+        # a handful of FP32 roundings per node (6e-8 each); n = 4 has central differences that
+        # cancel to no more than the values themselves
+        assert abs(rec[k] - float(v)) <= 2e-6 * abs(float(v)), (n, k, rec[k], float(v))
+    assert rec["nonfinite"] == 0
+    sim.close()
