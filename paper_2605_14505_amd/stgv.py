@@ -184,10 +184,18 @@ def lbm_sample(ctx):
 
 
 def lbm_diagnostics(ctx, max_records=4096, raise_unstable=True):
-    buf = (lbm_diag * max_records)()
-    got = ctypes.c_int32()
-    st = LIB.lbm_diagnostics(ctx, buf, max_records, ctypes.byref(got))
-    recs = [buf[i].as_dict() for i in range(got.value)]
+    # drained in buffers of up to 256 records: a buffer for a full ring takes longer to make than
+    # the usual few records take to fetch
+    recs, st = [], LBM_OK
+    while True:
+        room = min(max_records - len(recs), 256)
+        buf = (lbm_diag * room)()
+        got = ctypes.c_int32()
+        last = LIB.lbm_diagnostics(ctx, buf, room, ctypes.byref(got))
+        recs += [buf[i].as_dict() for i in range(got.value)]
+        st = last if last != LBM_OK else st
+        if last not in (LBM_OK, LBM_EUNSTABLE) or got.value < room or len(recs) == max_records:
+            break
     if st != LBM_OK and (st != LBM_EUNSTABLE or raise_unstable):
         raise LbmError(st, LIB.lbm_last_error(ctx).decode())
     return recs, st

@@ -650,3 +650,24 @@ def test_record_of_a_random_state_matches_fp64_of_its_fields(n):
         assert abs(rec[k] - float(v)) <= 2e-6 * abs(float(v)), (n, k, rec[k], float(v))
     assert rec["nonfinite"] == 0
     sim.close()
+
+
+def test_records_drained_in_runs_equal_records_drained_singly():
+    # several buffers per drain, a drain across the ring's end, and a limit below what is pending
+    a, b = (gpu_sim(**c1_kw(n=4, diag_every=1, g_over_n=0.02)) for _ in range(2))
+    ra, rb = [], []
+    for steps in (300, 3900, 257, 128, 1):
+        a.step(steps)
+        b.step(steps)
+        if steps == 257:
+            part, st = stgv.lbm_diagnostics(a.ctx, max_records=100)
+            assert st == stgv.LBM_OK and len(part) == 100
+            ra += part
+        ra += a.diagnostics()
+        while True:
+            one, _ = stgv.lbm_diagnostics(b.ctx, max_records=1)
+            rb += one
+            if not one:
+                break
+    assert [r["step"] for r in ra] == list(range(4586))
+    assert ra == rb
