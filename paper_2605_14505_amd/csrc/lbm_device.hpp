@@ -123,27 +123,22 @@ template <typename C, bool NT = false> __device__ __forceinline__ C load_as(cons
   return (C)__uint_as_float(((uint32_t)get<NT>(&p->bits)) << 16);
 }
 
-// Population stores bypass the caches by default (each value is read again only
-// one step later, after the whole ~GB state has streamed through).
-#ifndef STGV_NT_STORE
-#define STGV_NT_STORE 1
-#endif
-template <typename T>
+// Population stores bypass the caches too (NT) where the state does not stay in them
+// (cached_state): each value is read again only one step later, after the whole ~GB state has
+// streamed through.
+template <bool NT = true, typename T>
 __device__ __forceinline__ void put(T* p, T v) {
-#if STGV_NT_STORE
-  __builtin_nontemporal_store(v, p);
-#else
-  *p = v;
-#endif
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
 }
 // Rounding to the storage type is round-to-nearest-even in every case (a double
 // is rounded once, straight to FP32; FP16 / BF16 stores take FP32 values, and
 // the BF16 conversion is gfx950's own, v_cvt_pk_bf16_f32).
-__device__ __forceinline__ void store_as(float* p, float v) { put(p, v); }
-__device__ __forceinline__ void store_as(float* p, double v) { put(p, (float)v); }
-__device__ __forceinline__ void store_as(_Float16* p, float v) { put(p, (_Float16)v); }
-__device__ __forceinline__ void store_as(bf16_t* p, float v) {
-  put(&p->bits, __builtin_bit_cast(uint16_t, (__bf16)v));   // gfx950 converts in hardware
+template <bool NT = true> __device__ __forceinline__ void store_as(float* p, float v) { put<NT>(p, v); }
+template <bool NT = true> __device__ __forceinline__ void store_as(float* p, double v) { put<NT>(p, (float)v); }
+template <bool NT = true> __device__ __forceinline__ void store_as(_Float16* p, float v) { put<NT>(p, (_Float16)v); }
+template <bool NT = true> __device__ __forceinline__ void store_as(bf16_t* p, float v) {
+  put<NT>(&p->bits, __builtin_bit_cast(uint16_t, (__bf16)v));   // gfx950 converts in hardware
 }
 
 // ---------------------------------------------------------------------------
@@ -207,7 +202,8 @@ __device__ __forceinline__ void gather_seq(C* v, const T* pop, int first, const 
   (gather_one<Q, T, MODE, NTX, CACHED, I>(v, pop, first, ix, stride), ...);
 }
 // NTX: non-temporal loads for the odd step's x-aligned directions.  CACHED: no
-// non-temporal loads, for kernels that read a node more than once.
+// non-temporal loads (a state that stays in the last-level cache, or a kernel that reads a
+// node more than once).
 template <int Q, typename T, int MODE, bool NTX = false, bool CACHED = false, typename C>
 __device__ __forceinline__ void gather(C* v, const T* pop, int first, const NodeIndex& ix,
                                        int64_t stride) {
@@ -216,7 +212,7 @@ __device__ __forceinline__ void gather(C* v, const T* pop, int first, const Node
 
 // Scatter post-collision populations for MODE (AB writes into `dst`), one compile-time
 // direction at a time like gather.
-template <int Q, typename T, int MODE, int I, typename C>
+template <int Q, typename T, int MODE, bool CACHED, int I, typename C>
 __device__ __forceinline__ void scatter_one(const C* v, T* dst, int first, const NodeIndex& ix,
                                             int64_t stride) {
   using S = Stencil<Q>;
@@ -224,17 +220,17 @@ __device__ __forceinline__ void scatter_one(const C* v, T* dst, int first, const
                                              // odd / AB push: natural slot i at x + e_i
   const uint32_t off = even ? ix.base : ix.at(S::ex[I], S::ey[I], S::ez[I]);
   const int slot = even ? opp(I) : I;
-  store_as(at_node(dst + (int64_t)(first + slot) * stride, off), v[I]);
+  store_as<!CACHED>(at_node(dst + (int64_t)(first + slot) * stride, off), v[I]);
 }
-template <int Q, typename T, int MODE, typename C, int... I>
+template <int Q, typename T, int MODE, bool CACHED, typename C, int... I>
 __device__ __forceinline__ void scatter_seq(const C* v, T* dst, int first, const NodeIndex& ix,
                                             int64_t stride, std::integer_sequence<int, I...>) {
-  (scatter_one<Q, T, MODE, I>(v, dst, first, ix, stride), ...);
+  (scatter_one<Q, T, MODE, CACHED, I>(v, dst, first, ix, stride), ...);
 }
-template <int Q, typename T, int MODE, typename C>
+template <int Q, typename T, int MODE, bool CACHED = false, typename C>
 __device__ __forceinline__ void scatter(const C* v, T* dst, int first, const NodeIndex& ix,
                                         int64_t stride) {
-  scatter_seq<Q, T, MODE>(v, dst, first, ix, stride, std::make_integer_sequence<int, Q>{});
+  scatter_seq<Q, T, MODE, CACHED>(v, dst, first, ix, stride, std::make_integer_sequence<int, Q>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -270,8 +266,8 @@ __device__ __forceinline__ void put_rounded(bf16_t* p, bf16_t v) { put(&p->bits,
 // value that belongs across the edge stores it there, at x +- bx.  Every lane does one
 // load and one store per direction, every destination is written once, and the node
 // that reads a location before the step is the one that writes it, as in the plain AA
-// step.  All accesses are whole aligned lines except the two seam lanes', and bypass the
-// caches.
+// step.  All accesses are whole aligned lines except the two seam lanes'.  NT0 and NTX: whether
+// the accesses of the directions with e_x = 0 and of the others bypass the caches.
 // ---------------------------------------------------------------------------
 template <int Q>
 constexpr int x_slot(int i) {     // index of direction i among those with e_x != 0
@@ -316,7 +312,7 @@ __device__ __forceinline__ RowLane make_rowlane(int x, int n) {
 
 // The loads go to registers first (row_load_one) and are written to the ring or converted
 // afterwards (row_stage_one), so that a kernel can issue all of them before its first wait.
-template <int Q, typename T, bool NTX, int I>
+template <int Q, typename T, bool NT0, bool NTX, int I>
 __device__ __forceinline__ void row_load_one(T* raw, const T* pop, int first, const NodeIndex& ix, int64_t stride,
                                              const RowLane& l) {
   using S = Stencil<Q>;
@@ -324,7 +320,7 @@ __device__ __forceinline__ void row_load_one(T* raw, const T* pop, int first, co
   // the ring's seam lane for e_x = +1 is the last, for e_x = -1 the first
   const uint32_t xl = ex > 0 ? l.x_b : (ex < 0 ? l.x_a : l.x_own);
   const T* p = at_node(pop + (int64_t)(first + opp(I)) * stride, xl + ix.yo[1 - S::ey[I]] + ix.zo[1 - S::ez[I]]);
-  raw[I] = raw_load<ex == 0 || NTX>(p);
+  raw[I] = raw_load<ex == 0 ? NT0 : NTX>(p);
 }
 template <int Q, typename T, int I, typename C>
 __device__ __forceinline__ void row_stage_one(C* v, const T* raw, T (*xs)[256], int k0, const RowLane& l) {
@@ -342,7 +338,7 @@ __device__ __forceinline__ void row_put_one(const C* v, T (*xs)[256], int k0, co
   if constexpr (S::ex[I] != 0)
     xs[k0 + x_slot<Q>(I)][S::ex[I] > 0 ? l.place_p : l.place_m] = rounded((const T*)nullptr, v[I]);
 }
-template <int Q, typename T, bool NTX, int I, typename C>
+template <int Q, typename T, bool NT0, bool NTX, int I, typename C>
 __device__ __forceinline__ void row_store_one(const C* v, const T (*xs)[256], int k0, T* dst, int first,
                                               const NodeIndex& ix, int64_t stride, const RowLane& l) {
   using S = Stencil<Q>;
@@ -351,14 +347,14 @@ __device__ __forceinline__ void row_store_one(const C* v, const T (*xs)[256], in
   // e_x = +1, the last lane's for e_x = -1
   const uint32_t xd = ex > 0 ? l.x_a : (ex < 0 ? l.x_b : l.x_own);
   T* p = at_node(dst + (int64_t)(first + I) * stride, xd + ix.yo[1 + S::ey[I]] + ix.zo[1 + S::ez[I]]);
-  if constexpr (ex == 0) store_as(p, v[I]);
+  if constexpr (ex == 0) store_as<NT0>(p, v[I]);
   else raw_store<NTX>(p, xs[k0 + x_slot<Q>(I)][l.lid]);
 }
 
-template <int Q, typename T, bool NTX, int... I>
+template <int Q, typename T, bool NT0, bool NTX, int... I>
 __device__ __forceinline__ void row_load(T* raw, const T* pop, int first, const NodeIndex& ix, int64_t stride,
                                          const RowLane& l, std::integer_sequence<int, I...>) {
-  (row_load_one<Q, T, NTX, I>(raw, pop, first, ix, stride, l), ...);
+  (row_load_one<Q, T, NT0, NTX, I>(raw, pop, first, ix, stride, l), ...);
 }
 template <int Q, typename T, typename C, int... I>
 __device__ __forceinline__ void row_stage(C* v, const T* raw, T (*xs)[256], int k0, const RowLane& l,
@@ -375,11 +371,11 @@ __device__ __forceinline__ void row_put(const C* v, T (*xs)[256], int k0, const 
                                         std::integer_sequence<int, I...>) {
   (row_put_one<Q, T, I>(v, xs, k0, l), ...);
 }
-template <int Q, typename T, bool NTX, typename C, int... I>
+template <int Q, typename T, bool NT0, bool NTX, typename C, int... I>
 __device__ __forceinline__ void row_store(const C* v, const T (*xs)[256], int k0, T* dst, int first,
                                           const NodeIndex& ix, int64_t stride, const RowLane& l,
                                           std::integer_sequence<int, I...>) {
-  (row_store_one<Q, T, NTX, I>(v, xs, k0, dst, first, ix, stride, l), ...);
+  (row_store_one<Q, T, NT0, NTX, I>(v, xs, k0, dst, first, ix, stride, l), ...);
 }
 
 // ---------------------------------------------------------------------------

@@ -12,54 +12,52 @@ namespace stgv {
 // helpers, whose template arguments do not name the compute type.
 namespace {
 
-template <int QF, int QG, int FORCE, typename T, int MODE, int FLAGS>
-hipError_t go_step(hipStream_t st, T* pop, T* dst, Geometry geo,
-                   PhysConsts c, float* fields, double* partials) {
+template <int QF, int QG, int FORCE, typename T, int MODE, int FLAGS, bool ROWS, bool CACHED>
+hipError_t go_step(hipStream_t st, T* pop, T* dst, Geometry geo, PhysConsts c, float* fields, double* partials) {
   const size_t lds = (MODE == MODE_EVEN && FLAGS == K_COLLIDE) ? even_step_lds(sizeof(T), geo.n) : 0;
-  const dim3 grid(node_blocks(geo.n)), block(kNodeBlock);
-  if constexpr (MODE != MODE_EVEN) {
-    if (geo.n % 64 == 0) {
-      hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS, true>), grid, block, lds, st, pop, dst,
-                         geo, c, fields, partials);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS, false>), grid, block, lds, st, pop, dst, geo,
-                     c, fields, partials);
+  hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS, ROWS, CACHED>), dim3(node_blocks(geo.n)),
+                     dim3(kNodeBlock), lds, st, pop, dst, geo, c, fields, partials);
   return hipGetLastError();
 }
 
-template <int QF, int QG, int FORCE, typename T>
-hipError_t step_force(int mode, bool diag, hipStream_t st, T* pop, T* dst,
-                      Geometry geo, PhysConsts c, float* fields, double* partials) {
+template <int QF, int QG, int FORCE, typename T, bool CACHED>
+hipError_t step_mode(int mode, bool diag, hipStream_t st, T* pop, T* dst, Geometry geo, PhysConsts c, float* fields,
+                     double* partials) {
   constexpr int STEP = K_COLLIDE;
   constexpr int STEP_DIAG = K_COLLIDE | K_FIELDS | K_PARTIALS;
-#define STGV_GO(M) \
-  return diag ? go_step<QF, QG, FORCE, T, M, STEP_DIAG>(st, pop, dst, geo, c, fields, partials) \
-              : go_step<QF, QG, FORCE, T, M, STEP>(st, pop, dst, geo, c, fields, partials)
-  if (mode == MODE_EVEN) STGV_GO(MODE_EVEN);
+#define STGV_GO(M, FL, ROWS) return go_step<QF, QG, FORCE, T, M, FL, ROWS, CACHED>(st, pop, dst, geo, c, fields, partials)
+  if (mode == MODE_EVEN) { if (diag) STGV_GO(MODE_EVEN, STEP_DIAG, false); STGV_GO(MODE_EVEN, STEP, false); }
+  if (mode == MODE_AB) { if (diag) STGV_GO(MODE_AB, STEP_DIAG, false); STGV_GO(MODE_AB, STEP, false); }
+  if (mode != MODE_ODD) return hipErrorInvalidValue;
+  if (diag) STGV_GO(MODE_ODD, STEP_DIAG, false);
   if constexpr (sizeof(STGV_C) == 4 && ring_pair<QF, QG>(sizeof(T))) {
     const bool whole = ring_whole(geo.n, sizeof(T));
-    if (mode == MODE_ODD && !diag && (whole || ring_part(geo.n))) {
+    if (whole || ring_part(geo.n)) {
       const LaunchShape sh = ring_launch(geo.n);
       const size_t lds = ring_step_lds(sizeof(T), (size_t)(x_moving<QF>() + x_moving<QG>()) * 256 * sizeof(T));
       if (whole)
-        hipLaunchKernelGGL((lbm_step_ring_kernel<QF, QG, FORCE, T, STGV_C, false>), sh.grid, sh.block, lds,
-                           st, pop, geo, c);
+        hipLaunchKernelGGL((lbm_step_ring_kernel<QF, QG, FORCE, T, STGV_C, false, CACHED>), sh.grid, sh.block, lds, st,
+                           pop, geo, c);
       else
-        hipLaunchKernelGGL((lbm_step_ring_kernel<QF, QG, FORCE, T, STGV_C, true>), sh.grid, sh.block, lds,
-                           st, pop, geo, c);
+        hipLaunchKernelGGL((lbm_step_ring_kernel<QF, QG, FORCE, T, STGV_C, true, false>), sh.grid, sh.block, lds, st,
+                           pop, geo, c);
       return hipGetLastError();
     }
   }
-  if (mode == MODE_ODD) STGV_GO(MODE_ODD);
-  if (mode == MODE_AB) STGV_GO(MODE_AB);
+  if (geo.n % 64 == 0) STGV_GO(MODE_ODD, STEP, true);
+  STGV_GO(MODE_ODD, STEP, false);
 #undef STGV_GO
-  return hipErrorInvalidValue;
+}
+
+template <int QF, int QG, int FORCE, typename T>
+hipError_t step_force(int mode, bool diag, bool cached, hipStream_t st, T* pop, T* dst, Geometry geo, PhysConsts c,
+                      float* fields, double* partials) {
+  return cached ? step_mode<QF, QG, FORCE, T, true>(mode, diag, st, pop, dst, geo, c, fields, partials)
+                : step_mode<QF, QG, FORCE, T, false>(mode, diag, st, pop, dst, geo, c, fields, partials);
 }
 
 template <int QF, int QG, typename T>
-hipError_t step_pair(int force, int mode, int flags, hipStream_t st, T* pop,
+hipError_t step_pair(int force, int mode, int flags, bool cached, hipStream_t st, T* pop,
                      T* dst, Geometry geo, PhysConsts c, float* fields, double* partials) {
   constexpr int STEP = K_COLLIDE;
   constexpr int STEP_DIAG = K_COLLIDE | K_FIELDS | K_PARTIALS;
@@ -68,16 +66,16 @@ hipError_t step_pair(int force, int mode, int flags, hipStream_t st, T* pop,
   if (flags == STEP || flags == STEP_DIAG) {
     const bool d = flags == STEP_DIAG;
     switch (force) {
-      case FORCE_GUO: return step_force<QF, QG, FORCE_GUO, T>(mode, d, st, pop, dst, geo, c, fields, partials);
-      case FORCE_SHIFT: return step_force<QF, QG, FORCE_SHIFT, T>(mode, d, st, pop, dst, geo, c, fields, partials);
-      case FORCE_EDM: return step_force<QF, QG, FORCE_EDM, T>(mode, d, st, pop, dst, geo, c, fields, partials);
-      case FORCE_HCZ: return step_force<QF, QG, FORCE_HCZ, T>(mode, d, st, pop, dst, geo, c, fields, partials);
+      case FORCE_GUO: return step_force<QF, QG, FORCE_GUO, T>(mode, d, cached, st, pop, dst, geo, c, fields, partials);
+      case FORCE_SHIFT: return step_force<QF, QG, FORCE_SHIFT, T>(mode, d, cached, st, pop, dst, geo, c, fields, partials);
+      case FORCE_EDM: return step_force<QF, QG, FORCE_EDM, T>(mode, d, cached, st, pop, dst, geo, c, fields, partials);
+      case FORCE_HCZ: return step_force<QF, QG, FORCE_HCZ, T>(mode, d, cached, st, pop, dst, geo, c, fields, partials);
       default: return hipErrorInvalidValue;
     }
   }
   // Moment-only passes read the natural layout (MODE_EVEN, also the AB lattice)
   // or the odd AA layout; the physical velocity does not depend on the forcing.
-#define STGV_GO(M, FL) return go_step<QF, QG, FORCE_GUO, T, M, FL>(st, pop, dst, geo, c, fields, partials)
+#define STGV_GO(M, FL) return go_step<QF, QG, FORCE_GUO, T, M, FL, false, false>(st, pop, dst, geo, c, fields, partials)
   const int gm = (mode == MODE_ODD) ? MODE_ODD : MODE_EVEN;
   if (flags == SAMPLE) {
     if (gm == MODE_EVEN) STGV_GO(MODE_EVEN, SAMPLE);
@@ -94,11 +92,11 @@ hipError_t step_pair(int force, int mode, int flags, hipStream_t st, T* pop,
 }  // namespace
 
 template <>
-hipError_t launch_step<STGV_T, STGV_C>(int qf, int qg, int force, int mode, int flags,
+hipError_t launch_step<STGV_T, STGV_C>(int qf, int qg, int force, int mode, int flags, bool cached,
                                hipStream_t st, STGV_T* pop, STGV_T* dst,
                                Geometry geo, PhysConsts c, float* fields, double* partials) {
 #define STGV_STEP_PAIR(A, B) \
-  if (qf == A && qg == B) return step_pair<A, B, STGV_T>(force, mode, flags, st, pop, dst, geo, c, fields, partials);
+  if (qf == A && qg == B) return step_pair<A, B, STGV_T>(force, mode, flags, cached, st, pop, dst, geo, c, fields, partials);
   STGV_FOR_EACH_PAIR(STGV_STEP_PAIR)
 #undef STGV_STEP_PAIR
   return hipErrorInvalidValue;
@@ -117,30 +115,37 @@ hipError_t launch_init<STGV_T>(int qf, int qg, hipStream_t st, STGV_T* pop,
   return hipErrorInvalidValue;
 }
 
-template <>
-hipError_t launch_stream<STGV_T>(int qf, int qg, int mode, hipStream_t st,
-                                 STGV_T* pop, STGV_T* dst, Geometry geo) {
-  const bool whole = ring_whole(geo.n, sizeof(STGV_T)), ring = mode == MODE_ODD && (whole || ring_part(geo.n));
-  const bool rows = geo.n % 64 == 0;
+template <int A, int B, bool CACHED>
+static hipError_t stream_pair(int mode, hipStream_t st, STGV_T* pop, STGV_T* dst, Geometry geo) {
   const dim3 grid(node_blocks(geo.n)), block(kNodeBlock);
+  if constexpr (ring_pair<A, B>(sizeof(STGV_T))) {
+    const bool whole = ring_whole(geo.n, sizeof(STGV_T));
+    if (mode == MODE_ODD && (whole || ring_part(geo.n))) {
+      const LaunchShape sh = ring_launch(geo.n);
+      const size_t lds = ring_step_lds(sizeof(STGV_T), (size_t)(x_moving<A>() + x_moving<B>()) * 256 * sizeof(STGV_T));
+      if (whole) hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, false, CACHED>), sh.grid, sh.block, lds, st, pop, geo);
+      else hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, true, false>), sh.grid, sh.block, lds, st, pop, geo);
+      return hipGetLastError();
+    }
+  }
+  if (mode == MODE_EVEN)
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN, false, CACHED>), grid, block,
+                       even_step_lds(sizeof(STGV_T), geo.n), st, pop, dst, geo);
+  else if (mode == MODE_AB)
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, false, CACHED>), grid, block, 0, st, pop, dst, geo);
+  else if (geo.n % 64 == 0)
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, true, CACHED>), grid, block, 0, st, pop, dst, geo);
+  else
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, false, CACHED>), grid, block, 0, st, pop, dst, geo);
+  return hipGetLastError();
+}
+
+template <>
+hipError_t launch_stream<STGV_T>(int qf, int qg, int mode, bool cached, hipStream_t st, STGV_T* pop, STGV_T* dst,
+                                 Geometry geo) {
 #define STGV_STREAM(A, B) \
-  if (qf == A && qg == B) { \
-    if constexpr (ring_pair<A, B>(sizeof(STGV_T))) { \
-      if (ring) { \
-        const LaunchShape sh = ring_launch(geo.n); \
-        const size_t lds = ring_step_lds(sizeof(STGV_T), (size_t)(x_moving<A>() + x_moving<B>()) * 256 * sizeof(STGV_T)); \
-        if (whole) hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, false>), sh.grid, sh.block, lds, st, pop, geo); \
-        else hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, true>), sh.grid, sh.block, lds, st, pop, geo); \
-        return hipGetLastError(); \
-      } \
-    } \
-    if (mode == MODE_EVEN) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN, false>), grid, block, even_step_lds(sizeof(STGV_T), geo.n), st, pop, dst, geo); \
-    else if (mode == MODE_ODD && rows) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, true>), grid, block, 0, st, pop, dst, geo); \
-    else if (mode == MODE_ODD) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, false>), grid, block, 0, st, pop, dst, geo); \
-    else if (mode == MODE_AB && rows) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, true>), grid, block, 0, st, pop, dst, geo); \
-    else if (mode == MODE_AB) hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, false>), grid, block, 0, st, pop, dst, geo); \
-    else return hipErrorInvalidValue; \
-    return hipGetLastError(); }
+  if (qf == A && qg == B) \
+    return cached ? stream_pair<A, B, true>(mode, st, pop, dst, geo) : stream_pair<A, B, false>(mode, st, pop, dst, geo);
   STGV_FOR_EACH_PAIR(STGV_STREAM)
 #undef STGV_STREAM
   return hipErrorInvalidValue;

@@ -104,7 +104,7 @@ template <int MODE, int FLAGS, typename T, int QF>
 constexpr bool kBatchBf16 = MODE == MODE_EVEN && FLAGS == K_COLLIDE && std::is_same<T, bf16_t>::value && QF == 27;
 #define STGV_OPERANDS_27(a) "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15]), "+v"(a[16]), "+v"(a[17]), "+v"(a[18]), "+v"(a[19]), "+v"(a[20]), "+v"(a[21]), "+v"(a[22]), "+v"(a[23]), "+v"(a[24]), "+v"(a[25]), "+v"(a[26])
 
-template <int QF, int QG, int FORCE, typename T, typename C, int MODE, int FLAGS, bool ROWS>
+template <int QF, int QG, int FORCE, typename T, typename C, int MODE, int FLAGS, bool ROWS, bool CACHED>
 __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, T* dst, Geometry geo,
                                                        PhysConsts c, float* __restrict__ fields,
                                                        double* __restrict__ partials) {
@@ -120,9 +120,9 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
   if (active) {
     const NodeIndex ix = index_of<MODE, ROWS>(node, geo);
     C f[QF], g[QG];
-    gather<QF, T, MODE, true>(f, pop, 0, ix, geo.stride);
+    gather<QF, T, MODE, true, CACHED>(f, pop, 0, ix, geo.stride);
     if constexpr (kBatchBf16<MODE, FLAGS, T, QF>) asm volatile("" : STGV_OPERANDS_27(f) :: "memory");
-    gather<QG, T, MODE, true>(g, pop, QF, ix, geo.stride);
+    gather<QG, T, MODE, true, CACHED>(g, pop, QF, ix, geo.stride);
     StepMacro<C> m;
     step_macro<QF, QG, FORCE, sizeof(T) == 4>(f, g, c, m);
     if (FLAGS & (K_FIELDS | K_PARTIALS)) {
@@ -132,8 +132,8 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
     }
     if (FLAGS & K_COLLIDE) {
       step_collide<QF, QG, FORCE, sizeof(T) == 4>(f, g, c, m);
-      scatter<QF, T, MODE>(f, dst, 0, ix, geo.stride);
-      scatter<QG, T, MODE>(g, dst, QF, ix, geo.stride);
+      scatter<QF, T, MODE, CACHED>(f, dst, 0, ix, geo.stride);
+      scatter<QG, T, MODE, CACHED>(g, dst, QF, ix, geo.stride);
     }
   }
   if (kPart) {
@@ -147,7 +147,8 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
 // so every lane is active and reaches the barriers.
 // PART: blocks holding part of a row, whose x-moving loads and stores use the cache
 // policy STGV_RING_PART_NT_XLOAD / STGV_RING_PART_NT_XSTORE (1 = bypass); whole-row
-// blocks bypass the caches for every access.  A seam lane's load shares its line with
+// blocks bypass the caches for every access.  CACHED: every access goes through them
+// (cached_state).  A seam lane's load shares its line with
 // the neighbouring block's aligned load, which finds it in L2 only if it was loaded
 // cached: 512^3 odd step FP16 5.21 -> 4.80 ms, BF16 5.67 -> 4.82 ms with cached x-moving
 // loads; cached x-moving stores changed nothing further (4.80 / 4.80) and alone gave
@@ -161,20 +162,20 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
 // All of a ring kernel's loads, issued before the first wait: left to itself the compiler
 // wrote each value to the ring as it arrived in some instances and waited for every load by
 // itself (BF16 27 x 19 with Guo or HCZ forcing, odd step at 256^3: 1490 us against 555).
-template <int QF, int QG, typename T, bool NL, typename C>
+template <int QF, int QG, typename T, bool NT0, bool NL, typename C>
 __device__ __forceinline__ void ring_loads(C* f, C* g, T (*xs)[256], const T* pop, const NodeIndex& ix, int64_t stride,
                                            const RowLane& l) {
   T rf[QF], rg[QG];
-  row_load<QF, T, NL>(rf, pop, 0, ix, stride, l, std::make_integer_sequence<int, QF>{});
-  row_load<QG, T, NL>(rg, pop, QF, ix, stride, l, std::make_integer_sequence<int, QG>{});
+  row_load<QF, T, NT0, NL>(rf, pop, 0, ix, stride, l, std::make_integer_sequence<int, QF>{});
+  row_load<QG, T, NT0, NL>(rg, pop, QF, ix, stride, l, std::make_integer_sequence<int, QG>{});
   __builtin_amdgcn_sched_barrier(0);
   row_stage<QF>(f, rf, xs, 0, l, std::make_integer_sequence<int, QF>{});
   row_stage<QG>(g, rg, xs, x_moving<QF>(), l, std::make_integer_sequence<int, QG>{});
 }
 
-template <int QF, int QG, int FORCE, typename T, typename C, bool PART>
+template <int QF, int QG, int FORCE, typename T, typename C, bool PART, bool CACHED>
 __global__ STGV_STEP_BOUNDS void lbm_step_ring_kernel(T* pop, Geometry geo, PhysConsts c) {
-  constexpr bool NL = !PART || STGV_RING_PART_NT_XLOAD, NS = !PART || STGV_RING_PART_NT_XSTORE;
+  constexpr bool NL = !CACHED && (!PART || STGV_RING_PART_NT_XLOAD), NS = !CACHED && (!PART || STGV_RING_PART_NT_XSTORE);
   constexpr int KF = x_moving<QF>(), KG = x_moving<QG>();
   __shared__ T xs[KF + KG][256];
   const int n = geo.n;
@@ -184,7 +185,7 @@ __global__ STGV_STEP_BOUNDS void lbm_step_ring_kernel(T* pop, Geometry geo, Phys
   const NodeIndex ix = make_index(x, y, blk.bz, n);
   const RowLane l = make_rowlane(x, n);
   C f[QF], g[QG];
-  ring_loads<QF, QG, T, NL>(f, g, xs, pop, ix, geo.stride, l);
+  ring_loads<QF, QG, T, !CACHED, NL>(f, g, xs, pop, ix, geo.stride, l);
   __syncthreads();
   row_pick<QF>(f, (const T(*)[256])xs, 0, l, std::make_integer_sequence<int, QF>{});
   row_pick<QG>(g, (const T(*)[256])xs, KF, l, std::make_integer_sequence<int, QG>{});
@@ -195,8 +196,8 @@ __global__ STGV_STEP_BOUNDS void lbm_step_ring_kernel(T* pop, Geometry geo, Phys
   row_put<QF>(f, xs, 0, l, std::make_integer_sequence<int, QF>{});
   row_put<QG>(g, xs, KF, l, std::make_integer_sequence<int, QG>{});
   __syncthreads();
-  row_store<QF, T, NS>(f, (const T(*)[256])xs, 0, pop, 0, ix, geo.stride, l, std::make_integer_sequence<int, QF>{});
-  row_store<QG, T, NS>(g, (const T(*)[256])xs, KF, pop, QF, ix, geo.stride, l, std::make_integer_sequence<int, QG>{});
+  row_store<QF, T, !CACHED, NS>(f, (const T(*)[256])xs, 0, pop, 0, ix, geo.stride, l, std::make_integer_sequence<int, QF>{});
+  row_store<QG, T, !CACHED, NS>(g, (const T(*)[256])xs, KF, pop, QF, ix, geo.stride, l, std::make_integer_sequence<int, QG>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -206,23 +207,23 @@ __global__ STGV_STEP_BOUNDS void lbm_step_ring_kernel(T* pop, Geometry geo, Phys
 // through FP32, which holds every FP16 / BF16 value exactly, so a stream is exact in
 // every storage type.  It is the ceiling of the step's own access pattern.
 // ---------------------------------------------------------------------------
-template <int QF, int QG, typename T, int MODE, bool ROWS>
+template <int QF, int QG, typename T, int MODE, bool ROWS, bool CACHED>
 __global__ __launch_bounds__(kNodeBlock) void lbm_stream_kernel(T* pop, T* dst, Geometry geo) {
   const uint32_t node = node_of<MODE>(geo);
   if (node >= geo.n3) return;
   const NodeIndex ix = index_of<MODE, ROWS>(node, geo);
   float f[QF], g[QG];
-  gather<QF, T, MODE, true>(f, pop, 0, ix, geo.stride);
-  gather<QG, T, MODE, true>(g, pop, QF, ix, geo.stride);
-  scatter<QF, T, MODE>(f, dst, 0, ix, geo.stride);
-  scatter<QG, T, MODE>(g, dst, QF, ix, geo.stride);
+  gather<QF, T, MODE, true, CACHED>(f, pop, 0, ix, geo.stride);
+  gather<QG, T, MODE, true, CACHED>(g, pop, QF, ix, geo.stride);
+  scatter<QF, T, MODE, CACHED>(f, dst, 0, ix, geo.stride);
+  scatter<QG, T, MODE, CACHED>(g, dst, QF, ix, geo.stride);
 }
 
 // The odd free-streaming step row-aligned, on the shapes where the odd step runs
 // row-aligned (ring_shape; every lane active).
-template <int QF, int QG, typename T, bool PART>
+template <int QF, int QG, typename T, bool PART, bool CACHED>
 __global__ __launch_bounds__(256) void lbm_stream_ring_kernel(T* pop, Geometry geo) {
-  constexpr bool NL = !PART || STGV_RING_PART_NT_XLOAD, NS = !PART || STGV_RING_PART_NT_XSTORE;
+  constexpr bool NL = !CACHED && (!PART || STGV_RING_PART_NT_XLOAD), NS = !CACHED && (!PART || STGV_RING_PART_NT_XSTORE);
   constexpr int KF = x_moving<QF>(), KG = x_moving<QG>();
   __shared__ T xs[KF + KG][256];
   const int n = geo.n;
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(256) void lbm_stream_ring_kernel(T* pop, Geometry g
   const NodeIndex ix = make_index(x, y, blk.bz, n);
   const RowLane l = make_rowlane(x, n);
   float f[QF], g[QG];
-  ring_loads<QF, QG, T, NL>(f, g, xs, pop, ix, geo.stride, l);
+  ring_loads<QF, QG, T, !CACHED, NL>(f, g, xs, pop, ix, geo.stride, l);
   __syncthreads();
   row_pick<QF>(f, (const T(*)[256])xs, 0, l, std::make_integer_sequence<int, QF>{});
   row_pick<QG>(g, (const T(*)[256])xs, KF, l, std::make_integer_sequence<int, QG>{});
@@ -240,8 +241,8 @@ __global__ __launch_bounds__(256) void lbm_stream_ring_kernel(T* pop, Geometry g
   row_put<QF>(f, xs, 0, l, std::make_integer_sequence<int, QF>{});
   row_put<QG>(g, xs, KF, l, std::make_integer_sequence<int, QG>{});
   __syncthreads();
-  row_store<QF, T, NS>(f, (const T(*)[256])xs, 0, pop, 0, ix, geo.stride, l, std::make_integer_sequence<int, QF>{});
-  row_store<QG, T, NS>(g, (const T(*)[256])xs, KF, pop, QF, ix, geo.stride, l, std::make_integer_sequence<int, QG>{});
+  row_store<QF, T, !CACHED, NS>(f, (const T(*)[256])xs, 0, pop, 0, ix, geo.stride, l, std::make_integer_sequence<int, QF>{});
+  row_store<QG, T, !CACHED, NS>(g, (const T(*)[256])xs, KF, pop, QF, ix, geo.stride, l, std::make_integer_sequence<int, QG>{});
 }
 
 // ---------------------------------------------------------------------------

@@ -471,18 +471,19 @@ namespace {
 hipError_t launch_node(lbm_ctx* c, int mode, int flags, char* src, char* dst, float* fields,
                        double* partials) {
   const int qf = c->p.q_f, qg = c->p.q_g, fo = c->p.forcing;
+  const bool cached = cached_state(c->sz.pop_bytes);
   switch (c->p.storage) {
     case LBM_FP32:
       if (c->p.compute == LBM_COMPUTE_FP64)
-        return launch_step<float, double>(qf, qg, fo, mode, flags, c->stream, (float*)src,
+        return launch_step<float, double>(qf, qg, fo, mode, flags, cached, c->stream, (float*)src,
                                           (float*)dst, c->geo, c->c, fields, partials);
-      return launch_step<float, float>(qf, qg, fo, mode, flags, c->stream, (float*)src,
+      return launch_step<float, float>(qf, qg, fo, mode, flags, cached, c->stream, (float*)src,
                                        (float*)dst, c->geo, c->c, fields, partials);
     case LBM_FP16:
-      return launch_step<_Float16, float>(qf, qg, fo, mode, flags, c->stream, (_Float16*)src,
+      return launch_step<_Float16, float>(qf, qg, fo, mode, flags, cached, c->stream, (_Float16*)src,
                                           (_Float16*)dst, c->geo, c->c, fields, partials);
     default:
-      return launch_step<bf16_t, float>(qf, qg, fo, mode, flags, c->stream, (bf16_t*)src,
+      return launch_step<bf16_t, float>(qf, qg, fo, mode, flags, cached, c->stream, (bf16_t*)src,
                                         (bf16_t*)dst, c->geo, c->c, fields, partials);
   }
 }
@@ -627,7 +628,7 @@ int lbm_stream(lbm_ctx* c, int64_t nsteps) {
     }
     hipError_t e = by_storage(c->p.storage, [&](auto* tag) {
       using T = std::remove_pointer_t<decltype(tag)>;
-      return launch_stream<T>(c->p.q_f, c->p.q_g, mode, c->stream, (T*)src, (T*)dst, c->geo);
+      return launch_stream<T>(c->p.q_f, c->p.q_g, mode, cached_state(c->sz.pop_bytes), c->stream, (T*)src, (T*)dst, c->geo);
     });
     if (e != hipSuccess) return hip_fail(c, e, "free-streaming kernel");
     c->step++;
