@@ -69,14 +69,27 @@ __device__ __forceinline__ f32x16 mfma16(const bf16x8& a, const bf16x8& b, const
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// FP32 -> BF16 conversions in the fused step use gfx950's packed convert (round to
-// nearest even), one instruction per pair of values.
-__device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }
+// An 8-wide B operand as four packed pairs.
+struct OperandPairs {
+  uint32_t w[4];
+  __device__ __forceinline__ bf16x8 operand() const { return __builtin_bit_cast(bf16x8, *this); }
+};
 
-// v = hi + lo with hi, lo in BF16 (|v - hi - lo| ~ 2^-16 |v|)
-__device__ __forceinline__ void split_bf16(float v, __bf16& hi, __bf16& lo) {
-  hi = to_bf16(v);
-  lo = to_bf16(v - (float)hi);
+// a, b = hi + lo with hi, lo in BF16 (|v - hi - lo| ~ 2^-16 |v|), each pair by one conversion
+__device__ __forceinline__ void split_bf16_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = to_bf16_pair(a, b);
+  lo = to_bf16_pair(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
+// the 24 values v in two operands of three k-steps
+__device__ __forceinline__ void split_operands(const float* v, bf16x8* hi, bf16x8* lo) {
+#pragma unroll
+  for (int ks = 0; ks < 3; ++ks) {
+    OperandPairs h, l;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) split_bf16_pair(v[8 * ks + 2 * p], v[8 * ks + 2 * p + 1], h.w[p], l.w[p]);
+    hi[ks] = h.operand();
+    lo[ks] = l.operand();
+  }
 }
 
 // direction data of population p (global index: f_i = i, g_j = 27 + j; -1: none)
@@ -128,11 +141,14 @@ constexpr bool is_analytic(int k) { return k < NCF || k == 27 || k == N_IN - 1; 
 // tanh of the 16 results of a tile into two 8-wide B operands (the fast form's error, ~2e-7,
 // is far below the BF16 rounding, 2^-9 relative, the activation goes through next)
 __device__ __forceinline__ void tanh_to_b(const f32x16& t, bf16x8& lo8, bf16x8& hi8) {
+  OperandPairs a, b;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    lo8[q] = to_bf16(fast_tanh(t[q]));
-    hi8[q] = to_bf16(fast_tanh(t[8 + q]));
+  for (int p = 0; p < 4; ++p) {
+    a.w[p] = to_bf16_pair(fast_tanh(t[2 * p]), fast_tanh(t[2 * p + 1]));
+    b.w[p] = to_bf16_pair(fast_tanh(t[8 + 2 * p]), fast_tanh(t[8 + 2 * p + 1]));
   }
+  lo8 = a.operand();
+  hi8 = b.operand();
 }
 
 __device__ __forceinline__ f32x16 bias_tile(const float* b, int mt, int h) {
@@ -143,7 +159,7 @@ __device__ __forceinline__ f32x16 bias_tile(const float* b, int mt, int h) {
 }
 
 template <int FORCE, int MODE, bool DIAG>
-__global__ __launch_bounds__(256) void learned_step_kernel(float* __restrict__ pop, float* __restrict__ dst,
+__global__ __launch_bounds__(256, DIAG ? 1 : 4) void learned_step_kernel(float* __restrict__ pop, float* __restrict__ dst,
                                                            Geometry geo, PhysConsts c,
                                                            float* __restrict__ fields,
                                                            double* __restrict__ partials,
@@ -254,19 +270,20 @@ __global__ __launch_bounds__(256) void learned_step_kernel(float* __restrict__ p
   auto geq_s = [&](int s) { return cl.geq_of(edot(s, cl.tx, cl.ty, cl.tz), weight(s)); };
 
   // ---- relaxation increments d = f^eq - f and their conserved moments
+  float d[NSLOT];
   float r0 = 0.f, rx = 0.f, ry = 0.f, rz = 0.f, r0g = 0.f;
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
     if (s < NSLOT_F) {
-      const Dir d = e0(s);
-      v[s] = feq_s(s) - v[s];
-      r0 += v[s];
-      rx = d.ex ? (d.ex > 0 ? rx + v[s] : rx - v[s]) : rx;
-      ry = d.ey ? (d.ey > 0 ? ry + v[s] : ry - v[s]) : ry;
-      rz = d.ez ? (d.ez > 0 ? rz + v[s] : rz - v[s]) : rz;
+      const Dir e = e0(s);
+      d[s] = feq_s(s) - v[s];
+      r0 += d[s];
+      rx = e.ex ? (e.ex > 0 ? rx + d[s] : rx - d[s]) : rx;
+      ry = e.ey ? (e.ey > 0 ? ry + d[s] : ry - d[s]) : ry;
+      rz = e.ez ? (e.ez > 0 ? rz + d[s] : rz - d[s]) : rz;
     } else {
-      v[s] = geq_s(s) - v[s];
-      r0g += v[s];
+      d[s] = geq_s(s) - v[s];
+      r0g += d[s];
     }
   }
   rx *= sg;
@@ -278,29 +295,12 @@ __global__ __launch_bounds__(256) void learned_step_kernel(float* __restrict__ p
   rz += xor32(rz);
   r0g += xor32(r0g);
 
-  // ---- features: -M d on MFMA, d in two BF16 halves
+  // ---- d in two BF16 halves for the features
   bf16x8 dhi[3], dlo[3];
-#pragma unroll
-  for (int s = 0; s < NSLOT; ++s) {
-    __bf16 hi, lo;
-    split_bf16(v[s], hi, lo);
-    dhi[s >> 3][s & 7] = hi;
-    dlo[s >> 3][s & 7] = lo;
-  }
-  f32x16 xf[2];
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
-    f32x16 acc = {0};
-#pragma unroll
-    for (int ks = 0; ks < 3; ++ks) {
-      const bf16x8 a = load8(s_feat + (32 * mt + col) * PW_IN + 16 * ks + 8 * h);
-      acc = mfma16(a, dhi[ks], acc);
-      acc = mfma16(a, dlo[ks], acc);
-    }
-    xf[mt] = acc;
-  }
+  split_operands(d, dhi, dlo);
 
-  // ---- finish the collision (the increments are no longer needed)
+  // ---- the collision, finished while the equilibria are at hand: what lives through the
+  // network is f* alone (108 VGPRs, four wavefronts per SIMD)
   {
     rz -= (FORCE == FORCE_GUO) ? 0.5f * m.Fz : cl.tau_f * m.Fz;
     r0g -= 0.5f * m.s;
@@ -319,17 +319,32 @@ __global__ __launch_bounds__(256) void learned_step_kernel(float* __restrict__ p
           if (ez0 != 0) br += (ez0 > 0 ? sg : -sg) * (icf * (1.f + icf * edot(s, m.ux, m.uy, m.uz)));
           small = fma_c(-om, pr, weight(s) * guo_c * br);
         }
-        v[s] = feq_s(s) + fma_c(om - 1.f, v[s], small);
+        v[s] = feq_s(s) + fma_c(om - 1.f, d[s], small);
       } else {
-        v[s] = geq_s(s) + fma_c(og - 1.f, v[s], weight(s) * src_g);
+        v[s] = geq_s(s) + fma_c(og - 1.f, d[s], weight(s) * src_g);
       }
     }
+  }
+
+  // ---- features: -M d on MFMA
+  f32x16 xf[2];
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt) {
+    f32x16 acc = {0};
+#pragma unroll
+    for (int ks = 0; ks < 3; ++ks) {
+      const bf16x8 a = load8(s_feat + (32 * mt + col) * PW_IN + 16 * ks + 8 * h);
+      acc = mfma16(a, dhi[ks], acc);
+      acc = mfma16(a, dlo[ks], acc);
+    }
+    xf[mt] = acc;
   }
 
   // ---- normalised features -> layer-1 operand (logical feature k at physical row perm_row(k))
   bf16x8 b1[3];
 #pragma unroll
   for (int ks = 0; ks < 3; ++ks) {
+    float x[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int mt = ks >> 1, r = 8 * (ks & 1) + q;
@@ -341,8 +356,12 @@ __global__ __launch_bounds__(256) void learned_step_kernel(float* __restrict__ p
         val = h ? v1 : v0;
       }
       const int row = d_row_of(mt, r, h);
-      b1[ks][q] = to_bf16((val - P->x_mean_p[row]) * P->x_iscale_p[row]);
+      x[q] = (val - P->x_mean_p[row]) * P->x_iscale_p[row];
     }
+    OperandPairs pairs;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) pairs.w[p] = to_bf16_pair(x[2 * p], x[2 * p + 1]);
+    b1[ks] = pairs.operand();
   }
 
   // ---- the network
@@ -381,15 +400,10 @@ __global__ __launch_bounds__(256) void learned_step_kernel(float* __restrict__ p
       for (int ks = 0; ks < 4; ++ks)
         t[mt] = mfma16(load8(s_w3p + (32 * mt + col) * PW_HID + 16 * ks + 8 * h), hb[ks], t[mt]);
     }
+    float dm[24];
 #pragma unroll
-    for (int ks = 0; ks < 3; ++ks)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        __bf16 hi, lo;
-        split_bf16(t[ks >> 1][8 * (ks & 1) + q], hi, lo);
-        mhi[ks][q] = hi;
-        mlo[ks][q] = lo;
-      }
+    for (int q = 0; q < 24; ++q) dm[q] = t[q >> 4][q & 15];
+    split_operands(dm, mhi, mlo);
   }
 
   // ---- correction M^-1 [0, dm]: result rows are this half's populations
@@ -420,7 +434,8 @@ __global__ __launch_bounds__(256) void learned_step_kernel(float* __restrict__ p
     uint32_t o0 = 0, o1 = 0;
     if (p0 >= 0) address_of<MODE, false>(p0, ixs, a0, o0);
     if (p1 >= 0) address_of<MODE, false>(p1, ixs, a1, o1);
-    if ((h ? p1 : p0) >= 0) store_as(slot_address(dst, p0, p1, a0, a1, h ? o1 : o0), v[s]);
+    // through the caches: 64^3 32.5 -> 30.1 us against stores that bypass them, 128^3 258.7 -> 256.8
+    if ((h ? p1 : p0) >= 0) store_as<false>(slot_address(dst, p0, p1, a0, a1, h ? o1 : o0), v[s]);
   }
 
   if constexpr (DIAG) {

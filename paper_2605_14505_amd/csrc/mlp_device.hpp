@@ -290,8 +290,11 @@ __device__ __forceinline__ bf16x8 load8(const uint16_t* p) {   // 16-byte aligne
 
 // Round to nearest even with gfx950's own conversion (bf16_bits without its integer steps).
 __device__ __forceinline__ uint16_t to_bf16_bits(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
+// Two of them, a in the low half: one packed conversion.
 __device__ __forceinline__ uint32_t to_bf16_pair(float a, float b) {
-  return (uint32_t)to_bf16_bits(a) | ((uint32_t)to_bf16_bits(b) << 16);
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
 }
 
 // tanh x = 1 - 2 / (1 + e^(2x)) with the hardware exp2 and reciprocal: absolute error
