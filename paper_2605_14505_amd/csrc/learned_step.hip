@@ -210,6 +210,8 @@ __global__ __launch_bounds__(256, DIAG ? 1 : 4) void learned_step_kernel(float* 
   // one memory latency for both.
   __shared__ alignas(16) uint16_t s_feat[64 * PW_IN], s_minv[64 * PW_IN], s_w1p[64 * PW_IN];
   __shared__ alignas(16) uint16_t s_w2p[64 * PW_HID], s_w3p[64 * PW_HID];
+  // biases and normalisation: b1p, b2p, b3p, x_mean_p, x_iscale_p, contiguous in Packed
+  __shared__ alignas(16) float s_rows[5][64];
   {
     Staged<64, K_IN, PW_IN> feat, minv, w1;
     Staged<64, N_HID, PW_HID> w2, w3;
@@ -218,15 +220,18 @@ __global__ __launch_bounds__(256, DIAG ? 1 : 4) void learned_step_kernel(float* 
     w1.load(P->w1p);
     w2.load(P->w2p);
     w3.load(P->w3p);
+    const int rv = min((int)threadIdx.x, 5 * 16 - 1);
+    const u32x4 rows = reinterpret_cast<const u32x4*>(P->b1p)[rv];
     // every staged value is an input here, so the wave waits once, for all of the loads,
     // and no LDS write is scheduled above a load still to be issued
     asm volatile("" ::"v"(feat.t0), "v"(feat.t1), "v"(minv.t0), "v"(minv.t1), "v"(w1.t0), "v"(w1.t1),
-                 "v"(w2.t0), "v"(w2.t1), "v"(w3.t0), "v"(w3.t1));
+                 "v"(w2.t0), "v"(w2.t1), "v"(w3.t0), "v"(w3.t1), "v"(rows));
     feat.put(s_feat);
     minv.put(s_minv);
     w1.put(s_w1p);
     w2.put(s_w2p);
     w3.put(s_w3p);
+    if (threadIdx.x < 5 * 16) reinterpret_cast<u32x4*>(s_rows)[rv] = rows;
   }
   __syncthreads();
   // Direction of slot s in this half: sg * e0(s), e0 the half-0 direction; the
@@ -356,7 +361,7 @@ __global__ __launch_bounds__(256, DIAG ? 1 : 4) void learned_step_kernel(float* 
         val = h ? v1 : v0;
       }
       const int row = d_row_of(mt, r, h);
-      x[q] = (val - P->x_mean_p[row]) * P->x_iscale_p[row];
+      x[q] = (val - s_rows[3][row]) * s_rows[4][row];
     }
     OperandPairs pairs;
 #pragma unroll
@@ -370,7 +375,7 @@ __global__ __launch_bounds__(256, DIAG ? 1 : 4) void learned_step_kernel(float* 
     f32x16 t[2];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
-      t[mt] = bias_tile(P->b1p, mt, h);
+      t[mt] = bias_tile(s_rows[0], mt, h);
 #pragma unroll
       for (int ks = 0; ks < 3; ++ks)
         t[mt] = mfma16(load8(s_w1p + (32 * mt + col) * PW_IN + 16 * ks + 8 * h), b1[ks], t[mt]);
@@ -382,7 +387,7 @@ __global__ __launch_bounds__(256, DIAG ? 1 : 4) void learned_step_kernel(float* 
     f32x16 t[2];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
-      t[mt] = bias_tile(P->b2p, mt, h);
+      t[mt] = bias_tile(s_rows[1], mt, h);
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
         t[mt] = mfma16(load8(s_w2p + (32 * mt + col) * PW_HID + 16 * ks + 8 * h), hb[ks], t[mt]);
@@ -395,7 +400,7 @@ __global__ __launch_bounds__(256, DIAG ? 1 : 4) void learned_step_kernel(float* 
     f32x16 t[2];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
-      t[mt] = bias_tile(P->b3p, mt, h);
+      t[mt] = bias_tile(s_rows[2], mt, h);
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
         t[mt] = mfma16(load8(s_w3p + (32 * mt + col) * PW_HID + 16 * ks + 8 * h), hb[ks], t[mt]);

@@ -11,6 +11,7 @@
 // normalised as (x - mean) * iscale, outputs scaled by y_scale.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "lbm_device.hpp"
@@ -260,8 +261,10 @@ struct Packed {
   alignas(16) uint16_t w2p[64 * N_HID];
   alignas(16) uint16_t w3p[64 * N_HID];
   alignas(16) StepTables tab;
+  // one block of 5 x 64 values, read as such by the fused step
   alignas(16) float b1p[64], b2p[64], b3p[64], x_mean_p[64], x_iscale_p[64];
 };
+static_assert(offsetof(Packed, x_iscale_p) == offsetof(Packed, b1p) + 4 * 64 * sizeof(float), "contiguous rows");
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
