@@ -25,7 +25,11 @@
 
 namespace stgv {
 
-constexpr int kNodeBlock = 256;   // threads (and nodes) of a node kernel's block
+// Threads (and nodes) of a node kernel's block: 256, and single wavefronts where the box has
+// no more than two of them per CU, so that every CU has some (mean step: 32^3 6.59 -> 5.36 us,
+// 16^3 4.94 -> 4.54; 128 threads 6.01 and 4.60; at 40^3 single wavefronts lose, 9.34 -> 10.1).
+constexpr int kNodeBlock = 256;
+constexpr int node_threads(int n) { return (int64_t)n * n * n <= 2 * 256 * 64 ? 64 : kNodeBlock; }
 
 enum Mode : int { MODE_EVEN = 0, MODE_ODD = 1, MODE_AB = 2 };
 // Guo source term, Shan-Chen velocity shift (Eq. (10)), exact difference method
@@ -86,8 +90,8 @@ inline Geometry make_geometry(int n, int64_t stride) {
   while ((1 << s) < n) ++s;
   g.div_mul = (uint32_t)((1ull << (31 + s)) / (unsigned)n + 1);
   g.div_shift = s - 1;
-  // blocks of kNodeBlock nodes that make up whole rows (at most 8 of them)
-  int rows = n, blk = kNodeBlock;
+  // blocks that make up whole rows (at most 8 of them)
+  int rows = n, blk = node_threads(n);
   while (blk > 1 && rows % 2 == 0) { rows /= 2; blk /= 2; }
   g.xcd_group = rows < 8 ? rows : 8;
   return g;

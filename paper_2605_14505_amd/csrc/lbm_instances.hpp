@@ -16,7 +16,7 @@ template <int QF, int QG, int FORCE, typename T, int MODE, int FLAGS, bool ROWS,
 hipError_t go_step(hipStream_t st, T* pop, T* dst, Geometry geo, PhysConsts c, float* fields, double* partials) {
   const size_t lds = (MODE == MODE_EVEN && FLAGS == K_COLLIDE) ? even_step_lds(sizeof(T), geo.n) : 0;
   hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS, ROWS, CACHED>), dim3(node_blocks(geo.n)),
-                     dim3(kNodeBlock), lds, st, pop, dst, geo, c, fields, partials);
+                     dim3(node_threads(geo.n)), lds, st, pop, dst, geo, c, fields, partials);
   return hipGetLastError();
 }
 
@@ -108,7 +108,7 @@ hipError_t launch_init<STGV_T>(int qf, int qg, hipStream_t st, STGV_T* pop,
                                Geometry geo, double u0, double noise_amp, uint64_t seed) {
 #define STGV_INIT(A, B) \
   if (qf == A && qg == B) { \
-    hipLaunchKernelGGL((lbm_init_tgv_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, u0, noise_amp, seed); \
+    hipLaunchKernelGGL((lbm_init_tgv_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(node_threads(geo.n)), 0, st, pop, geo, u0, noise_amp, seed); \
     return hipGetLastError(); }
   STGV_FOR_EACH_PAIR(STGV_INIT)
 #undef STGV_INIT
@@ -117,7 +117,7 @@ hipError_t launch_init<STGV_T>(int qf, int qg, hipStream_t st, STGV_T* pop,
 
 template <int A, int B, bool CACHED>
 static hipError_t stream_pair(int mode, hipStream_t st, STGV_T* pop, STGV_T* dst, Geometry geo) {
-  const dim3 grid(node_blocks(geo.n)), block(kNodeBlock);
+  const dim3 grid(node_blocks(geo.n)), block(node_threads(geo.n));
   if constexpr (ring_pair<A, B>(sizeof(STGV_T))) {
     const bool whole = ring_whole(geo.n, sizeof(STGV_T));
     if (mode == MODE_ODD && (whole || ring_part(geo.n))) {
@@ -170,7 +170,7 @@ hipError_t launch_canon<STGV_T>(int qf, int qg, int mode, hipStream_t st, const 
   if (mode != MODE_ODD) return convert<false>(qf + qg, st, const_cast<STGV_T*>(pop), geo, out);
 #define STGV_CANON(A, B) \
   if (qf == A && qg == B) { \
-    hipLaunchKernelGGL((lbm_canon_odd_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(kNodeBlock), 0, st, pop, geo, out); \
+    hipLaunchKernelGGL((lbm_canon_odd_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(node_threads(geo.n)), 0, st, pop, geo, out); \
     return hipGetLastError(); }
   STGV_FOR_EACH_PAIR(STGV_CANON)
 #undef STGV_CANON

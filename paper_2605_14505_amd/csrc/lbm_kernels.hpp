@@ -29,8 +29,8 @@ constexpr int step_min_blocks() {
 #define STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) __launch_bounds__(256, (step_min_blocks<MODE, FLAGS, T, C>()))
 #define STGV_STEP_BOUNDS STGV_STEP_BOUNDS_FOR(MODE_ODD, K_COLLIDE, T, C)
 
-// Nodes of the plain node kernels: block b holds the kNodeBlock consecutive nodes from
-// kNodeBlock b of the linear order x + n (y + n z), whatever the box, so that no lane is idle
+// Nodes of the plain node kernels: block b holds the node_threads(n) consecutive nodes from
+// node_threads(n) b of the linear order x + n (y + n z), whatever the box, so that no lane is idle
 // and every wavefront's access is one contiguous run.  Against x-y block shapes (128 x 2 for
 // 90^3 and 100^3, 32 x 8 for 96^3 and 160^3), mean step in us: 90^3 FP16 27 x 7 35.6 -> 23.8,
 // FP32 27 x 19 72.2 -> 50.1; 100^3 FP32 91.7 -> 67.5; 160^3 FP16 215 -> 145; 96^3 FP32
@@ -57,7 +57,7 @@ __device__ __forceinline__ uint32_t node_block(const Geometry& geo) {
 }
 template <int MODE>
 __device__ __forceinline__ uint32_t node_of(const Geometry& geo) {
-  return node_block<MODE>(geo) * kNodeBlock + threadIdx.x;
+  return node_block<MODE>(geo) * blockDim.x + threadIdx.x;
 }
 
 // Neighbour offsets of node i.  ROWS: n is a multiple of 64, so a wavefront's nodes lie in one

@@ -16,9 +16,9 @@ struct LaunchShape {
 // to each.
 #define STGV_FOR_EACH_PAIR(X) X(27, 19) X(27, 7) X(19, 7) X(27, 27) X(19, 19) X(19, 15) X(15, 7) X(7, 27)
 
-// Blocks of the plain node kernels (kNodeBlock consecutive nodes each).
+// Blocks of the plain node kernels (node_threads(n) consecutive nodes each).
 inline unsigned node_blocks(int n) {
-  return (unsigned)(((int64_t)n * n * n + kNodeBlock - 1) / kNodeBlock);
+  return (unsigned)(((int64_t)n * n * n + node_threads(n) - 1) / node_threads(n));
 }
 
 // Whether a step's loads and stores go through the caches instead of bypassing them: for a
