@@ -32,6 +32,9 @@ constexpr int kNodeBlock = 256;
 constexpr int node_threads(int n) { return (int64_t)n * n * n <= 2 * 256 * 64 ? 64 : kNodeBlock; }
 
 enum Mode : int { MODE_EVEN = 0, MODE_ODD = 1, MODE_AB = 2 };
+// Rows of the box as a node kernel sees them: of any length, of whole 128-byte lines, of whole
+// wavefronts (n a multiple of 64).
+enum RowKind : int { ROWS_ANY = 0, ROWS_LINES = 1, ROWS_WAVES = 2 };
 // Guo source term, Shan-Chen velocity shift (Eq. (10)), exact difference method
 // (Kupershtokh), He-Shan-Doolen source term: the four schemes of the forcing comparison.
 enum Forcing : int { FORCE_GUO = 0, FORCE_SHIFT = 1, FORCE_EDM = 2, FORCE_HCZ = 3 };
@@ -104,12 +107,12 @@ struct bf16_t { uint16_t bits; };
 
 // Population loads that bypass the caches, per layout mode (bit MODE of the mask), and in
 // the odd step for the directions with e_x = 0 (whose lines no neighbouring wavefront
-// shares) where the kernel asks for it.  Every value is read once per step; measured on
-// gfx950 (256^3 D3Q27 x D3Q19, FP32 / FP16 storage), non-temporal loads of the even step
-// and of the odd step's x-aligned directions take 7-8 % off both steps, while
-// non-temporal loads of the x-shifted directions, whose lines two wavefronts share, make
-// the odd step 20-30 % slower.  (The row-aligned odd step, lbm_step_ring_kernel, sets
-// its own cache policy.)
+// shares where rows are whole lines, RowKind) where the kernel asks for it.  Every value is
+// read once per step; measured on gfx950 (256^3 D3Q27 x D3Q19, FP32 / FP16 storage),
+// non-temporal loads of the even step and of the odd step's x-aligned directions take 7-8 % off
+// both steps, while non-temporal loads of the x-shifted directions, whose lines two wavefronts
+// share, make the odd step 20-30 % slower.  (The row-aligned odd step, lbm_step_ring_kernel,
+// sets its own cache policy.)
 #ifndef STGV_NT_LOAD_MODES
 #define STGV_NT_LOAD_MODES 1
 #endif

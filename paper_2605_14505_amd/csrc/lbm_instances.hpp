@@ -12,7 +12,7 @@ namespace stgv {
 // helpers, whose template arguments do not name the compute type.
 namespace {
 
-template <int QF, int QG, int FORCE, typename T, int MODE, int FLAGS, bool ROWS, bool CACHED>
+template <int QF, int QG, int FORCE, typename T, int MODE, int FLAGS, int ROWS, bool CACHED>
 hipError_t go_step(hipStream_t st, T* pop, T* dst, Geometry geo, PhysConsts c, float* fields, double* partials) {
   const size_t lds = (MODE == MODE_EVEN && FLAGS == K_COLLIDE) ? even_step_lds(sizeof(T), geo.n) : 0;
   hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS, ROWS, CACHED>), dim3(node_blocks(geo.n)),
@@ -26,10 +26,10 @@ hipError_t step_mode(int mode, bool diag, hipStream_t st, T* pop, T* dst, Geomet
   constexpr int STEP = K_COLLIDE;
   constexpr int STEP_DIAG = K_COLLIDE | K_FIELDS | K_PARTIALS;
 #define STGV_GO(M, FL, ROWS) return go_step<QF, QG, FORCE, T, M, FL, ROWS, CACHED>(st, pop, dst, geo, c, fields, partials)
-  if (mode == MODE_EVEN) { if (diag) STGV_GO(MODE_EVEN, STEP_DIAG, false); STGV_GO(MODE_EVEN, STEP, false); }
-  if (mode == MODE_AB) { if (diag) STGV_GO(MODE_AB, STEP_DIAG, false); STGV_GO(MODE_AB, STEP, false); }
+  if (mode == MODE_EVEN) { if (diag) STGV_GO(MODE_EVEN, STEP_DIAG, ROWS_ANY); STGV_GO(MODE_EVEN, STEP, ROWS_ANY); }
+  if (mode == MODE_AB) { if (diag) STGV_GO(MODE_AB, STEP_DIAG, ROWS_ANY); STGV_GO(MODE_AB, STEP, ROWS_ANY); }
   if (mode != MODE_ODD) return hipErrorInvalidValue;
-  if (diag) STGV_GO(MODE_ODD, STEP_DIAG, false);
+  if (diag) STGV_GO(MODE_ODD, STEP_DIAG, ROWS_LINES);
   if constexpr (sizeof(STGV_C) == 4 && ring_pair<QF, QG>(sizeof(T))) {
     const bool whole = ring_whole(geo.n, sizeof(T));
     if (whole || ring_part(geo.n)) {
@@ -44,8 +44,12 @@ hipError_t step_mode(int mode, bool diag, hipStream_t st, T* pop, T* dst, Geomet
       return hipGetLastError();
     }
   }
-  if (geo.n % 64 == 0) STGV_GO(MODE_ODD, STEP, true);
-  STGV_GO(MODE_ODD, STEP, false);
+  const int rows = row_kind(geo.n, sizeof(T));
+  if (rows == ROWS_WAVES) STGV_GO(MODE_ODD, STEP, ROWS_WAVES);
+  if constexpr (!CACHED && sizeof(T) == 4) {      // 2-byte rows of whole lines are whole wavefronts
+    if (rows == ROWS_LINES) STGV_GO(MODE_ODD, STEP, ROWS_LINES);
+  }
+  STGV_GO(MODE_ODD, STEP, ROWS_ANY);
 #undef STGV_GO
 }
 
@@ -75,7 +79,7 @@ hipError_t step_pair(int force, int mode, int flags, bool cached, hipStream_t st
   }
   // Moment-only passes read the natural layout (MODE_EVEN, also the AB lattice)
   // or the odd AA layout; the physical velocity does not depend on the forcing.
-#define STGV_GO(M, FL) return go_step<QF, QG, FORCE_GUO, T, M, FL, false, false>(st, pop, dst, geo, c, fields, partials)
+#define STGV_GO(M, FL) return go_step<QF, QG, FORCE_GUO, T, M, FL, ROWS_LINES, false>(st, pop, dst, geo, c, fields, partials)
   const int gm = (mode == MODE_ODD) ? MODE_ODD : MODE_EVEN;
   if (flags == SAMPLE) {
     if (gm == MODE_EVEN) STGV_GO(MODE_EVEN, SAMPLE);
@@ -129,14 +133,16 @@ static hipError_t stream_pair(int mode, hipStream_t st, STGV_T* pop, STGV_T* dst
     }
   }
   if (mode == MODE_EVEN)
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN, false, CACHED>), grid, block,
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN, ROWS_ANY, CACHED>), grid, block,
                        even_step_lds(sizeof(STGV_T), geo.n), st, pop, dst, geo);
   else if (mode == MODE_AB)
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, false, CACHED>), grid, block, 0, st, pop, dst, geo);
-  else if (geo.n % 64 == 0)
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, true, CACHED>), grid, block, 0, st, pop, dst, geo);
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, ROWS_ANY, CACHED>), grid, block, 0, st, pop, dst, geo);
+  else if (row_kind(geo.n, sizeof(STGV_T)) == ROWS_WAVES)
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_WAVES, CACHED>), grid, block, 0, st, pop, dst, geo);
+  else if (!CACHED && row_kind(geo.n, sizeof(STGV_T)) == ROWS_LINES)
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_LINES, false>), grid, block, 0, st, pop, dst, geo);
   else
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, false, CACHED>), grid, block, 0, st, pop, dst, geo);
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_ANY, CACHED>), grid, block, 0, st, pop, dst, geo);
   return hipGetLastError();
 }
 

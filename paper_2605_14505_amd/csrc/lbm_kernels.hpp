@@ -60,16 +60,16 @@ __device__ __forceinline__ uint32_t node_of(const Geometry& geo) {
   return node_block<MODE>(geo) * blockDim.x + threadIdx.x;
 }
 
-// Neighbour offsets of node i.  ROWS: n is a multiple of 64, so a wavefront's nodes lie in one
-// row and its y and z are scalar.  Even steps address their own node only.
-template <int MODE, bool ROWS>
+// Neighbour offsets of node i.  ROWS_WAVES: n is a multiple of 64, so a wavefront's nodes lie in
+// one row and its y and z are scalar.  Even steps address their own node only.
+template <int MODE, int ROWS>
 __device__ __forceinline__ NodeIndex index_of(uint32_t i, const Geometry& geo) {
   NodeIndex ix{};
   ix.base = i;
   if constexpr (MODE != MODE_EVEN) {
     uint32_t r = __umulhi(i, geo.div_mul) >> geo.div_shift;
     const uint32_t x = i - r * (uint32_t)geo.n;
-    if constexpr (ROWS) r = (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
+    if constexpr (ROWS == ROWS_WAVES) r = (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
     const uint32_t z = __umulhi(r, geo.div_mul) >> geo.div_shift;
     ix = make_index((int)x, (int)(r - z * (uint32_t)geo.n), (int)z, geo.n);
   }
@@ -104,7 +104,7 @@ template <int MODE, int FLAGS, typename T, int QF>
 constexpr bool kBatchBf16 = MODE == MODE_EVEN && FLAGS == K_COLLIDE && std::is_same<T, bf16_t>::value && QF == 27;
 #define STGV_OPERANDS_27(a) "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15]), "+v"(a[16]), "+v"(a[17]), "+v"(a[18]), "+v"(a[19]), "+v"(a[20]), "+v"(a[21]), "+v"(a[22]), "+v"(a[23]), "+v"(a[24]), "+v"(a[25]), "+v"(a[26])
 
-template <int QF, int QG, int FORCE, typename T, typename C, int MODE, int FLAGS, bool ROWS, bool CACHED>
+template <int QF, int QG, int FORCE, typename T, typename C, int MODE, int FLAGS, int ROWS, bool CACHED>
 __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, T* dst, Geometry geo,
                                                        PhysConsts c, float* __restrict__ fields,
                                                        double* __restrict__ partials) {
@@ -120,9 +120,9 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
   if (active) {
     const NodeIndex ix = index_of<MODE, ROWS>(node, geo);
     C f[QF], g[QG];
-    gather<QF, T, MODE, true, CACHED>(f, pop, 0, ix, geo.stride);
+    gather<QF, T, MODE, ROWS != ROWS_ANY, CACHED>(f, pop, 0, ix, geo.stride);
     if constexpr (kBatchBf16<MODE, FLAGS, T, QF>) asm volatile("" : STGV_OPERANDS_27(f) :: "memory");
-    gather<QG, T, MODE, true, CACHED>(g, pop, QF, ix, geo.stride);
+    gather<QG, T, MODE, ROWS != ROWS_ANY, CACHED>(g, pop, QF, ix, geo.stride);
     StepMacro<C> m;
     step_macro<QF, QG, FORCE, sizeof(T) == 4>(f, g, c, m);
     if (FLAGS & (K_FIELDS | K_PARTIALS)) {
@@ -207,14 +207,14 @@ __global__ STGV_STEP_BOUNDS void lbm_step_ring_kernel(T* pop, Geometry geo, Phys
 // through FP32, which holds every FP16 / BF16 value exactly, so a stream is exact in
 // every storage type.  It is the ceiling of the step's own access pattern.
 // ---------------------------------------------------------------------------
-template <int QF, int QG, typename T, int MODE, bool ROWS, bool CACHED>
+template <int QF, int QG, typename T, int MODE, int ROWS, bool CACHED>
 __global__ __launch_bounds__(kNodeBlock) void lbm_stream_kernel(T* pop, T* dst, Geometry geo) {
   const uint32_t node = node_of<MODE>(geo);
   if (node >= geo.n3) return;
   const NodeIndex ix = index_of<MODE, ROWS>(node, geo);
   float f[QF], g[QG];
-  gather<QF, T, MODE, true, CACHED>(f, pop, 0, ix, geo.stride);
-  gather<QG, T, MODE, true, CACHED>(g, pop, QF, ix, geo.stride);
+  gather<QF, T, MODE, ROWS != ROWS_ANY, CACHED>(f, pop, 0, ix, geo.stride);
+  gather<QG, T, MODE, ROWS != ROWS_ANY, CACHED>(g, pop, QF, ix, geo.stride);
   scatter<QF, T, MODE, CACHED>(f, dst, 0, ix, geo.stride);
   scatter<QG, T, MODE, CACHED>(g, dst, QF, ix, geo.stride);
 }
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(kNodeBlock) void lbm_canon_odd_kernel(const T* pop,
                                                                    float* __restrict__ out) {
   const uint32_t node = node_of<MODE_EVEN>(geo);
   if (node >= geo.n3) return;
-  const NodeIndex ix = index_of<MODE_ODD, false>(node, geo);
+  const NodeIndex ix = index_of<MODE_ODD, ROWS_ANY>(node, geo);
   const int64_t n3 = geo.n3;
   float f[QF], g[QG];
   gather<QF, T, MODE_ODD>(f, pop, 0, ix, geo.stride);

@@ -33,6 +33,15 @@ inline unsigned node_blocks(int n) {
 #endif
 inline bool cached_state(size_t bytes) { return bytes <= STGV_CACHED_BYTES; }
 
+// Rows of the box for the shifted odd step.  Where rows are no whole 128-byte lines, the lines of
+// the x-aligned directions are shared by wavefronts too and their loads stay cached.  Mean step
+// in us, bypassing / cached: FP32 130^3 148 / 145, 200^3 596 / 587, 250^3 1220 / 1169, 300^3 2094 /
+// 2004; FP16 150^3 129 / 117, 160^3 144 / 139, 250^3 599 / 556; with whole lines, FP32 160^3 270 /
+// 285, 320^3 2250 / 2338, FP16 320^3 1158 / 1171.
+inline int row_kind(int n, size_t elem) {
+  return n % 64 == 0 ? ROWS_WAVES : ((size_t)n * elem % 128 == 0 ? ROWS_LINES : ROWS_ANY);
+}
+
 // Whether the plain odd step runs row-aligned through an LDS ring (lbm_step_ring_kernel):
 // on blocks of whole rows that tile the box or on 256-node blocks holding part of one
 // row (n a multiple of 256, from 512); whole rows from n = 128 for 2-byte storage, from

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(kNodeBlock) void lbm_fd_kernel(const float* __restr
   } else {
     const uint32_t hi = (uint32_t)(n3 * (b + 1) / nb);
     for (uint32_t i = (uint32_t)(n3 * b / nb) + threadIdx.x; i < hi; i += kNodeBlock) {
-      const NodeIndex ix = index_of<MODE_ODD, false>(i, geo);
+      const NodeIndex ix = index_of<MODE_ODD, ROWS_ANY>(i, geo);
       const uint32_t xm = ix.at(-1, 0, 0), xp = ix.at(1, 0, 0), ym = ix.at(0, -1, 0), yp = ix.at(0, 1, 0),
                      zm = ix.at(0, 0, -1), zp = ix.at(0, 0, 1);
       const float duz_dx = 0.5f * (uz[xp] - uz[xm]), duz_dy = 0.5f * (uz[yp] - uz[ym]);
