@@ -27,7 +27,9 @@ hipError_t step_mode(int mode, bool diag, hipStream_t st, T* pop, T* dst, Geomet
   constexpr int STEP_DIAG = K_COLLIDE | K_FIELDS | K_PARTIALS;
 #define STGV_GO(M, FL, ROWS) return go_step<QF, QG, FORCE, T, M, FL, ROWS, CACHED>(st, pop, dst, geo, c, fields, partials)
   if (mode == MODE_EVEN) { if (diag) STGV_GO(MODE_EVEN, STEP_DIAG, ROWS_ANY); STGV_GO(MODE_EVEN, STEP, ROWS_ANY); }
-  if (mode == MODE_AB) { if (diag) STGV_GO(MODE_AB, STEP_DIAG, ROWS_ANY); STGV_GO(MODE_AB, STEP, ROWS_ANY); }
+  if (mode == MODE_AB)      // through the caches whatever the box: every shifted store shares its lines
+    return diag ? go_step<QF, QG, FORCE, T, MODE_AB, STEP_DIAG, ROWS_ANY, true>(st, pop, dst, geo, c, fields, partials)
+                : go_step<QF, QG, FORCE, T, MODE_AB, STEP, ROWS_ANY, true>(st, pop, dst, geo, c, fields, partials);
   if (mode != MODE_ODD) return hipErrorInvalidValue;
   if (diag) STGV_GO(MODE_ODD, STEP_DIAG, ROWS_LINES);
   if constexpr (sizeof(STGV_C) == 4 && ring_pair<QF, QG>(sizeof(T))) {
@@ -49,8 +51,8 @@ hipError_t step_mode(int mode, bool diag, hipStream_t st, T* pop, T* dst, Geomet
   if constexpr (!CACHED && sizeof(T) == 4) {      // 2-byte rows of whole lines are whole wavefronts
     if (rows == ROWS_LINES) STGV_GO(MODE_ODD, STEP, ROWS_LINES);
   }
-  STGV_GO(MODE_ODD, STEP, ROWS_ANY);
 #undef STGV_GO
+  return go_step<QF, QG, FORCE, T, MODE_ODD, STEP, ROWS_ANY, true>(st, pop, dst, geo, c, fields, partials);
 }
 
 template <int QF, int QG, int FORCE, typename T>
@@ -136,13 +138,13 @@ static hipError_t stream_pair(int mode, hipStream_t st, STGV_T* pop, STGV_T* dst
     hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN, ROWS_ANY, CACHED>), grid, block,
                        even_step_lds(sizeof(STGV_T), geo.n), st, pop, dst, geo);
   else if (mode == MODE_AB)
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, ROWS_ANY, CACHED>), grid, block, 0, st, pop, dst, geo);
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, ROWS_ANY, true>), grid, block, 0, st, pop, dst, geo);
   else if (row_kind(geo.n, sizeof(STGV_T)) == ROWS_WAVES)
     hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_WAVES, CACHED>), grid, block, 0, st, pop, dst, geo);
   else if (!CACHED && row_kind(geo.n, sizeof(STGV_T)) == ROWS_LINES)
     hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_LINES, false>), grid, block, 0, st, pop, dst, geo);
   else
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_ANY, CACHED>), grid, block, 0, st, pop, dst, geo);
+    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_ANY, true>), grid, block, 0, st, pop, dst, geo);
   return hipGetLastError();
 }
 

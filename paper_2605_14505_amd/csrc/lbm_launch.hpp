@@ -27,16 +27,18 @@ inline unsigned node_blocks(int n) {
 // 72^3 27.0 / 22.9, 90^3 49.7 / 42.8, 104^3 (207 MB) 75.0 / 63.9, 112^3 (258 MB) 96.8 / 78.6,
 // 120^3 (318 MB) 115.5 / 117.8, 128^3 124 / 149; FP16 64^3 10.7 / 9.2, 96^3 (BF16) 34.3 / 28.3,
 // 128^3 (193 MB) 69.7 / 60.2, 140^3 (252 MB) 100.8 / 79.6, 144^3 (275 MB) 106.6 / 115.8,
-// 160^3 141 / 149.
+// 160^3 141 / 149.  The A-B push always does, FP32 128^3 181 / 154, 200^3 944 / 652, 256^3 1526 / 1220,
+// FP16 256^3 730 / 606.
 #ifndef STGV_CACHED_BYTES
 #define STGV_CACHED_BYTES ((size_t)256 << 20)
 #endif
 inline bool cached_state(size_t bytes) { return bytes <= STGV_CACHED_BYTES; }
 
 // Rows of the box for the shifted odd step.  Where rows are no whole 128-byte lines, the lines of
-// the x-aligned directions are shared by wavefronts too and their loads stay cached.  Mean step
-// in us, bypassing / cached: FP32 130^3 148 / 145, 200^3 596 / 587, 250^3 1220 / 1169, 300^3 2094 /
-// 2004; FP16 150^3 129 / 117, 160^3 144 / 139, 250^3 599 / 556; with whole lines, FP32 160^3 270 /
+// the x-aligned directions are shared by wavefronts too, and everything goes through the caches.
+// Mean step in us, bypassing / x-aligned loads cached / stores cached as well: FP32 130^3 148 /
+// 145 / 139, 200^3 596 / 575 / 561, 250^3 1220 / 1174 / 1130, 300^3 2094 / 2002 / 1952; FP16
+// 150^3 129 / 115 / 115, 250^3 599 / 549 / 543; with whole lines, the first two, FP32 160^3 270 /
 // 285, 320^3 2250 / 2338, FP16 320^3 1158 / 1171.
 inline int row_kind(int n, size_t elem) {
   return n % 64 == 0 ? ROWS_WAVES : ((size_t)n * elem % 128 == 0 ? ROWS_LINES : ROWS_ANY);
