@@ -14,7 +14,7 @@ namespace {
 
 template <int QF, int QG, int FORCE, typename T, int MODE, int FLAGS, int ROWS, bool CACHED>
 hipError_t go_step(hipStream_t st, T* pop, T* dst, Geometry geo, PhysConsts c, float* fields, double* partials) {
-  const size_t lds = (MODE == MODE_EVEN && FLAGS == K_COLLIDE) ? even_step_lds(sizeof(T), geo.n) : 0;
+  const size_t lds = MODE == MODE_EVEN ? even_step_lds(sizeof(T), geo.n, FLAGS) : 0;
   hipLaunchKernelGGL((lbm_step_kernel<QF, QG, FORCE, T, STGV_C, MODE, FLAGS, ROWS, CACHED>), dim3(node_blocks(geo.n)),
                      dim3(node_threads(geo.n)), lds, st, pop, dst, geo, c, fields, partials);
   return hipGetLastError();
@@ -136,7 +136,7 @@ static hipError_t stream_pair(int mode, hipStream_t st, STGV_T* pop, STGV_T* dst
   }
   if (mode == MODE_EVEN)
     hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN, ROWS_ANY, CACHED>), grid, block,
-                       even_step_lds(sizeof(STGV_T), geo.n), st, pop, dst, geo);
+                       even_step_lds(sizeof(STGV_T), geo.n, K_COLLIDE), st, pop, dst, geo);
   else if (mode == MODE_AB)
     hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, ROWS_ANY, true>), grid, block, 0, st, pop, dst, geo);
   else if (row_kind(geo.n, sizeof(STGV_T)) == ROWS_WAVES)

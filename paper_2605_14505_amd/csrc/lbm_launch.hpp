@@ -87,8 +87,16 @@ inline LaunchShape ring_launch(int n) {
 #ifndef STGV_EVEN_CAP_2B
 #define STGV_EVEN_CAP_2B 3
 #endif
-inline size_t even_step_lds(size_t elem, int n) {
-  const int cap = elem == 4 ? (n >= 256 ? STGV_EVEN_CAP_FP32 : 0) : (n >= 512 ? STGV_EVEN_CAP_2B : 0);
+// The passes that read the state in natural order without or beside the collision have caps of
+// their own: diagnostic step FP32 2 (256^3 1314 -> 1269 us, 384^3 -7 %; 2-byte loses with any);
+// fields FP32 2 (256^3 675 -> 645, 512^3 5250 -> 4919), 2-byte 3 (256^3 FP16 367 -> 352); fields and
+// partials FP32 3 (256^3 record 722 -> 709, 512^3 5910 -> 5670), 2-byte 4 (436 -> 428).
+inline size_t even_step_lds(size_t elem, int n, int flags) {
+  int cap = 0;
+  if (flags == K_COLLIDE) cap = elem == 4 ? (n >= 256 ? STGV_EVEN_CAP_FP32 : 0) : (n >= 512 ? STGV_EVEN_CAP_2B : 0);
+  else if (n >= 256 && flags == (K_COLLIDE | K_FIELDS | K_PARTIALS)) cap = elem == 4 ? 2 : 0;
+  else if (n >= 256 && flags == K_FIELDS) cap = elem == 4 ? 2 : 3;
+  else if (n >= 256 && flags == (K_FIELDS | K_PARTIALS)) cap = elem == 4 ? 3 : 4;
   if (cap <= 0) return 0;
   // just over a (cap + 1)-th of the CU's LDS, so that cap blocks fit and cap + 1 do not
   size_t b = (160u * 1024u) / (size_t)(cap + 1) + 1024u;
