@@ -16,70 +16,72 @@ __constant__ StepTables kStepTables = make_step_tables();
 
 // ---------------------------------------------------------------------------
 // packing: FP32 master parameters (W1 [64][47], b1, W2 [64][64], b2, W3 [41][64],
-// b3) and the normalisation (x_mean[47], x_iscale[47], y_scale[41]) -> Packed.  One element
-// of each table per thread: the time is a few dependent load latencies (27 -> 5 us against one
-// 256-thread block walking the tables).
+// b3) and the normalisation (x_mean[47], x_iscale[47], y_scale[41]) -> Packed.
+// The time is a few dependent load latencies: 27 us when one 256-thread block walked the
+// tables, 5 with one element of every table per thread, 2.9 as below.
 // ---------------------------------------------------------------------------
-constexpr int kPackBlocks = N_HID * N_HID / 256;      // the largest table
+// The tables are divided over the grid's rows (blockIdx.y), so that no thread waits for more
+// than two or three loads in turn.
+constexpr int kPackBlocks = N_HID * N_HID / 256;      // the largest table, one element per thread
+constexpr int kPackRows = 4;
 
 __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ theta,
                                                    const float* __restrict__ norm,
                                                    Packed* __restrict__ P) {
-  const int tid = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
   const float* W1 = theta;
   const float* b1 = W1 + N_HID * N_IN;
   const float* W2 = b1 + N_HID;
   const float* b2 = W2 + N_HID * N_HID;
   const float* W3 = b2 + N_HID;
   const float* b3 = W3 + N_OUT * N_HID;
-  for (int t = tid; t < N_HID * K_IN; t += step) {
-    const int r = t / K_IN, c = t % K_IN;
-    P->w1[t] = c < N_IN ? bf16_bits(W1[r * N_IN + c]) : 0;
-  }
-  for (int t = tid; t < N_HID * N_HID; t += step) {
-    const int r = t / N_HID, c = t % N_HID;
-    P->w2[t] = bf16_bits(W2[t]);
-    P->w2t[t] = bf16_bits(W2[c * N_HID + r]);
-  }
-  for (int t = tid; t < M_OUT * N_HID; t += step) {
-    const int r = t / N_HID, c = t % N_HID;               // w3: [output r][hidden c]
-    P->w3[t] = r < N_OUT ? bf16_bits(W3[r * N_HID + c]) : 0;
-    const int h = t / M_OUT, o = t % M_OUT;               // w3t: [hidden h][output o]
-    P->w3t[t] = o < N_OUT ? bf16_bits(W3[o * N_HID + h]) : 0;
-  }
-  for (int t = tid; t < M_OUT; t += step) {
-    P->b1[t] = t < N_HID ? b1[t] : 0.f;
-    P->b2[t] = t < N_HID ? b2[t] : 0.f;
-    P->b3[t] = t < N_OUT ? b3[t] : 0.f;
-    P->y_scale[t] = t < N_OUT ? norm[2 * N_IN + t] : 0.f;
-    P->zero[t] = 0.f;
-  }
-  for (int t = tid; t < K_IN; t += step) {
-    P->x_mean[t] = t < N_IN ? norm[t] : 0.f;
-    P->x_iscale[t] = t < N_IN ? norm[N_IN + t] : 0.f;
-  }
-  // the fused step's copies: logical row k at physical row perm_row(k); the output
-  // layer carries y_scale so that its result is the moment correction itself
-  for (int t = tid; t < 64 * K_IN; t += step) {
-    const int row = t / K_IN, c = t % K_IN, k = perm_row(row);
-    P->w1p[t] = c < N_IN ? bf16_bits(W1[k * N_IN + c]) : 0;
+  const float* y_scale = norm + 2 * N_IN;
+  // The fused step's copies (..p) hold logical row k at physical row perm_row(k); their output
+  // layer carries y_scale so that its result is the moment correction itself.
+  if (blockIdx.y == 0) {
+    if (t >= N_HID * K_IN) return;
+    const int r = t / K_IN, c = t % K_IN, k = perm_row(r);
+    const float w = W1[r * N_IN + min(c, N_IN - 1)], wp = W1[k * N_IN + min(c, N_IN - 1)];
+    P->w1[t] = c < N_IN ? bf16_bits(w) : 0;
+    P->w1p[t] = c < N_IN ? bf16_bits(wp) : 0;
     P->tab.feat[t] = kStepTables.feat[t];
     P->tab.minv[t] = kStepTables.minv[t];
-  }
-  for (int t = tid; t < 64 * N_HID; t += step) {
-    const int row = t / N_HID, c = t % N_HID, k = perm_row(row);
-    P->w2p[t] = bf16_bits(W2[k * N_HID + c]);
-    P->w3p[t] = k < N_OUT ? bf16_bits(norm[2 * N_IN + k] * W3[k * N_HID + c]) : 0;
-  }
-  for (int row = tid; row < 64; row += step) {
-    const int k = perm_row(row);
-    P->b1p[row] = b1[k];
-    P->b2p[row] = b2[k];
-    P->b3p[row] = k < N_OUT ? norm[2 * N_IN + k] * b3[k] : 0.f;
-    P->x_mean_p[row] = k < N_IN ? norm[k] : 0.f;
-    P->x_iscale_p[row] = k < N_IN ? norm[N_IN + k] : 0.f;
+  } else if (blockIdx.y == 1) {
+    const int r = t / N_HID, c = t % N_HID, k = perm_row(r);
+    const float w = W2[t], wt = W2[c * N_HID + r], wp = W2[k * N_HID + c];
+    P->w2[t] = bf16_bits(w);
+    P->w2t[t] = bf16_bits(wt);
+    P->w2p[t] = bf16_bits(wp);
+  } else if (blockIdx.y == 2) {
+    const int r = t / N_HID, c = t % N_HID, k = perm_row(r);     // w3: [output r][hidden c]
+    const int h = t / M_OUT, o = t % M_OUT;                      // w3t: [hidden h][output o]
+    const int rr = min(r, N_OUT - 1), oo = min(o, N_OUT - 1), kk = min(k, N_OUT - 1);
+    const float w = W3[rr * N_HID + c], wt = W3[oo * N_HID + h], wp = y_scale[kk] * W3[kk * N_HID + c];
+    P->w3[t] = r < N_OUT ? bf16_bits(w) : 0;
+    P->w3t[t] = o < N_OUT ? bf16_bits(wt) : 0;
+    P->w3p[t] = k < N_OUT ? bf16_bits(wp) : 0;
+  } else if (t < M_OUT) {
+    const int k = perm_row(t), o = min(t, N_OUT - 1), ko = min(k, N_OUT - 1), in = min(t, N_IN - 1), ki = min(k, N_IN - 1);
+    const float v1 = b1[t], v2 = b2[t], v3 = b3[o], ys = y_scale[o], xm = norm[in], xi = norm[N_IN + in];
+    const float p1 = b1[k], p2 = b2[k], p3 = y_scale[ko] * b3[ko], pm = norm[ki], pi = norm[N_IN + ki];
+    P->b1[t] = v1;
+    P->b2[t] = v2;
+    P->b3[t] = t < N_OUT ? v3 : 0.f;
+    P->y_scale[t] = t < N_OUT ? ys : 0.f;
+    P->zero[t] = 0.f;
+    if (t < K_IN) {
+      P->x_mean[t] = t < N_IN ? xm : 0.f;
+      P->x_iscale[t] = t < N_IN ? xi : 0.f;
+    }
+    P->b1p[t] = p1;
+    P->b2p[t] = p2;
+    P->b3p[t] = k < N_OUT ? p3 : 0.f;
+    P->x_mean_p[t] = k < N_IN ? pm : 0.f;
+    P->x_iscale_p[t] = k < N_IN ? pi : 0.f;
   }
 }
+static_assert(N_HID == 64 && M_OUT == 64 && N_HID * K_IN <= N_HID * N_HID && M_OUT * N_HID == N_HID * N_HID &&
+              64 * K_IN == N_HID * K_IN, "one thread per element of each table");
 
 // V floats read or written at once.
 template <int V> struct FloatPiece { typedef float type __attribute__((ext_vector_type(V))); };
@@ -842,7 +844,7 @@ __global__ __launch_bounds__(256) void pairs_kernel(const float* __restrict__ a,
 // host launchers
 // ---------------------------------------------------------------------------
 hipError_t mlp_launch_pack(const float* theta, const float* norm, void* packed, hipStream_t st) {
-  hipLaunchKernelGGL(mlp::pack_kernel, dim3(mlp::kPackBlocks), dim3(256), 0, st, theta, norm, (mlp::Packed*)packed);
+  hipLaunchKernelGGL(mlp::pack_kernel, dim3(mlp::kPackBlocks, mlp::kPackRows), dim3(256), 0, st, theta, norm, (mlp::Packed*)packed);
   return hipGetLastError();
 }
 
