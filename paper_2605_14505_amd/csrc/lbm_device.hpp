@@ -21,15 +21,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "node_order.hpp"
 #include "stencil.hpp"
 
 namespace stgv {
-
-// Threads (and nodes) of a node kernel's block: 256, and single wavefronts where the box has
-// no more than two of them per CU, so that every CU has some (mean step: 32^3 6.59 -> 5.36 us,
-// 16^3 4.94 -> 4.54; 128 threads 6.01 and 4.60; at 40^3 single wavefronts lose, 9.34 -> 10.1).
-constexpr int kNodeBlock = 256;
-constexpr int node_threads(int n) { return (int64_t)n * n * n <= 2 * 256 * 64 ? 64 : kNodeBlock; }
 
 enum Mode : int { MODE_EVEN = 0, MODE_ODD = 1, MODE_AB = 2 };
 // Rows of the box as a node kernel sees them: of any length, of whole 128-byte lines, of whole
@@ -71,34 +66,6 @@ struct PhysConsts {
   double beta;        // (d rho_b / dz)_LU
   double g_over_n;    // G / N for the potential energy
 };
-
-struct Geometry {
-  int n;             // box edge
-  int64_t stride;    // elements between population arrays
-  uint32_t n3;       // nodes
-  uint32_t div_mul;  // i / n = (i div_mul) >> (32 + div_shift) for i < 2^30
-  int div_shift;
-  int xcd_group;     // consecutive blocks that the x-shifted steps keep on one XCD
-};
-
-// Division by n as a multiplication: with 2^(s-1) < n <= 2^s and m = floor(2^(31 + s) / n) + 1
-// (< 2^32), m n exceeds 2^(31 + s) by at most n <= 2^s, so i m / 2^(31 + s) exceeds i / n by less
-// than 1 / n for every i < 2^31 (n^3 <= 2^30).
-inline Geometry make_geometry(int n, int64_t stride) {
-  Geometry g{};
-  g.n = n;
-  g.stride = stride;
-  g.n3 = (uint32_t)n * n * n;
-  int s = 0;
-  while ((1 << s) < n) ++s;
-  g.div_mul = (uint32_t)((1ull << (31 + s)) / (unsigned)n + 1);
-  g.div_shift = s - 1;
-  // blocks that make up whole rows (at most 8 of them)
-  int rows = n, blk = node_threads(n);
-  while (blk > 1 && rows % 2 == 0) { rows /= 2; blk /= 2; }
-  g.xcd_group = rows < 8 ? rows : 8;
-  return g;
-}
 
 // ---------------------------------------------------------------------------
 // storage <-> compute conversion (compute type C is float or double)

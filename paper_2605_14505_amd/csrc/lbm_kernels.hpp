@@ -34,26 +34,11 @@ constexpr int step_min_blocks() {
 // and every wavefront's access is one contiguous run.  Against x-y block shapes (128 x 2 for
 // 90^3 and 100^3, 32 x 8 for 96^3 and 160^3), mean step in us: 90^3 FP16 27 x 7 35.6 -> 23.8,
 // FP32 27 x 19 72.2 -> 50.1; 100^3 FP32 91.7 -> 67.5; 160^3 FP16 215 -> 145; 96^3 FP32
-// 60.2 -> 58.5; boxes whose rows are whole wavefronts are unchanged within 1 %.
-//
-// The hardware hands consecutive workgroups to the 8 XCDs in turn, each with its own L2, so
-// neighbouring blocks sit on different XCDs; the steps whose loads or stores are shifted
-// along x (odd AA, A-B) share a line at every block seam inside a row, and then fetch it from
-// HBM twice (at 512^3 FP16, 15 % more than the algorithmic bytes).  For those steps the
-// workgroups are renumbered so that the `xcd_group` consecutive blocks that make up whole
-// rows are 8 apart in dispatch order, i.e. on one XCD: workgroup L = 8 (G q + h) + k holds
-// block G (8 q + k) + h; the blocks past the last multiple of 8 G keep their places.
+// 60.2 -> 58.5; boxes whose rows are whole wavefronts are unchanged within 1 %.  The steps shifted along x take their blocks in the
+// XCD-aware order of block_at.
 template <int MODE>
 __device__ __forceinline__ uint32_t node_block(const Geometry& geo) {
-  uint32_t b = blockIdx.x;
-  if (MODE != MODE_EVEN && geo.xcd_group > 1) {
-    const uint32_t G = (uint32_t)geo.xcd_group, whole = gridDim.x / (8 * G) * (8 * G);
-    if (b < whole) {
-      const uint32_t k = b & 7, rest = b >> 3;
-      b = G * (8 * (rest / G) + k) + rest % G;
-    }
-  }
-  return b;
+  return MODE != MODE_EVEN ? block_at(blockIdx.x, gridDim.x, geo) : blockIdx.x;
 }
 template <int MODE>
 __device__ __forceinline__ uint32_t node_of(const Geometry& geo) {
@@ -67,10 +52,10 @@ __device__ __forceinline__ NodeIndex index_of(uint32_t i, const Geometry& geo) {
   NodeIndex ix{};
   ix.base = i;
   if constexpr (MODE != MODE_EVEN) {
-    uint32_t r = __umulhi(i, geo.div_mul) >> geo.div_shift;
+    uint32_t r = over_n(i, geo);
     const uint32_t x = i - r * (uint32_t)geo.n;
     if constexpr (ROWS == ROWS_WAVES) r = (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
-    const uint32_t z = __umulhi(r, geo.div_mul) >> geo.div_shift;
+    const uint32_t z = over_n(r, geo);
     ix = make_index((int)x, (int)(r - z * (uint32_t)geo.n), (int)z, geo.n);
   }
   return ix;

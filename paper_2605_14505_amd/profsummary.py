@@ -24,8 +24,8 @@ PROFILES = os.path.join(ROOT, "profiles")
 
 
 # the sources the step kernels are compiled from (the profiled kernels)
-STEP_SOURCES = ("stencil.hpp", "lbm_device.hpp", "mlp_device.hpp", "lbm_kernels.hpp", "lbm_launch.hpp",
-                "lbm_instances.hpp", "lbm_fp32.hip", "lbm_fp16.hip", "lbm_bf16.hip", "learned_step.hip")
+STEP_SOURCES = ("stencil.hpp", "node_order.hpp", "lbm_device.hpp", "mlp_device.hpp", "lbm_kernels.hpp",
+                "lbm_launch.hpp", "lbm_instances.hpp", "lbm_fp32.hip", "lbm_fp16.hip", "lbm_bf16.hip", "learned_step.hip")
 
 
 def code_only(src):

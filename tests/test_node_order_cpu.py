@@ -1,0 +1,51 @@
+"""The node kernels' index maps (csrc/node_order.hpp), compiled for the host: division by the
+box edge against the integer division, and the block order against a permutation."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_14505_amd", "csrc")
+
+# The quotient is monotone in i, so it is right everywhere if it is right on both sides of
+# every multiple of n below the box's n^3 nodes.
+PROGRAM = r"""
+#include "node_order.hpp"
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+using namespace stgv;
+int main(int, char** argv) {
+  for (int n = atoi(argv[1]); n <= atoi(argv[2]); ++n) {
+    const Geometry g = make_geometry(n, 0);
+    for (uint32_t q = 0; q < (uint32_t)n * n; ++q)
+      if (over_n(q * n, g) != q || over_n(q * n + n - 1, g) != q) { printf("n %d: quotient %u\n", n, q); return 1; }
+    const uint32_t blocks = (g.n3 + node_threads(n) - 1) / node_threads(n);
+    std::vector<char> seen(blocks, 0);
+    for (uint32_t b = 0; b < blocks; ++b) {
+      const uint32_t to = block_at(b, blocks, g);
+      if (to >= blocks || seen[to]) { printf("n %d: block %u -> %u\n", n, b, to); return 1; }
+      seen[to] = 1;
+    }
+  }
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def checker(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if not cxx:
+        pytest.skip("no host compiler")
+    d = tmp_path_factory.mktemp("node_order")
+    (d / "check.cpp").write_text(PROGRAM)
+    subprocess.run([cxx, "-O2", "-std=c++17", "-I", CSRC, str(d / "check.cpp"), "-o", str(d / "check")], check=True)
+    return str(d / "check")
+
+
+@pytest.mark.parametrize("lo,hi", [(4, 64), (65, 200), (250, 260), (384, 385), (511, 513), (1023, 1024)])
+def test_division_and_block_order(checker, lo, hi):
+    r = subprocess.run([checker, str(lo), str(hi)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
