@@ -695,15 +695,23 @@ __global__ __launch_bounds__(kRestrictThreads) void restrict_kernel(const T* __r
   const RestrictShape sh = restrict_shape(nc);
   const bool ring = sh.segs == 1;
   // consecutive workgroups go to the 8 XCDs in turn: renumbered so that each XCD has a run of
-  // neighbouring (Z, Y), whose shared rows its L2 may still hold
+  // neighbouring (Y, Z), whose shared rows its L2 may still hold; in tiles of 8 x 8 of them
+  // (about what an XCD has resident) where the box divides into such tiles
   int bx = blockIdx.x, by = blockIdx.y, Z = blockIdx.z;
   const int gx = gridDim.x, gy = gridDim.y, blocks = gx * gy * (int)gridDim.z;
   if ((blocks & 7) == 0) {
     int b = bx + gx * (by + gy * Z);
     b = (b & 7) * (blocks >> 3) + (b >> 3);
     bx = b % gx;
-    by = (b / gx) % gy;
-    Z = b / (gx * gy);
+    b /= gx;
+    if (((gy | nc) & 7) == 0) {
+      const int tile = b >> 6, ty = gy >> 3;
+      by = 8 * (tile % ty) + (b & 7);
+      Z = 8 * (tile / ty) + ((b >> 3) & 7);
+    } else {
+      by = b % gy;
+      Z = b / gy;
+    }
   }
   const int Y0 = by * sh.rows, X0 = bx * sh.xseg;
   const int width = ring ? n : kRestrictThreads;
@@ -718,14 +726,14 @@ __global__ __launch_bounds__(kRestrictThreads) void restrict_kernel(const T* __r
 #pragma unroll
   for (int k = 0; k < NV; ++k) a[k] = 0.f;
   if (yy < sh.rows && Y < nc && (ring || x < n)) {
-    // neighbouring Y sweep in opposite directions, so that the row they share is read by
-    // both at the same time
-    const int dir = (Y & 1) ? -1 : 1;
+    // neighbouring Y, and neighbouring Z, sweep in opposite directions, so that the rows they
+    // share are read by both at the same time
+    const int dir = (Y & 1) ? -1 : 1, dirz = (Z & 1) ? -1 : 1;
 #pragma unroll 1
-    for (int dz = -2; dz <= 2; ++dz)
+    for (int dzi = -2; dzi <= 2; ++dzi)
 #pragma unroll 1
       for (int dyi = -2; dyi <= 2; ++dyi) {
-        const int dy = dir * dyi;
+        const int dy = dir * dyi, dz = dirz * dzi;
         const float w = wf(dy) * wf(dz);
         const NodeIndex ix = make_index(x, wrap(4 * Y + dy), wrap(4 * Z + dz), n);
         float f[27], g[19];
