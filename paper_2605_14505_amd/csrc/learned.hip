@@ -662,37 +662,45 @@ __global__ __launch_bounds__(64) void norm_kernel(const double* __restrict__ par
 // and each fine node's equilibria are formed 25 / 16 times, against 125 / 64 strided reads
 // and evaluations when a thread walked its coarse node's whole 5^3 stencil.
 //
-// A block is 256 lanes: with n <= 256 whole fine rows of 256 / n neighbouring Y (the x sums
-// wrap around in LDS), else the row segment of kRestrictX coarse nodes and the halo of two
-// fine nodes on its left and right.
+// A block is LANES lanes (256): with n <= LANES whole fine rows of LANES / n neighbouring Y (the
+// x sums wrap around in LDS), else the row segment of (LANES - 1) / 4 coarse nodes and the halo
+// of two fine nodes on its left and right.
+//
+// Up to 64^3 that is too few wavefronts for the card and the time is the chain of 25 rows: there a
+// block has a wavefront for each of the five planes, added through LDS (64^3 -> 16^3 44.5 -> 21.0
+// us, 32^3 38.9 -> 18.7).  Above, the split loses: with two segments a row 46.0 -> 59.6 us at 68^3,
+// with 128 lanes, which spill, 48.7.
 //
 // 256^3 -> 64^3, FP32: 3480 us for the per-node stencil, 816 in this form with loads that
 // bypass the caches, 725 with cached ones (four rows in sixteen are read by two blocks), 712
-// with the XCD order; 500 us is one read of the state.
+// with a run of (Y, Z) per XCD, 659 with tiles of them and both sweeps opposed; 500 us is one
+// read of the state.
 // ---------------------------------------------------------------------------
 constexpr int kRestrictThreads = 256, kRestrictChunk = 23;     // 92 sums go through LDS in four chunks
-constexpr int kRestrictX = (kRestrictThreads - 1) / 4;         // 63 coarse nodes need 4 x 63 + 1 fine ones
 
 struct RestrictShape {
   int rows;     // coarse rows (Y) of a block
   int xseg;     // coarse nodes of a block's row segment
   int segs;     // segments of a row
 };
+template <int LANES>
 __host__ __device__ inline RestrictShape restrict_shape(int nc) {
   const int n = 4 * nc;
-  if (n <= kRestrictThreads) return {kRestrictThreads / n, nc, 1};
-  return {1, kRestrictX, (nc + kRestrictX - 1) / kRestrictX};
+  if (n <= LANES) return {LANES / n, nc, 1};
+  constexpr int X = (LANES - 1) / 4;                             // X coarse nodes need 4 X + 1 fine ones
+  return {1, X, (nc + X - 1) / X};
 }
 
-template <typename T, int MODE>
-__global__ __launch_bounds__(kRestrictThreads) void restrict_kernel(const T* __restrict__ fine, Geometry gf,
+template <typename T, int MODE, int LANES, int PLANES>
+__global__ __launch_bounds__(LANES * PLANES) void restrict_kernel(const T* __restrict__ fine, Geometry gf,
                                                                     PhysConsts cf, int nc, float sf, float sg,
                                                                     float* __restrict__ out) {
   constexpr int NV = 2 * (27 + 19);
   static_assert(NV % kRestrictChunk == 0, "chunks of equal size");
-  __shared__ float xs[kRestrictChunk][kRestrictThreads];
-  const int n = gf.n, t = threadIdx.x;
-  const RestrictShape sh = restrict_shape(nc);
+  static_assert((PLANES == 1 && LANES == kRestrictThreads) || PLANES == 5, "all five planes, or one each");
+  __shared__ float xs[kRestrictChunk][LANES * PLANES];
+  const int n = gf.n, t = (int)threadIdx.x % LANES, plane = (int)threadIdx.x / LANES;
+  const RestrictShape sh = restrict_shape<LANES>(nc);
   const bool ring = sh.segs == 1;
   // consecutive workgroups go to the 8 XCDs in turn: renumbered so that each XCD has a run of
   // neighbouring (Y, Z), whose shared rows its L2 may still hold; in tiles of 8 x 8 of them
@@ -714,7 +722,7 @@ __global__ __launch_bounds__(kRestrictThreads) void restrict_kernel(const T* __r
     }
   }
   const int Y0 = by * sh.rows, X0 = bx * sh.xseg;
-  const int width = ring ? n : kRestrictThreads;
+  const int width = ring ? n : LANES;
   const int yy = t / width, l = t % width;
   const int Y = Y0 + yy;
   int x = ring ? l : 4 * X0 - 2 + l;
@@ -730,7 +738,7 @@ __global__ __launch_bounds__(kRestrictThreads) void restrict_kernel(const T* __r
     // share are read by both at the same time
     const int dir = (Y & 1) ? -1 : 1, dirz = (Z & 1) ? -1 : 1;
 #pragma unroll 1
-    for (int dzi = -2; dzi <= 2; ++dzi)
+    for (int dzi = PLANES > 1 ? plane - 2 : -2; dzi <= (PLANES > 1 ? plane - 2 : 2); ++dzi)
 #pragma unroll 1
       for (int dyi = -2; dyi <= 2; ++dyi) {
         const int dy = dir * dyi, dz = dirz * dzi;
@@ -751,7 +759,7 @@ __global__ __launch_bounds__(kRestrictThreads) void restrict_kernel(const T* __r
   }
   // the five fine x of this thread's coarse node (threads q < rows * xseg)
   const int cy = t / sh.xseg, cx = t % sh.xseg;
-  const bool coarse = cy < sh.rows && Y0 + cy < nc && X0 + cx < nc;
+  const bool coarse = plane == 0 && cy < sh.rows && Y0 + cy < nc && X0 + cx < nc;
   int at[5];
 #pragma unroll
   for (int d = 0; d < 5; ++d) {
@@ -763,8 +771,17 @@ __global__ __launch_bounds__(kRestrictThreads) void restrict_kernel(const T* __r
   for (int k0 = 0; k0 < NV; k0 += kRestrictChunk) {
     if (k0) __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kRestrictChunk; ++k) xs[k][t] = a[k0 + k];
+    for (int k = 0; k < kRestrictChunk; ++k) xs[k][threadIdx.x] = a[k0 + k];
     __syncthreads();
+    if constexpr (PLANES > 1) {
+      for (int k = plane; k < kRestrictChunk; k += PLANES) {
+        float z = xs[k][t];
+#pragma unroll
+        for (int p = 1; p < PLANES; ++p) z += xs[k][p * LANES + t];
+        xs[k][t] = z;
+      }
+      __syncthreads();
+    }
     if (coarse) {
 #pragma unroll
       for (int k = 0; k < kRestrictChunk; ++k)
@@ -902,15 +919,24 @@ hipError_t mlp_launch_norm(const float* x, const float* y, int64_t rows, double*
   return hipGetLastError();
 }
 
+template <typename T, int LANES, int PLANES>
+static void restrict_launch(const T* fine, int mode, Geometry gf, PhysConsts cf, int nc, float sf, float sg,
+                            float* out, hipStream_t st) {
+  const mlp::RestrictShape sh = mlp::restrict_shape<LANES>(nc);
+  const dim3 grid((unsigned)sh.segs, (unsigned)((nc + sh.rows - 1) / sh.rows), (unsigned)nc), block(LANES * PLANES);
+  if (mode == MODE_ODD)
+    hipLaunchKernelGGL((mlp::restrict_kernel<T, MODE_ODD, LANES, PLANES>), grid, block, 0, st, fine, gf, cf, nc, sf, sg, out);
+  else
+    hipLaunchKernelGGL((mlp::restrict_kernel<T, MODE_EVEN, LANES, PLANES>), grid, block, 0, st, fine, gf, cf, nc, sf, sg, out);
+}
+
 template <typename T>
 static hipError_t restrict_t(const void* fine, int mode, Geometry gf, PhysConsts cf, int nc, float sf,
                              float sg, float* out, hipStream_t st) {
-  const mlp::RestrictShape sh = mlp::restrict_shape(nc);
-  const dim3 grid((unsigned)sh.segs, (unsigned)((nc + sh.rows - 1) / sh.rows), (unsigned)nc), block(mlp::kRestrictThreads);
-  if (mode == MODE_ODD)
-    hipLaunchKernelGGL((mlp::restrict_kernel<T, MODE_ODD>), grid, block, 0, st, (const T*)fine, gf, cf, nc, sf, sg, out);
+  if (gf.n <= 64)
+    restrict_launch<T, 64, 5>((const T*)fine, mode, gf, cf, nc, sf, sg, out, st);
   else
-    hipLaunchKernelGGL((mlp::restrict_kernel<T, MODE_EVEN>), grid, block, 0, st, (const T*)fine, gf, cf, nc, sf, sg, out);
+    restrict_launch<T, mlp::kRestrictThreads, 1>((const T*)fine, mode, gf, cf, nc, sf, sg, out, st);
   return hipGetLastError();
 }
 

@@ -316,7 +316,7 @@ def test_restriction_matches_oracle(forcing):
 # (fine n, tile): blocks of 16, 4 (a remainder of Y), 2 and 1 fine rows, idle lanes (60, 180), and
 # rows split into segments with a remainder (260, 516: n > 256)
 @pytest.mark.parametrize("storage", ["fp32", "bf16"])
-@pytest.mark.parametrize("n,tile", [(16, 16), (60, 20), (104, 8), (128, 32), (180, 20), (260, 20), (516, 12)])
+@pytest.mark.parametrize("n,tile", [(16, 16), (60, 20), (64, 16), (68, 68), (104, 8), (128, 32), (180, 20), (260, 20), (516, 12)])
 def test_restriction_of_a_tiled_state_matches_oracle(n, tile, storage):
     # a state periodic with a small tile restricts to the tile's restriction, tiled; an odd step
     # count (of free streaming, exact) covers the in-place layout's other parity
