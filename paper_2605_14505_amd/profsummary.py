@@ -81,11 +81,13 @@ def is_step_kernel(name):
 
 
 def is_plain_step(name):
-    """A time step without diagnostic outputs: FLAGS == 1 (the last template argument, in
-    the demangled or the mangled name), or the row-aligned odd step, which has no flags."""
+    """A time step without diagnostic outputs: FLAGS == 1 (the template argument before the row
+    kind and the cache policy, in the demangled or the mangled name), or the row-aligned odd
+    step, which has no flags."""
     if "lbm_step_ring_kernel" in name:
         return True
-    m = re.search(r"lbm_step_kernel<[^>]*, (\d+)>\(", name) or re.search(r"lbm_step_kernelI.*ELi(\d+)EEEv", name)
+    m = (re.search(r"lbm_step_kernel<[^>]*, (\d+), \d+, (?:true|false)>\(", name) or
+         re.search(r"lbm_step_kernelI.*ELi(\d+)ELi\d+ELb[01]EEEv", name))
     return bool(m) and m.group(1) == "1"
 
 
