@@ -35,7 +35,7 @@ int main(int, char** argv) {
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def program(tmp_path_factory):
     cxx = shutil.which("g++") or shutil.which("c++")
     if not cxx:
         pytest.skip("no host compiler")
@@ -46,6 +46,6 @@ def checker(tmp_path_factory):
 
 
 @pytest.mark.parametrize("lo,hi", [(4, 64), (65, 200), (250, 260), (384, 385), (511, 513), (1023, 1024)])
-def test_division_and_block_order(checker, lo, hi):
-    r = subprocess.run([checker, str(lo), str(hi)], capture_output=True, text=True)
+def test_division_and_block_order(program, lo, hi):
+    r = subprocess.run([program, str(lo), str(hi)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
