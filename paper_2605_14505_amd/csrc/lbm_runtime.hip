@@ -1017,7 +1017,7 @@ int lbm_ke_spectrum(lbm_ctx* c, void* work, size_t work_bytes, double* shells) {
   if (e != hipSuccess) return hip_fail(c, e, "fields kernel");
   const size_t n3 = (size_t)n * n * n;
   char err[512] = {0};
-  e = spectrum_launch(fields + n3, fields + 2 * n3, fields + 3 * n3, n, c->p.u0, static_cast<char*>(work) + fb,
+  e = spectrum_launch(fields + n3, n, c->p.u0, static_cast<char*>(work) + fb,
                       work_bytes - fb, shells, c->stream, err);
   if (e == hipErrorInvalidValue && err[0]) { set_err(c->err, "%s", err); return LBM_ESIZE; }
   if (e == hipErrorUnknown && err[0]) { set_err(c->err, "%s", err); return LBM_EHIP; }

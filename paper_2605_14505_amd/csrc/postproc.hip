@@ -17,8 +17,19 @@
 namespace stgv {
 namespace {
 
-constexpr int kShellBlocks = 1024;
+constexpr int kShellBlocks = 1024;           // at most, a component
 constexpr int kShellThreads = 256;
+// Components that one transform and one binning launch take.  Up to 200^3 all three: the time is
+// launches (16^3 33.9 -> 16.1 us, 64^3 53.4 -> 30.1) and, above, the tail of each (128^3 191 -> 140,
+// 160^3 329 -> 260, 200^3 535 -> 496), the results the same; beyond, the three half spectra outgrow
+// the last-level cache (251^3 2489 -> 2790, 256^3 1117 -> 1062, 300^3 1857 -> 2018) and one is held.
+constexpr int kBatchUpTo = 200;
+inline int components_at_once(int n) { return n <= kBatchUpTo ? 3 : 1; }
+inline int64_t half_spectrum(int n) { return (int64_t)(n / 2 + 1) * n * n; }
+inline int shell_blocks(int n) {
+  const int64_t b = (half_spectrum(n) + kShellThreads - 1) / kShellThreads;
+  return b < kShellBlocks ? (int)b : kShellBlocks;
+}
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
@@ -27,7 +38,7 @@ size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 // (kx, ky, kz) along by adding the stride's own digits, so no element needs a division, and
 // the shell is taken in FP32: |k|^2 is an integer below 2^20, and the values next to a shell's
 // edge, (s - 1/2)^2 -+ 1/4 and 3/4, are 1e-4 or more away from it in |k|, twice the rounding.
-// Bound by reading c: 256^3 30 -> 20 us a component.  partial is [shell][block], so that
+// Bound by reading c: 256^3 30 -> 20 us a component.  blockIdx.y is the component of a batch; partial is [shell][block], so that
 // the reduction reads a shell's partials contiguously.
 struct Digits {
   int kx, ky, kz;
@@ -40,6 +51,8 @@ __global__ __launch_bounds__(kShellThreads) void shell_kernel(const float2* __re
   for (int s = threadIdx.x; s < nshell; s += blockDim.x) hist[s] = 0.0;
   __syncthreads();
   const int nh = n / 2 + 1, total = nh * n * n, step = gridDim.x * blockDim.x;
+  c += (int64_t)blockIdx.y * total;
+  part0 += blockIdx.y * gridDim.x;
   auto digits = [=](int i) { return Digits{i % nh, (i / nh) % n, i / nh / n}; };
   const Digits d = digits(step);
   int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -93,7 +106,7 @@ const Plan* get_plan(int n, char* err) {
   Plan p;
   const size_t lengths[3] = {(size_t)n, (size_t)n, (size_t)n};
   if (rocfft_plan_create(&p.plan, rocfft_placement_notinplace, rocfft_transform_type_real_forward,
-                         rocfft_precision_single, 3, lengths, 1, nullptr) != rocfft_status_success) {
+                         rocfft_precision_single, 3, lengths, components_at_once(n), nullptr) != rocfft_status_success) {
     snprintf(err, 512, "rocfft_plan_create failed for %d^3", n);
     return nullptr;
   }
@@ -111,10 +124,10 @@ struct Layout {
 
 Layout layout(int n, size_t fft_work) {
   Layout l;
-  const size_t cbytes = (size_t)(n / 2 + 1) * n * n * sizeof(float2);
+  const size_t cbytes = (size_t)half_spectrum(n) * components_at_once(n) * sizeof(float2);
   l.complex_off = 0;
   l.partial_off = align256(cbytes);
-  l.fft_off = l.partial_off + align256((size_t)3 * kShellBlocks * spectrum_shells(n) * sizeof(double));
+  l.fft_off = l.partial_off + align256((size_t)3 * shell_blocks(n) * spectrum_shells(n) * sizeof(double));
   l.total = l.fft_off + align256(fft_work);
   return l;
 }
@@ -128,7 +141,7 @@ size_t spectrum_extra_bytes(int n, char* err) {
   return p ? layout(n, p->work).total : 0;
 }
 
-hipError_t spectrum_launch(const float* ux, const float* uy, const float* uz, int n, double u0, void* work,
+hipError_t spectrum_launch(const float* u, int n, double u0, void* work,
                            size_t work_bytes, double* out, hipStream_t st, char* err) {
   const Plan* p = get_plan(n, err);
   if (!p) return hipErrorUnknown;
@@ -151,14 +164,14 @@ hipError_t spectrum_launch(const float* ux, const float* uy, const float* uz, in
     ok = rocfft_execution_info_set_work_buffer(info, base + l.fft_off, p->work) == rocfft_status_success;
   const int nshell = spectrum_shells(n);
   const double scale = 1.0 / (2.0 * std::pow((double)n, 6.0) * u0 * u0);
-  const float* comps[3] = {ux, uy, uz};
-  for (int c = 0; ok && c < 3; ++c) {
-    void* in[1] = {const_cast<float*>(comps[c])};
+  const int at_once = components_at_once(n), blocks = shell_blocks(n);
+  for (int c = 0; ok && c < 3; c += at_once) {
+    void* in[1] = {const_cast<float*>(u + c * (int64_t)n * n * n)};
     void* outp[1] = {cbuf};
     ok = rocfft_execute(p->plan, in, outp, info) == rocfft_status_success;
     if (!ok) break;
-    hipLaunchKernelGGL(shell_kernel, dim3(kShellBlocks), dim3(kShellThreads), nshell * sizeof(double), st, cbuf, n,
-                       nshell, scale, partial, 3 * kShellBlocks, c * kShellBlocks);
+    hipLaunchKernelGGL(shell_kernel, dim3(blocks, at_once), dim3(kShellThreads), nshell * sizeof(double), st, cbuf, n,
+                       nshell, scale, partial, 3 * blocks, c * blocks);
     e = hipGetLastError();
     if (e != hipSuccess) break;
   }
@@ -168,7 +181,7 @@ hipError_t spectrum_launch(const float* ux, const float* uy, const float* uz, in
     return hipErrorUnknown;
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(shell_reduce_kernel, dim3(nshell), dim3(256), 0, st, partial, 3 * kShellBlocks, out);
+  hipLaunchKernelGGL(shell_reduce_kernel, dim3(nshell), dim3(256), 0, st, partial, 3 * blocks, out);
   return hipGetLastError();
 }
 

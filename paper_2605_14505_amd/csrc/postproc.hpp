@@ -1,5 +1,5 @@
-// Kinetic-energy spectrum of a velocity field on the GPU: three rocFFT real-to-complex
-// transforms and a shell-binning reduction (Section 3.5, spectra at peak activity).
+// Kinetic-energy spectrum of a velocity field on the GPU: rocFFT real-to-complex
+// transforms of the three components and a shell-binning reduction (Section 3.5, spectra at peak activity).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
@@ -15,10 +15,10 @@ int spectrum_shells(int n);
 // err when rocFFT fails.
 size_t spectrum_extra_bytes(int n, char* err);
 
-// E(k) of u = (ux, uy, uz) / u0 (each n^3 FP32, x fastest) into out[spectrum_shells(n)]
-// (FP64, device).  work: spectrum_extra_bytes(n) bytes, 256-byte aligned.  Queued on st.
+// E(k) of the three components u / u0 (n^3 FP32 each, x fastest, one behind the other) into
+// out[spectrum_shells(n)] (FP64, device).  work: spectrum_extra_bytes(n) bytes, 256-byte aligned.  Queued on st.
 // Returns a HIP error, or hipErrorUnknown with err filled when rocFFT fails.
-hipError_t spectrum_launch(const float* ux, const float* uy, const float* uz, int n, double u0,
-                           void* work, size_t work_bytes, double* out, hipStream_t st, char* err);
+hipError_t spectrum_launch(const float* u, int n, double u0, void* work, size_t work_bytes, double* out,
+                           hipStream_t st, char* err);
 
 }  // namespace stgv
