@@ -34,7 +34,8 @@ constexpr int step_min_blocks() {
 // and every wavefront's access is one contiguous run.  Against x-y block shapes (128 x 2 for
 // 90^3 and 100^3, 32 x 8 for 96^3 and 160^3), mean step in us: 90^3 FP16 27 x 7 35.6 -> 23.8,
 // FP32 27 x 19 72.2 -> 50.1; 100^3 FP32 91.7 -> 67.5; 160^3 FP16 215 -> 145; 96^3 FP32
-// 60.2 -> 58.5; boxes whose rows are whole wavefronts are unchanged within 1 %.  The steps shifted along x take their blocks in the
+// 60.2 -> 58.5; boxes whose rows are whole wavefronts are unchanged within 1 %.  The steps shifted
+// along x take their blocks in the
 // XCD-aware order of block_at.
 template <int MODE>
 __device__ __forceinline__ uint32_t node_block(const Geometry& geo) {
@@ -89,6 +90,15 @@ template <int MODE, int FLAGS, typename T, int QF>
 constexpr bool kBatchBf16 = MODE == MODE_EVEN && FLAGS == K_COLLIDE && std::is_same<T, bf16_t>::value && QF == 27;
 #define STGV_OPERANDS_27(a) "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15]), "+v"(a[16]), "+v"(a[17]), "+v"(a[18]), "+v"(a[19]), "+v"(a[20]), "+v"(a[21]), "+v"(a[22]), "+v"(a[23]), "+v"(a[24]), "+v"(a[25]), "+v"(a[26])
 
+// FP32 states that stay in the last-level cache: all loads of the in-place steps ahead of the first
+// wait.  Their time is latency, and the compiler left a wait for the first values between two
+// batches of the even step's loads and, with Guo forcing, between single loads of the odd step's.
+// Mean step in us: 8^3 4.37 -> 4.29, 32^3 5.36 -> 5.26, 64^3 16.05 -> 15.90, 90^3 42.7 -> 42.1,
+// 27 x 27 64^3 18.98 -> 18.08.  2-byte storage (BF16 64^3 9.33 -> 9.46), the A-B push (128^3 153.3
+// -> 154.9) and larger states (192^3 464 -> 468, 250^3 1095 -> 1110) are better left alone.
+template <int MODE, int FLAGS, typename T, typename C, bool CACHED>
+constexpr bool kLoadsFirst = CACHED && MODE != MODE_AB && FLAGS == K_COLLIDE && sizeof(T) == 4 && sizeof(C) == 4;
+
 template <int QF, int QG, int FORCE, typename T, typename C, int MODE, int FLAGS, int ROWS, bool CACHED>
 __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, T* dst, Geometry geo,
                                                        PhysConsts c, float* __restrict__ fields,
@@ -108,6 +118,7 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
     gather<QF, T, MODE, ROWS != ROWS_ANY, CACHED>(f, pop, 0, ix, geo.stride);
     if constexpr (kBatchBf16<MODE, FLAGS, T, QF>) asm volatile("" : STGV_OPERANDS_27(f) :: "memory");
     gather<QG, T, MODE, ROWS != ROWS_ANY, CACHED>(g, pop, QF, ix, geo.stride);
+    if constexpr (kLoadsFirst<MODE, FLAGS, T, C, CACHED>) __builtin_amdgcn_sched_barrier(0);
     StepMacro<C> m;
     step_macro<QF, QG, FORCE, sizeof(T) == 4>(f, g, c, m);
     if (FLAGS & (K_FIELDS | K_PARTIALS)) {
