@@ -19,12 +19,17 @@ namespace {
 
 constexpr int kShellBlocks = 1024;           // at most, a component
 constexpr int kShellThreads = 256;
-// Components that one transform and one binning launch take.  Up to 200^3 all three: the time is
-// launches (16^3 33.9 -> 16.1 us, 64^3 53.4 -> 30.1) and, above, the tail of each (128^3 191 -> 140,
-// 160^3 329 -> 260, 200^3 535 -> 496), the results the same; beyond, the three half spectra outgrow
-// the last-level cache (251^3 2489 -> 2790, 256^3 1117 -> 1062, 300^3 1857 -> 2018) and one is held.
-constexpr int kBatchUpTo = 200;
-inline int components_at_once(int n) { return n <= kBatchUpTo ? 3 : 1; }
+// Components that one transform and one binning launch take: all three up to the size where the
+// three half spectra and rocFFT's work space outgrow the last-level cache, then one.  Below, the
+// time is launches (16^3 33.9 -> 16.1 us, 64^3 53.4 -> 30.1) and the tail of each (128^3 191 -> 140,
+// 160^3 329 -> 260); the results are the same.  The line, one by one / at once: odd boxes, whose
+// rows are transformed at full length, 181^3 1100 / 1040, 199^3 1458 / 1467, 225^3 1313 / 1430;
+// even ones 216^3 667 / 595, 240^3 917 / 842, 250^3 1101 / 1170; rows of whole 64-byte pieces
+// 224^3 750 / 688, 256^3 1101 / 1048, 288^3 1559 / 1582, 320^3 2116 / 2232.
+inline int components_at_once(int n) {
+  const int up_to = n % 16 == 0 ? 256 : (n % 2 == 0 ? 240 : 181);
+  return n <= up_to ? 3 : 1;
+}
 inline int64_t half_spectrum(int n) { return (int64_t)(n / 2 + 1) * n * n; }
 inline int shell_blocks(int n) {
   const int64_t b = (half_spectrum(n) + kShellThreads - 1) / kShellThreads;
