@@ -464,6 +464,7 @@ __global__ __launch_bounds__(kGradThreads) void grad_kernel(const Packed* __rest
           lacc = row < N_OUT && node < live ? fma_c(res, res, lacc) : lacc;
         }
     lsum[lane] = lacc;
+    wave_lds_sync();
     if (lane == 0) {
       double t = 0.0;
 #pragma unroll
