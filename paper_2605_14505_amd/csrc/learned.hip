@@ -539,7 +539,12 @@ __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, fl
 
 // ---------------------------------------------------------------------------
 // normalisation: column sums of the features and their squares and of the squared targets
-// over all rows, FP64, in two stages.
+// over all rows, FP64, in two stages.  The features are taken relative to the first row, so a
+// constant column sums to exactly zero whatever the order of the sums (without, its variance was a
+// rounding residue that came out positive for about half of all constants at 262 144 rows, and
+// 1 / std of it some 1e8), and a mean far from zero costs no digits: a row is at most sqrt(rows)
+// standard deviations from the mean, so the variance loses no more than the factor `rows` of FP64's
+// 1e-16.
 //
 // One pass over the rows, HBM-bound (369 MB at 1 048 576 rows).  V rows of C columns are a
 // run of C pieces of V floats; C neighbouring threads take one piece each, so a thread's V
@@ -562,17 +567,27 @@ constexpr int inverse_mod(int V, int C) {
   return 1;
 }
 
+// What column c of the features is taken relative to: its first row, unless that is infinite or NaN.
+__device__ __forceinline__ double shift_of(const float* __restrict__ x, int c) {
+  return isfinite(x[c]) ? (double)x[c] : 0.0;
+}
+
 // Column sums of a [rows][C] table: runs [u0, u1) of V rows by this block's threads, the
-// per-thread sums left in LDS as [piece element][thread].
+// per-thread sums left in LDS as [piece element][thread].  FIRST: sums of t - shift_of and squares
+// of that, else squares of t alone.
 template <int C, int V, bool FIRST>
 __device__ __forceinline__ void column_sums(const float* __restrict__ t, int64_t u0, int64_t u1,
                                             double (*sum)[kStatsThreads], double (*sq)[kStatsThreads]) {
   using Piece = typename FloatPiece<V>::type;
   constexpr int G = kStatsThreads / C;
   const int g = threadIdx.x / C, i = threadIdx.x % C;
-  double s[V], s2[V];
+  double s[V], s2[V], shift[V];
 #pragma unroll
-  for (int j = 0; j < V; ++j) { s[j] = 0.0; s2[j] = 0.0; }
+  for (int j = 0; j < V; ++j) {
+    s[j] = 0.0;
+    s2[j] = 0.0;
+    shift[j] = FIRST ? shift_of(t, (V * i + j) % C) : 0.0;
+  }
   if (g < G) {
     const Piece* p = reinterpret_cast<const Piece*>(t);
 #pragma unroll 4
@@ -580,7 +595,7 @@ __device__ __forceinline__ void column_sums(const float* __restrict__ t, int64_t
       const Piece v = p[u * C + i];
 #pragma unroll
       for (int j = 0; j < V; ++j) {
-        const double d = (double)piece_at<V>(v, j);
+        const double d = FIRST ? (double)piece_at<V>(v, j) - shift[j] : (double)piece_at<V>(v, j);
         if (FIRST) s[j] += d;
         s2[j] = fma_c(d, d, s2[j]);
       }
@@ -624,15 +639,15 @@ __global__ __launch_bounds__(kStatsThreads) void stats_kernel(const float* __res
                         : (which == 1 ? column_total<N_IN, V>(sx2, c) : column_total<N_OUT, V>(sy2, c));
   if (b == nb - 1)
     for (int64_t r = runs * V; r < rows; ++r) {
-      const double d = which < 2 ? (double)x[r * N_IN + c] : (double)y[r * N_OUT + c];
+      const double d = which < 2 ? (double)x[r * N_IN + c] - shift_of(x, c) : (double)y[r * N_OUT + c];
       s += which == 0 ? d : d * d;
     }
   part[(which * N_IN + c) * nb + b] = s;
 }
 
 // One wavefront per column: the blocks' partial sums (contiguous per statistic) to the norm.
-__global__ __launch_bounds__(64) void norm_kernel(const double* __restrict__ part, int nblocks,
-                                                  int64_t rows, float* __restrict__ norm) {
+__global__ __launch_bounds__(64) void norm_kernel(const float* __restrict__ x, const double* __restrict__ part,
+                                                  int nblocks, int64_t rows, float* __restrict__ norm) {
   const int c = blockIdx.x, lane = threadIdx.x;
   auto total = [&](int stat) {
     double s = 0.0;
@@ -645,7 +660,7 @@ __global__ __launch_bounds__(64) void norm_kernel(const double* __restrict__ par
     const double mean = s / rows;
     const double var = s2 / rows - mean * mean;
     if (lane == 63) {
-      norm[c] = (float)mean;
+      norm[c] = (float)(shift_of(x, c) + mean);
       norm[N_IN + c] = var > 1e-300 ? (float)(1.0 / sqrt(var)) : 0.f;
     }
   } else {
@@ -916,7 +931,7 @@ hipError_t mlp_launch_norm(const float* x, const float* y, int64_t rows, double*
     hipLaunchKernelGGL(mlp::stats_kernel<1>, dim3(nblocks), dim3(mlp::kStatsThreads), 0, st, x, y, rows, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mlp::norm_kernel, dim3(mlp::N_IN + mlp::N_OUT), dim3(64), 0, st, part, nblocks, rows, norm);
+  hipLaunchKernelGGL(mlp::norm_kernel, dim3(mlp::N_IN + mlp::N_OUT), dim3(64), 0, st, x, part, nblocks, rows, norm);
   return hipGetLastError();
 }
 

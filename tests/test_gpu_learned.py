@@ -266,6 +266,23 @@ def test_normalisation_edges_match_oracle(rows, start):
     np.testing.assert_allclose(got[94:], ref[2], rtol=1e-6)
 
 
+@pytest.mark.parametrize("start", [0, 1])
+@pytest.mark.parametrize("rows", [5, 4096, 20000, 262144])
+def test_normalisation_of_constant_columns(rows, start):
+    # every column constant: its own value as the mean, 0 as 1 / std, whatever the row count
+    rng = np.random.default_rng(rows + start)
+    c = rng.uniform(0.1, 2, 47).astype(np.float32) * rng.choice([-1, 1], 47).astype(np.float32)
+    cy = rng.uniform(0.1, 2, 41).astype(np.float32)
+    x, y = (torch.from_numpy(v).to(DEV).repeat(rows + start, 1)[start:] for v in (c, cy))
+    norm = torch.empty(135, dtype=torch.float32, device=DEV)
+    work = torch.empty(stgv.lbm_mlp_norm_work_bytes(), dtype=torch.uint8, device=DEV)
+    stgv.lbm_mlp_norm(x, y, rows, norm, work, stream())
+    got = norm.cpu().numpy()
+    assert np.array_equal(got[:47], c)
+    assert np.all(got[47:94] == 0.0), np.flatnonzero(got[47:94])
+    np.testing.assert_allclose(got[94:], cy, rtol=1e-6)
+
+
 @pytest.mark.parametrize("batch", [1, 63, 64, 65, 1100])
 def test_gradient_edges_match_oracle(batch):
     # batches around the 64 samples of a block, and more blocks than a reduction slice
