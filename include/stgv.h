@@ -299,7 +299,9 @@ int lbm_spectrum_work_bytes(int32_t n, size_t* bytes);
 /* Kinetic-energy spectrum of the current state, E(k) = sum over wavevectors with
  * round(|k|) = k of |u_hat|^2 / 2, u_hat = FFT(u / U) / n^3 (u of Eq. (7)), so that
  * sum_k E(k) = E_k.  shells_dev: lbm_spectrum_shells(n) FP64 values (device); work:
- * lbm_spectrum_work_bytes bytes (device, 256-byte aligned), both caller-owned.
+ * lbm_spectrum_work_bytes bytes (device, 256-byte aligned), both caller-owned.  Where
+ * those hold the half spectra of three components, a buffer with room for one (two
+ * times n^2 (n / 2 + 1) 8 bytes less) does too, with one transform at a time.
  * Queued on the context's stream (the result is valid after it synchronises). */
 int lbm_ke_spectrum(lbm_ctx* ctx, void* work_dev, size_t work_bytes, double* shells_dev);
 

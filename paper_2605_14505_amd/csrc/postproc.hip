@@ -94,10 +94,10 @@ struct Plan {
   size_t work = 0;
 };
 std::mutex g_mutex;
-std::map<int, Plan> g_plans;
+std::map<std::pair<int, int>, Plan> g_plans;      // (n, components at once)
 bool g_setup = false;
 
-const Plan* get_plan(int n, char* err) {
+const Plan* get_plan(int n, int at_once, char* err) {
   std::lock_guard<std::mutex> lock(g_mutex);
   if (!g_setup) {
     if (rocfft_setup() != rocfft_status_success) {
@@ -106,12 +106,12 @@ const Plan* get_plan(int n, char* err) {
     }
     g_setup = true;
   }
-  auto it = g_plans.find(n);
+  auto it = g_plans.find({n, at_once});
   if (it != g_plans.end()) return &it->second;
   Plan p;
   const size_t lengths[3] = {(size_t)n, (size_t)n, (size_t)n};
   if (rocfft_plan_create(&p.plan, rocfft_placement_notinplace, rocfft_transform_type_real_forward,
-                         rocfft_precision_single, 3, lengths, components_at_once(n), nullptr) != rocfft_status_success) {
+                         rocfft_precision_single, 3, lengths, at_once, nullptr) != rocfft_status_success) {
     snprintf(err, 512, "rocfft_plan_create failed for %d^3", n);
     return nullptr;
   }
@@ -120,16 +120,16 @@ const Plan* get_plan(int n, char* err) {
     rocfft_plan_destroy(p.plan);
     return nullptr;
   }
-  return &(g_plans[n] = p);
+  return &(g_plans[{n, at_once}] = p);
 }
 
 struct Layout {
   size_t complex_off, partial_off, fft_off, total;
 };
 
-Layout layout(int n, size_t fft_work) {
+Layout layout(int n, int at_once, size_t fft_work) {
   Layout l;
-  const size_t cbytes = (size_t)half_spectrum(n) * components_at_once(n) * sizeof(float2);
+  const size_t cbytes = (size_t)half_spectrum(n) * at_once * sizeof(float2);
   l.complex_off = 0;
   l.partial_off = align256(cbytes);
   l.fft_off = l.partial_off + align256((size_t)3 * shell_blocks(n) * spectrum_shells(n) * sizeof(double));
@@ -142,15 +142,23 @@ Layout layout(int n, size_t fft_work) {
 int spectrum_shells(int n) { return (int)std::floor(std::sqrt(3.0) * n / 2.0 + 0.5) + 1; }
 
 size_t spectrum_extra_bytes(int n, char* err) {
-  const Plan* p = get_plan(n, err);
-  return p ? layout(n, p->work).total : 0;
+  const int at_once = components_at_once(n);
+  const Plan* p = get_plan(n, at_once, err);
+  return p ? layout(n, at_once, p->work).total : 0;
 }
 
 hipError_t spectrum_launch(const float* u, int n, double u0, void* work,
                            size_t work_bytes, double* out, hipStream_t st, char* err) {
-  const Plan* p = get_plan(n, err);
+  int at_once = components_at_once(n);
+  const Plan* p = get_plan(n, at_once, err);
   if (!p) return hipErrorUnknown;
-  const Layout l = layout(n, p->work);
+  Layout l = layout(n, at_once, p->work);
+  if (at_once > 1 && work_bytes < l.total) {      // room for one component's half spectrum may do
+    at_once = 1;
+    p = get_plan(n, at_once, err);
+    if (!p) return hipErrorUnknown;
+    l = layout(n, at_once, p->work);
+  }
   if (work_bytes < l.total) {
     snprintf(err, 512, "spectrum work buffer has %zu bytes, needs %zu", work_bytes, l.total);
     return hipErrorInvalidValue;
@@ -169,7 +177,7 @@ hipError_t spectrum_launch(const float* u, int n, double u0, void* work,
     ok = rocfft_execution_info_set_work_buffer(info, base + l.fft_off, p->work) == rocfft_status_success;
   const int nshell = spectrum_shells(n);
   const double scale = 1.0 / (2.0 * std::pow((double)n, 6.0) * u0 * u0);
-  const int at_once = components_at_once(n), blocks = shell_blocks(n);
+  const int blocks = shell_blocks(n);
   for (int c = 0; ok && c < 3; c += at_once) {
     void* in[1] = {const_cast<float*>(u + c * (int64_t)n * n * n)};
     void* outp[1] = {cbuf};
