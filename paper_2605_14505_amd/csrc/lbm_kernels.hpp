@@ -34,12 +34,11 @@ constexpr int step_min_blocks() {
 // and every wavefront's access is one contiguous run.  Against x-y block shapes (128 x 2 for
 // 90^3 and 100^3, 32 x 8 for 96^3 and 160^3), mean step in us: 90^3 FP16 27 x 7 35.6 -> 23.8,
 // FP32 27 x 19 72.2 -> 50.1; 100^3 FP32 91.7 -> 67.5; 160^3 FP16 215 -> 145; 96^3 FP32
-// 60.2 -> 58.5; boxes whose rows are whole wavefronts are unchanged within 1 %.  The steps shifted
-// along x take their blocks in the
-// XCD-aware order of block_at.
+// 60.2 -> 58.5; boxes whose rows are whole wavefronts are unchanged within 1 %.  Blocks are
+// taken in the XCD-aware order of block_at.
 template <int MODE>
 __device__ __forceinline__ uint32_t node_block(const Geometry& geo) {
-  return MODE != MODE_EVEN ? block_at(blockIdx.x, gridDim.x, geo) : blockIdx.x;
+  return block_at(blockIdx.x, gridDim.x, geo, MODE != MODE_EVEN);
 }
 template <int MODE>
 __device__ __forceinline__ uint32_t node_of(const Geometry& geo) {

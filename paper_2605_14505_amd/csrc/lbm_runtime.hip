@@ -544,7 +544,7 @@ int lbm_init_tgv(const lbm_params* p, void* pop_dev, size_t pop_bytes, void* wor
   c->c.G = d.G;
   c->c.beta = d.beta;
   c->c.g_over_n = p->g_over_n;
-  c->geo = make_geometry(p->n, s.stride);
+  c->geo = make_geometry(p->n, s.stride, near_state((int64_t)s.pop_bytes));
   c->pop = (char*)pop_dev;
   c->pop_b = p->layout == LBM_LAYOUT_AB
                  ? (char*)pop_dev + (size_t)(p->q_f + p->q_g) * s.stride * s.elem
