@@ -159,17 +159,20 @@ hipError_t launch_stream<STGV_T>(int qf, int qg, int mode, bool cached, hipStrea
   return hipErrorInvalidValue;
 }
 
-// Conversion in natural order: four values at a time where every array of both sides starts on
-// four of them and holds a whole number (n even makes n^3 a multiple of 8; the natural side is
-// the caller's buffer), else single values.
+// Conversion in natural order (lbm_convert_kernel): four values at a time where every array of the
+// natural side starts on 16 bytes and holds a multiple of four values (n even makes n^3 a multiple of
+// 8).  Elsewhere four of a 2-byte type all the same, single values of FP32.  Read-back / load in us,
+// one thread per node, single values, four at a time: FP16 101^3 75 / 70, 97 / 86, 57 / 60, 251^3
+// 1290 / 1230, 1310 / 1110, 757 / 718; FP32 225^3 1115 / 1141, 714 / 675, 798 / 719, 251^3 1678 /
+// 1342, 991 / 931, 1096 / 961.
 template <bool LOAD>
 static hipError_t convert(int arrays, hipStream_t st, STGV_T* pop, Geometry geo, float* natural) {
-  constexpr int V = 4;
-  const bool wide = geo.n % 2 == 0 && (uintptr_t)natural % 16 == 0;
-  const unsigned chunk = kNodeBlock * kConvertUnroll * (wide ? V : 1);
+  constexpr int V = 4, VU = sizeof(STGV_T) == 4 ? 1 : V;
+  const bool lines = geo.n % 2 == 0 && (uintptr_t)natural % 16 == 0;
+  const unsigned chunk = kNodeBlock * kConvertUnroll * (lines ? V : VU);
   const dim3 grid((geo.n3 + chunk - 1) / chunk, (unsigned)arrays), block(kNodeBlock);
-  if (wide) hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, V, LOAD>), grid, block, 0, st, pop, geo, natural);
-  else hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, 1, LOAD>), grid, block, 0, st, pop, geo, natural);
+  if (lines) hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, V, LOAD, true>), grid, block, 0, st, pop, geo, natural);
+  else hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, VU, LOAD, false>), grid, block, 0, st, pop, geo, natural);
   return hipGetLastError();
 }
 

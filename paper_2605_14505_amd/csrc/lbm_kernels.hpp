@@ -311,55 +311,74 @@ __global__ __launch_bounds__(kNodeBlock) void lbm_init_tgv_kernel(T* pop, Geomet
 // ---------------------------------------------------------------------------
 // Where the array is in natural order (an even number of steps, A-B, a load) a conversion is a
 // copy of each population array by itself: block (b, q) converts a contiguous chunk of array
-// q, four values at a time (contiguous over a wavefront on both sides: eight of a 2-byte type
-// left gaps between the 16-byte stores, 512^3 FP16 read-back 8.81 ms) or one at a time, all
-// loads ahead of the stores.  HBM-bound, 5.7-5.9 TB/s: 512^3 FP16 read-back 7.86 -> 6.26 ms and
+// q, V values at a time (contiguous over a wavefront on both sides: eight of a 2-byte type
+// left gaps between the 16-byte stores, 512^3 FP16 read-back 8.81 ms), all loads ahead of the
+// stores.  The population arrays start on whole lines, the natural ones on any float (odd boxes,
+// the caller's buffer); global memory takes four floats there all the same.  ALIGNED: the natural
+// arrays start on 16 bytes; their stores bypass the caches only then.
+// HBM-bound, 5.7-5.9 TB/s: 512^3 FP16 read-back 7.86 -> 6.26 ms and
 // load 7.33 -> 6.26, 256^3 FP32 1171 -> 1081 us and 1144 -> 1088, against one thread per node with
 // 46 streams open.
 constexpr int kConvertUnroll = 4;
 
 template <typename T, int V> struct Packet { T v[V]; };
-template <int BYTES> struct PacketWord { typedef uint32_t type __attribute__((ext_vector_type(BYTES / 4))); };
-template <int V, typename T>
+template <int BYTES, int ALIGN> struct PacketWord {
+  typedef uint32_t type __attribute__((ext_vector_type(BYTES / 4), aligned(ALIGN)));
+};
+// ALIGN: what the address is a multiple of (4 for single values of any type).
+template <int V, int ALIGN, typename T>
 __device__ __forceinline__ Packet<T, V> load_packet(const T* p) {
   if constexpr (V == 1) return Packet<T, V>{{raw_load<true>(p)}};
-  else return __builtin_bit_cast(Packet<T, V>, __builtin_nontemporal_load((const typename PacketWord<sizeof(T) * V>::type*)p));
+  else return __builtin_bit_cast(Packet<T, V>, __builtin_nontemporal_load((const typename PacketWord<sizeof(T) * V, ALIGN>::type*)p));
 }
-template <int V, typename T>
+template <int V, int ALIGN, bool NT, typename T>
 __device__ __forceinline__ void store_packet(T* p, const Packet<T, V>& v) {
   if constexpr (V == 1) {
-    put_rounded(p, v.v[0]);
+    raw_store<NT>(p, v.v[0]);
   } else {
-    using Word = typename PacketWord<sizeof(T) * V>::type;
-    __builtin_nontemporal_store(__builtin_bit_cast(Word, v), (Word*)p);
+    using Word = typename PacketWord<sizeof(T) * V, ALIGN>::type;
+    put<NT>((Word*)p, __builtin_bit_cast(Word, v));
   }
 }
+template <typename T, int V, bool LOAD, bool NT>
+__device__ __forceinline__ void convert_store(T* a, float* b, Packet<T, V> t, Packet<float, V> f) {
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    if constexpr (LOAD) t.v[j] = rounded((const T*)nullptr, f.v[j]);
+    else f.v[j] = load_as<float>(&t.v[j]);
+  }
+  if constexpr (LOAD) store_packet<V, V * sizeof(T), true>(a, t);
+  else store_packet<V, 4, NT>(b, f);
+}
 
-template <typename T, int V, bool LOAD>
+template <typename T, int V, bool LOAD, bool ALIGNED>
 __global__ __launch_bounds__(kNodeBlock) void lbm_convert_kernel(T* pop, Geometry geo, float* natural) {
+  constexpr bool NT = ALIGNED || V == 1;
   T* const a = pop + (int64_t)blockIdx.y * geo.stride;
   float* const b = natural + (int64_t)blockIdx.y * geo.n3;
-  const uint32_t e0 = (blockIdx.x * (kNodeBlock * kConvertUnroll) + threadIdx.x) * V;
+  const uint32_t e0 = (blockIdx.x * (kNodeBlock * kConvertUnroll) + threadIdx.x) * V, rest = geo.n3 % V, whole = geo.n3 - rest;
   Packet<T, V> t[kConvertUnroll];
   Packet<float, V> f[kConvertUnroll];
 #pragma unroll
   for (int k = 0; k < kConvertUnroll; ++k) {
     const uint32_t e = e0 + k * (kNodeBlock * V);
-    if (e >= geo.n3) continue;
-    if constexpr (LOAD) f[k] = load_packet<V>(b + e);
-    else t[k] = load_packet<V>(a + e);
+    if (e >= whole) continue;
+    if constexpr (LOAD) f[k] = load_packet<V, 4>(b + e);
+    else t[k] = load_packet<V, V * sizeof(T)>(a + e);
   }
 #pragma unroll
   for (int k = 0; k < kConvertUnroll; ++k) {
     const uint32_t e = e0 + k * (kNodeBlock * V);
-    if (e >= geo.n3) continue;
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      if constexpr (LOAD) t[k].v[j] = rounded((const T*)nullptr, f[k].v[j]);
-      else f[k].v[j] = load_as<float>(&t[k].v[j]);
-    }
-    if constexpr (LOAD) store_packet<V>(a + e, t[k]);
-    else store_packet<V>(b + e, f[k]);
+    if (e >= whole) continue;
+    convert_store<T, V, LOAD, NT>(a + e, b + e, t[k], f[k]);
+  }
+  if (V > 1 && rest && blockIdx.x == 0 && threadIdx.x < rest) {       // the last values of an odd box
+    const uint32_t e = whole + threadIdx.x;
+    Packet<T, 1> t1;
+    Packet<float, 1> f1;
+    if constexpr (LOAD) f1 = load_packet<1, 4>(b + e);
+    else t1 = load_packet<1, 4>(a + e);
+    convert_store<T, 1, LOAD, NT>(a + e, b + e, t1, f1);
   }
 }
 

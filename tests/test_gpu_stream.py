@@ -135,3 +135,21 @@ def test_load_and_read_back_round_trip(n, start, storage):
         assert np.array_equal(got[start:start + dev.size].reshape(ref.shape), ref)
         assert np.all(got[:start] == 7.0) and np.all(got[start + dev.size:] == 7.0)
     sim.close()
+
+
+@pytest.mark.parametrize("storage", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("n,start", [(5, 0), (33, 0), (33, 1), (35, 0)])
+def test_round_trip_of_odd_boxes(n, start, storage):
+    # arrays of the caller's that start on any float, one and three values past the last four, and
+    # more than one block an array
+    dev = torch.from_numpy(uniform_deviations(46, n, 1e-2, seed=n)).to("cuda:0")
+    ref = {"fp32": dev, "fp16": dev.half().float(), "bf16": dev.bfloat16().float()}[storage]
+    sim = make_sim(n, 27, 19, storage)
+    src = torch.zeros(start + dev.numel(), dtype=torch.float32, device="cuda:0")
+    src[start:] = dev.reshape(-1)
+    out = torch.full((start + dev.numel() + 5,), 7.0, dtype=torch.float32, device="cuda:0")
+    stgv.lbm_load_populations(sim.ctx, src[start:], 0)
+    stgv.lbm_read_populations(sim.ctx, out[start:])
+    assert torch.equal(out[start:start + dev.numel()].reshape(ref.shape), ref)
+    assert torch.all(out[:start] == 7.0) and torch.all(out[start + dev.numel():] == 7.0)
+    sim.close()
