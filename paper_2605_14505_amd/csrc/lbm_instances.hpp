@@ -179,9 +179,12 @@ static hipError_t convert(int arrays, hipStream_t st, STGV_T* pop, Geometry geo,
 template <>
 hipError_t launch_canon<STGV_T>(int qf, int qg, int mode, hipStream_t st, const STGV_T* pop, Geometry geo, float* out) {
   if (mode != MODE_ODD) return convert<false>(qf + qg, st, const_cast<STGV_T*>(pop), geo, out);
+  const bool lines = geo.n3 % 32 == 0 && (uintptr_t)out % 128 == 0;
+  const dim3 grid(node_blocks(geo.n)), block(node_threads(geo.n));
 #define STGV_CANON(A, B) \
   if (qf == A && qg == B) { \
-    hipLaunchKernelGGL((lbm_canon_odd_kernel<A, B, STGV_T>), dim3(node_blocks(geo.n)), dim3(node_threads(geo.n)), 0, st, pop, geo, out); \
+    if (lines) hipLaunchKernelGGL((lbm_canon_odd_kernel<A, B, STGV_T, true>), grid, block, 0, st, pop, geo, out); \
+    else hipLaunchKernelGGL((lbm_canon_odd_kernel<A, B, STGV_T, false>), grid, block, 0, st, pop, geo, out); \
     return hipGetLastError(); }
   STGV_FOR_EACH_PAIR(STGV_CANON)
 #undef STGV_CANON

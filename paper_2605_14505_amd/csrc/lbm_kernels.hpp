@@ -382,11 +382,15 @@ __global__ __launch_bounds__(kNodeBlock) void lbm_convert_kernel(T* pop, Geometr
   }
 }
 
-// Read-back of the odd AA layout: one thread per node, x-shifted loads.
-template <int QF, int QG, typename T>
+// Read-back of the odd AA layout: one thread per node, x-shifted loads.  The blocks are renumbered as
+// in the odd step, and the stores bypass the caches only where every natural array starts on a whole
+// line (LINES).  In us, x-y blocks with cached stores / linear order in dispatch order with stores
+// that bypass / this: FP16 81^3 39 / 45 / 34, 90^3 45 / 56 / 40, 225^3 773 / 670-877 / 568; FP32 127^3
+// 178 / 202 / 170, 251^3 1285 / 1495 / 1240; with whole lines, cached stores / this, FP16 128^3 126 / 81.
+template <int QF, int QG, typename T, bool LINES>
 __global__ __launch_bounds__(kNodeBlock) void lbm_canon_odd_kernel(const T* pop, Geometry geo,
                                                                    float* __restrict__ out) {
-  const uint32_t node = node_of<MODE_EVEN>(geo);
+  const uint32_t node = node_of<MODE_ODD>(geo);
   if (node >= geo.n3) return;
   const NodeIndex ix = index_of<MODE_ODD, ROWS_ANY>(node, geo);
   const int64_t n3 = geo.n3;
@@ -394,9 +398,9 @@ __global__ __launch_bounds__(kNodeBlock) void lbm_canon_odd_kernel(const T* pop,
   gather<QF, T, MODE_ODD>(f, pop, 0, ix, geo.stride);
   gather<QG, T, MODE_ODD>(g, pop, QF, ix, geo.stride);
 #pragma unroll
-  for (int i = 0; i < QF; ++i) put(out + i * n3 + node, f[i]);
+  for (int i = 0; i < QF; ++i) put<LINES>(out + i * n3 + node, f[i]);
 #pragma unroll
-  for (int j = 0; j < QG; ++j) put(out + (QF + j) * n3 + node, g[j]);
+  for (int j = 0; j < QG; ++j) put<LINES>(out + (QF + j) * n3 + node, g[j]);
 }
 
 }  // namespace stgv
