@@ -168,11 +168,15 @@ hipError_t launch_stream<STGV_T>(int qf, int qg, int mode, bool cached, hipStrea
 template <bool LOAD>
 static hipError_t convert(int arrays, hipStream_t st, STGV_T* pop, Geometry geo, float* natural) {
   constexpr int V = 4, VU = sizeof(STGV_T) == 4 ? 1 : V;
-  const bool lines = geo.n % 2 == 0 && (uintptr_t)natural % 16 == 0;
-  const unsigned chunk = kNodeBlock * kConvertUnroll * (lines ? V : VU);
+  const bool aligned = geo.n % 2 == 0 && (uintptr_t)natural % 16 == 0;
+  const bool cached = cached_state((size_t)arrays * geo.n3 * (LOAD ? sizeof(float) : sizeof(STGV_T)));
+  const unsigned chunk = kNodeBlock * kConvertUnroll * (aligned ? V : VU);
   const dim3 grid((geo.n3 + chunk - 1) / chunk, (unsigned)arrays), block(kNodeBlock);
-  if (lines) hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, V, LOAD, true>), grid, block, 0, st, pop, geo, natural);
-  else hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, VU, LOAD, false>), grid, block, 0, st, pop, geo, natural);
+#define STGV_CONVERT(W, ALIGNED, CACHED) \
+  hipLaunchKernelGGL((lbm_convert_kernel<STGV_T, W, LOAD, ALIGNED, CACHED>), grid, block, 0, st, pop, geo, natural)
+  if (aligned) { if (cached) STGV_CONVERT(V, true, true); else STGV_CONVERT(V, true, false); }
+  else { if (cached) STGV_CONVERT(VU, false, true); else STGV_CONVERT(VU, false, false); }
+#undef STGV_CONVERT
   return hipGetLastError();
 }
 

@@ -315,7 +315,10 @@ __global__ __launch_bounds__(kNodeBlock) void lbm_init_tgv_kernel(T* pop, Geomet
 // left gaps between the 16-byte stores, 512^3 FP16 read-back 8.81 ms), all loads ahead of the
 // stores.  The population arrays start on whole lines, the natural ones on any float (odd boxes,
 // the caller's buffer); global memory takes four floats there all the same.  ALIGNED: the natural
-// arrays start on 16 bytes; their stores bypass the caches only then.
+// arrays start on 16 bytes; their stores bypass the caches only then.  CACHED: the source may still be
+// in the last-level cache (cached_state of its size) and is read through the caches: load and read-back
+// in us, bypassing / cached, 64^3 FP32 27.8 / 24.6 and 29.7 / 24.4, 101^3 FP16 60 / 51 and 54 / 53; a source
+// of 326 MB (121^3 FP16 load) 91 / 97.
 // HBM-bound, 5.7-5.9 TB/s: 512^3 FP16 read-back 7.86 -> 6.26 ms and
 // load 7.33 -> 6.26, 256^3 FP32 1171 -> 1081 us and 1144 -> 1088, against one thread per node with
 // 46 streams open.
@@ -325,11 +328,11 @@ template <typename T, int V> struct Packet { T v[V]; };
 template <int BYTES, int ALIGN> struct PacketWord {
   typedef uint32_t type __attribute__((ext_vector_type(BYTES / 4), aligned(ALIGN)));
 };
-// ALIGN: what the address is a multiple of (4 for single values of any type).
-template <int V, int ALIGN, typename T>
+// ALIGN: what the address is a multiple of (4 for single values of any type).  NT: past the caches.
+template <int V, int ALIGN, bool NT, typename T>
 __device__ __forceinline__ Packet<T, V> load_packet(const T* p) {
-  if constexpr (V == 1) return Packet<T, V>{{raw_load<true>(p)}};
-  else return __builtin_bit_cast(Packet<T, V>, __builtin_nontemporal_load((const typename PacketWord<sizeof(T) * V, ALIGN>::type*)p));
+  if constexpr (V == 1) return Packet<T, V>{{raw_load<NT>(p)}};
+  else return __builtin_bit_cast(Packet<T, V>, get<NT>((const typename PacketWord<sizeof(T) * V, ALIGN>::type*)p));
 }
 template <int V, int ALIGN, bool NT, typename T>
 __device__ __forceinline__ void store_packet(T* p, const Packet<T, V>& v) {
@@ -340,45 +343,49 @@ __device__ __forceinline__ void store_packet(T* p, const Packet<T, V>& v) {
     put<NT>((Word*)p, __builtin_bit_cast(Word, v));
   }
 }
-template <typename T, int V, bool LOAD, bool NT>
-__device__ __forceinline__ void convert_store(T* a, float* b, Packet<T, V> t, Packet<float, V> f) {
+template <typename T, int V>
+__device__ __forceinline__ Packet<float, V> widened(const Packet<T, V>& t) {
+  Packet<float, V> f;
 #pragma unroll
-  for (int j = 0; j < V; ++j) {
-    if constexpr (LOAD) t.v[j] = rounded((const T*)nullptr, f.v[j]);
-    else f.v[j] = load_as<float>(&t.v[j]);
-  }
-  if constexpr (LOAD) store_packet<V, V * sizeof(T), true>(a, t);
-  else store_packet<V, 4, NT>(b, f);
+  for (int j = 0; j < V; ++j) f.v[j] = load_as<float>(&t.v[j]);
+  return f;
+}
+template <typename T, int V>
+__device__ __forceinline__ Packet<T, V> narrowed(const Packet<float, V>& f) {
+  Packet<T, V> t;
+#pragma unroll
+  for (int j = 0; j < V; ++j) t.v[j] = rounded((const T*)nullptr, f.v[j]);
+  return t;
 }
 
-template <typename T, int V, bool LOAD, bool ALIGNED>
+template <typename T, int V, bool LOAD, bool ALIGNED, bool CACHED>
 __global__ __launch_bounds__(kNodeBlock) void lbm_convert_kernel(T* pop, Geometry geo, float* natural) {
   constexpr bool NT = ALIGNED || V == 1;
   T* const a = pop + (int64_t)blockIdx.y * geo.stride;
   float* const b = natural + (int64_t)blockIdx.y * geo.n3;
   const uint32_t e0 = (blockIdx.x * (kNodeBlock * kConvertUnroll) + threadIdx.x) * V, rest = geo.n3 % V, whole = geo.n3 - rest;
-  Packet<T, V> t[kConvertUnroll];
   Packet<float, V> f[kConvertUnroll];
 #pragma unroll
   for (int k = 0; k < kConvertUnroll; ++k) {
     const uint32_t e = e0 + k * (kNodeBlock * V);
     if (e >= whole) continue;
-    if constexpr (LOAD) f[k] = load_packet<V, 4>(b + e);
-    else t[k] = load_packet<V, V * sizeof(T)>(a + e);
+    if constexpr (LOAD) f[k] = load_packet<V, 4, !CACHED>(b + e);
+    else f[k] = widened(load_packet<V, V * sizeof(T), !CACHED>(a + e));
+    // each packet of a 2-byte read-back is waited for here, which measures better than all four loads
+    // in flight: 256^3 FP16 787 -> 743 us, BF16 780 -> 736, 250^3 796 -> 737 and 789 -> 737
+    if constexpr (!LOAD && sizeof(T) == 2) asm volatile("" : "+v"(f[k].v[0]));
   }
 #pragma unroll
   for (int k = 0; k < kConvertUnroll; ++k) {
     const uint32_t e = e0 + k * (kNodeBlock * V);
     if (e >= whole) continue;
-    convert_store<T, V, LOAD, NT>(a + e, b + e, t[k], f[k]);
+    if constexpr (LOAD) store_packet<V, V * sizeof(T), true>(a + e, narrowed<T>(f[k]));
+    else store_packet<V, 4, NT>(b + e, f[k]);
   }
   if (V > 1 && rest && blockIdx.x == 0 && threadIdx.x < rest) {       // the last values of an odd box
     const uint32_t e = whole + threadIdx.x;
-    Packet<T, 1> t1;
-    Packet<float, 1> f1;
-    if constexpr (LOAD) f1 = load_packet<1, 4>(b + e);
-    else t1 = load_packet<1, 4>(a + e);
-    convert_store<T, 1, LOAD, NT>(a + e, b + e, t1, f1);
+    if constexpr (LOAD) store_packet<1, 4, true>(a + e, narrowed<T>(load_packet<1, 4, !CACHED>(b + e)));
+    else store_packet<1, 4, NT>(b + e, widened(load_packet<1, 4, !CACHED>(a + e)));
   }
 }
 
