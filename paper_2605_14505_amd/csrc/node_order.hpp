@@ -47,7 +47,7 @@ constexpr Geometry make_geometry(int n, int64_t stride, bool near = false) {
   while (blk > 1 && rows % 2 == 0) { rows /= 2; blk /= 2; }
   g.xcd_group = rows < 8 ? rows : 8;
   const uint32_t blocks = (g.n3 + node_threads(n) - 1) / node_threads(n);
-  if (near && g.xcd_group > 1) {
+  if (near) {
     g.slab = blocks / 8 << 4 | blocks % 8 << 1 | 1;
     g.xcd_group = 1;
   }
@@ -70,12 +70,13 @@ constexpr uint32_t over_n(uint32_t i, const Geometry& geo) {
 // A small state (near_state) is another matter: there a step finds what the step before left in its
 // XCD's L2, if the same XCD wrote it.  Renumbered in the shifted steps alone, a node moved to
 // another XCD every step (19 x 7 FP32 48^3 6.3 -> 9.4 us a step against blocks of 64 x 4 nodes in
-// dispatch order).  So where rows are no whole blocks, every step of a small state gives XCD k the
-// k-th slab of consecutive blocks, whose inner neighbours it owns too.  Mean step in us, 64 x 4
-// blocks / renumbered shifted steps / slabs: 27 x 19 FP32 36^3 7.7 / 8.8 / 6.0, 48^3 11.2 / 11.3 /
-// 7.9; FP16 52^3 9.9 / 11.0 / 7.1, 80^3 (47 MB) 28.1 / 17.8 / 16.4; 19 x 7 FP32 40^3 5.3 / 6.9 /
-// 4.5, 48^3 6.3 / 9.4 / 5.6.  Beyond 64 MB, renumbered / slabs: 27 x 19 FP32 72^3 22.4 / 22.2,
-// 19 x 7 88^3 23.1 / 23.1, 27 x 7 96^3 (120 MB) 37.1 / 37.6.
+// dispatch order).  So every step of a small state gives XCD k the k-th slab of consecutive blocks,
+// whose inner neighbours it owns too.  Mean step in us, 64 x 4 blocks / renumbered shifted steps /
+// slabs: 27 x 19 FP32 36^3 7.7 / 8.8 / 6.0, 48^3 11.2 / 11.3 / 7.9; FP16 52^3 9.9 / 11.0 / 7.1, 80^3
+// (47 MB) 28.1 / 17.8 / 16.4; 19 x 7 FP32 40^3 5.3 / 6.9 / 4.5, 48^3 6.3 / 9.4 / 5.6; where rows are
+// whole blocks, which are not renumbered, 27 x 19 FP32 64^3 16.0 / 15.6 / 14.7, 7 x 27 FP16 64^3 7.6 /
+// 8.0 / 7.3, FP64 arithmetic 64^3 19.5 / 19.8 / 19.3, 32^3 6.5 / 5.2 / 5.0.  Beyond 64 MB, renumbered /
+// slabs: 27 x 19 FP32 72^3 22.4 / 22.2, 19 x 7 88^3 23.1 / 23.1, 27 x 7 96^3 (120 MB) 37.1 / 37.6.
 constexpr uint32_t block_at(uint32_t b, uint32_t blocks, const Geometry& geo, bool shifted = true) {
   // without a branch, so that its constants come with the kernel's other scalar loads: a wait more
   // costs 0.2 us of a 4 us step
