@@ -52,7 +52,8 @@ hipError_t step_mode(int mode, bool diag, hipStream_t st, T* pop, T* dst, Geomet
     if (rows == ROWS_LINES) STGV_GO(MODE_ODD, STEP, ROWS_LINES);
   }
 #undef STGV_GO
-  return go_step<QF, QG, FORCE, T, MODE_ODD, STEP, ROWS_ANY, true>(st, pop, dst, geo, c, fields, partials);
+  // ragged rows go through the caches in any case; only kLoadsFirst tells large states from small
+  return go_step<QF, QG, FORCE, T, MODE_ODD, STEP, ROWS_ANY, CACHED || sizeof(T) != 4 || sizeof(STGV_C) != 4>(st, pop, dst, geo, c, fields, partials);
 }
 
 template <int QF, int QG, int FORCE, typename T>

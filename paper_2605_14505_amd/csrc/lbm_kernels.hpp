@@ -94,7 +94,8 @@ constexpr bool kBatchBf16 = MODE == MODE_EVEN && FLAGS == K_COLLIDE && std::is_s
 // batches of the even step's loads and, with Guo forcing, between single loads of the odd step's.
 // Mean step in us: 8^3 4.37 -> 4.29, 32^3 5.36 -> 5.26, 64^3 16.05 -> 15.90, 90^3 42.7 -> 42.1,
 // 27 x 27 64^3 18.98 -> 18.08.  2-byte storage (BF16 64^3 9.33 -> 9.46), the A-B push (128^3 153.3
-// -> 154.9) and larger states (192^3 464 -> 468, 250^3 1095 -> 1110) are better left alone.
+// -> 154.9) and larger states (192^3 464 -> 468, 250^3 1116 -> 1120, with Guo forcing 1091 -> 1098) are
+// better left alone.
 template <int MODE, int FLAGS, typename T, typename C, bool CACHED>
 constexpr bool kLoadsFirst = CACHED && MODE != MODE_AB && FLAGS == K_COLLIDE && sizeof(T) == 4 && sizeof(C) == 4;
 
@@ -127,8 +128,9 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
     }
     if (FLAGS & K_COLLIDE) {
       step_collide<QF, QG, FORCE, sizeof(T) == 4>(f, g, c, m);
-      scatter<QF, T, MODE, CACHED>(f, dst, 0, ix, geo.stride);
-      scatter<QG, T, MODE, CACHED>(g, dst, QF, ix, geo.stride);
+      constexpr bool cached = CACHED || (MODE == MODE_ODD && ROWS == ROWS_ANY);      // row_kind
+      scatter<QF, T, MODE, cached>(f, dst, 0, ix, geo.stride);
+      scatter<QG, T, MODE, cached>(g, dst, QF, ix, geo.stride);
     }
   }
   if (kPart) {

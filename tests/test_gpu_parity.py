@@ -395,6 +395,28 @@ def test_closed_forms_at_t0_on_gpu():
     assert r["ep"] < 1e-12
 
 
+@pytest.mark.parametrize("storage,n,forcing", [("fp32", 130, "shift"), ("fp32", 130, "guo"), ("fp32", 160, "shift"),
+                                               ("fp32", 160, "hcz"), ("fp32", 192, "shift"), ("fp16", 150, "shift"),
+                                               ("bf16", 150, "edm"), ("fp16", 192, "shift")])
+def test_aa_equals_ab_bitwise_beyond_the_last_level_cache(storage, n, forcing):
+    # states of more than 256 MB: rows of no whole lines (130 FP32, 150 2-byte), of whole lines
+    # (160 FP32) and of whole wavefronts (192); the A-B push takes one path for all three
+    kw = c1_kw(n=n, forcing=forcing, storage=storage, g_over_n=0.02)
+    aa = gpu_sim(layout="aa", **kw)
+    ab = gpu_sim(layout="ab", **kw)
+    for k in (1, 2, 3):               # ends at odd, odd, even step counts
+        aa.step(k)
+        ab.step(k)
+        assert torch.equal(aa.populations(), ab.populations()), k
+    aa.close()
+    ab.close()
+
+
+@pytest.mark.parametrize("n", [130, 160])
+def test_random_state_parity_beyond_the_last_level_cache(n):
+    _random_state_parity(n, "shift", 27, 19)
+
+
 @pytest.mark.parametrize("forcing", ["guo", "shift", "edm", "hcz"])
 def test_mass_is_conserved_to_rounding(forcing):
     # 10^4 steps.  G/N = 0.01: with G/N = 1 the weakly compressible coupling lets acoustic

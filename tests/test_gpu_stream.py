@@ -153,3 +153,10 @@ def test_round_trip_of_odd_boxes(n, start, storage):
     assert torch.equal(out[start:start + dev.numel()].reshape(ref.shape), ref)
     assert torch.all(out[:start] == 7.0) and torch.all(out[start + dev.numel():] == 7.0)
     sim.close()
+
+
+@pytest.mark.parametrize("n,storage", [(160, "fp32"), (150, "fp16"), (150, "bf16")])
+def test_free_streaming_beyond_the_last_level_cache(n, storage):
+    # states of more than 256 MB in the plain odd step: rows of whole lines but no whole wavefronts
+    # (160 FP32), rows of no whole lines in 2-byte storage (150)
+    check_free_streaming(n, 27, 19, storage, "aa", seed=n)
