@@ -693,3 +693,23 @@ def test_records_drained_in_runs_equal_records_drained_singly():
                 break
     assert [r["step"] for r in ra] == list(range(4586))
     assert ra == rb
+
+
+@pytest.mark.parametrize("storage,n", [("fp32", 130), ("fp32", 160), ("fp16", 150)])
+def test_diagnostic_steps_equal_plain_steps_beyond_the_last_level_cache(storage, n):
+    # the step with a record beside the plain one, bit for bit, and its record beside a sample of
+    # the same state: ragged rows and rows of whole lines
+    kw = c1_kw(n=n, forcing="shift", storage=storage, g_over_n=0.02)
+    a, b = gpu_sim(diag_every=1, **kw), gpu_sim(diag_every=0, **kw)
+    for k in range(4):
+        b.sample()
+        a.step(1)
+        b.step(1)
+        assert torch.equal(a.populations(), b.populations()), k
+        ra, rb = a.diagnostics()[0], b.diagnostics()[0]
+        assert ra["step"] == rb["step"] == k
+        for key in ("ek", "ep", "eps_k", "eps_p", "mass", "umax"):
+            # a handful of FP32 roundings per node (the step forms the fields with the collision)
+            assert abs(ra[key] - rb[key]) <= 2e-6 * abs(rb[key]), (k, key, ra[key], rb[key])
+    a.close()
+    b.close()
