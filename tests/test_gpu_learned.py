@@ -586,3 +586,57 @@ def test_learned_form_rejects_unsupported_boxes(n, storage):
     assert ei.value.status == stgv.LBM_EINVAL
     assert "n <= 256" in str(ei.value)
     sim.close()
+
+
+@pytest.mark.parametrize("n,tile", [(272, 16), (288, 16)])
+def test_restriction_of_split_rows_in_the_xcd_order(n, tile):
+    # n > 256 (two segments a row) with block counts that are renumbered over the XCDs, row by row (272)
+    # and in tiles of 8 x 8 rows (288)
+    test_restriction_of_a_tiled_state_matches_oracle(n, tile, "fp32")
+
+
+def test_hidden_activation_is_the_rounded_tanh():
+    # The network reduced to its activation: three inputs that add up to an FP32 argument exactly
+    # feed a hidden unit, the second layer (2^-10, where tanh is the identity in BF16) and the
+    # output (2^10) hand the unit's BF16 value through.  Arguments: every BF16 value, a dense
+    # spread, and the neighbourhoods of the arguments whose tanh lies between two BF16 values.
+    units = 15
+    w1, w2, w3 = np.zeros((64, 47)), np.zeros((64, 64)), np.zeros((41, 64))
+    for h in range(units):
+        w1[h, 3 * h:3 * h + 3] = 1.0
+        w2[h, h] = 2.0 ** -10
+        w3[h, h] = 2.0 ** 10
+    theta = L.pack(dict(W1=w1, b1=np.zeros(64), W2=w2, b2=np.zeros(64), W3=w3, b3=np.zeros(41)))
+    packed = packed_net(theta, (np.zeros(47), np.ones(47), np.ones(41)))
+    rng = np.random.default_rng(0)
+    bf16 = (np.arange(1 << 15, dtype=np.uint32) << 16).view(np.float32)
+    bf16 = bf16[(bf16 >= 2.0 ** -40) & (bf16 <= 16)]
+    e, m = np.meshgrid(np.arange(-24, 0), np.arange(128))
+    mid = (2.0 ** e * (1 + (m + 0.5) / 128)).ravel()
+    at = np.arctanh(mid).astype(np.float32)
+    near = np.concatenate([(at.view(np.int32) + k).view(np.float32) for k in range(-8, 9)])
+    spread = (2.0 ** rng.uniform(-40, 4, 500000)).astype(np.float32)
+    v = np.concatenate([bf16, near, spread, np.linspace(0, 10, 200001).astype(np.float32)])
+    v = np.concatenate([v, -v])
+    v = np.concatenate([v, np.zeros(-v.size % units, np.float32)]).reshape(-1, units)
+    t = torch.from_numpy(v).to(DEV)
+    hi = t.bfloat16().float()
+    mid = (t - hi).bfloat16().float()
+    lo = t - hi - mid
+    assert torch.equal(lo.bfloat16().float(), lo)
+    x = torch.zeros((v.shape[0], 47), dtype=torch.float32, device=DEV)
+    for k, part in enumerate((hi, mid, lo)):
+        x[:, k:3 * units:3] = part
+    y = torch.empty((v.shape[0], 41), dtype=torch.float32, device=DEV)
+    stgv.lbm_mlp_forward(packed, x, v.shape[0], y, stream())
+    got = y.cpu().numpy()[:, :units].astype(np.float64)
+    ref = np.tanh(v.astype(np.float64))
+    big = np.maximum(np.abs(got), np.abs(ref))
+    binade = 2.0 ** np.floor(np.log2(np.where(big > 0, big, 1.0)))
+    # half a BF16 spacing, and the 5 ulp that an FP32 tanh may be off
+    bound = binade * (2.0 ** -8 + 5 * 2.0 ** -23)
+    err = np.abs(got - ref)
+    other = torch.tanh(t).bfloat16().float().cpu().numpy()
+    print(f"\ntanh: {v.size} arguments, error / bound max {np.max(err / bound):.6f}, "
+          f"{int((other != got).sum())} differ from torch's tanh rounded to BF16")
+    assert np.all(err <= bound), v[err > bound][:5]
