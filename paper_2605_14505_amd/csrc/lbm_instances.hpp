@@ -43,8 +43,8 @@ hipError_t step_mode(int mode, bool diag, hipStream_t st, T* pop, T* dst, Geomet
       const LaunchShape sh = ring_launch(geo.n);
       const size_t lds = ring_step_lds(sizeof(T), (size_t)(x_moving<QF>() + x_moving<QG>()) * 256 * sizeof(T));
       if (whole)
-        hipLaunchKernelGGL((lbm_step_ring_kernel<QF, QG, FORCE, T, STGV_C, false, CACHED>), sh.grid, sh.block, lds, st,
-                           pop, geo, c);
+        hipLaunchKernelGGL((lbm_step_ring_kernel<QF, QG, FORCE, T, STGV_C, false, CACHED && sizeof(T) != 4>), sh.grid,
+                           sh.block, lds, st, pop, geo, c);
       else
         hipLaunchKernelGGL((lbm_step_ring_kernel<QF, QG, FORCE, T, STGV_C, true, false>), sh.grid, sh.block, lds, st,
                            pop, geo, c);
@@ -138,22 +138,34 @@ static hipError_t stream_pair(int mode, hipStream_t st, STGV_T* pop, STGV_T* dst
     if (mode == MODE_ODD && (whole || ring_part(geo.n))) {
       const LaunchShape sh = ring_launch(geo.n);
       const size_t lds = ring_step_lds(sizeof(STGV_T), (size_t)(x_moving<A>() + x_moving<B>()) * 256 * sizeof(STGV_T));
-      if (whole) hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, false, CACHED>), sh.grid, sh.block, lds, st, pop, geo);
+      if (whole) hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, false, CACHED && sizeof(STGV_T) != 4>), sh.grid, sh.block, lds, st, pop, geo);
       else hipLaunchKernelGGL((lbm_stream_ring_kernel<A, B, STGV_T, true, false>), sh.grid, sh.block, lds, st, pop, geo);
       return hipGetLastError();
     }
   }
-  if (mode == MODE_EVEN)
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_EVEN, ROWS_ANY, CACHED>), grid, block,
-                       even_step_lds(sizeof(STGV_T), geo.n, K_COLLIDE), st, pop, dst, geo);
-  else if (mode == MODE_AB)
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_AB, ROWS_ANY, true>), grid, block, 0, st, pop, dst, geo);
-  else if (row_kind(geo.n, sizeof(STGV_T)) == ROWS_WAVES)
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_WAVES, CACHED>), grid, block, 0, st, pop, dst, geo);
-  else if (!CACHED && row_kind(geo.n, sizeof(STGV_T)) == ROWS_LINES)
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_LINES, false>), grid, block, 0, st, pop, dst, geo);
-  else
-    hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE_ODD, ROWS_ANY, true>), grid, block, 0, st, pop, dst, geo);
+#define STGV_STREAM_GO(MODE, ROWS, C, LDS) \
+  hipLaunchKernelGGL((lbm_stream_kernel<A, B, STGV_T, MODE, ROWS, C>), grid, block, LDS, st, pop, dst, geo)
+  if (mode == MODE_EVEN) {
+    STGV_STREAM_GO(MODE_EVEN, ROWS_ANY, CACHED, even_step_lds(sizeof(STGV_T), geo.n, K_COLLIDE));
+    return hipGetLastError();
+  }
+  if (mode == MODE_AB) {
+    STGV_STREAM_GO(MODE_AB, ROWS_ANY, true, 0);
+    return hipGetLastError();
+  }
+  const int rows = row_kind(geo.n, sizeof(STGV_T));
+  if (rows == ROWS_WAVES) {
+    STGV_STREAM_GO(MODE_ODD, ROWS_WAVES, CACHED, 0);
+    return hipGetLastError();
+  }
+  if constexpr (!CACHED && sizeof(STGV_T) == 4) {      // 2-byte rows of whole lines are whole wavefronts
+    if (rows == ROWS_LINES) {
+      STGV_STREAM_GO(MODE_ODD, ROWS_LINES, false, 0);
+      return hipGetLastError();
+    }
+  }
+  STGV_STREAM_GO(MODE_ODD, ROWS_ANY, true, 0);
+#undef STGV_STREAM_GO
   return hipGetLastError();
 }
 

@@ -139,7 +139,7 @@ __global__ STGV_STEP_BOUNDS_FOR(MODE, FLAGS, T, C) void lbm_step_kernel(T* pop, 
 }
 
 // The plain odd step row-aligned, its x-shift taken through a ring in LDS per block row
-// (row_load / row_pick / row_put / row_store), on the shapes of ring_shape (blocks of
+// (row_load / row_pick / row_put / row_store), on the shapes of ring_whole and ring_part (blocks of
 // whole rows, or 256-node blocks holding part of one row), which tile the box exactly,
 // so every lane is active and reaches the barriers.
 // PART: blocks holding part of a row, whose x-moving loads and stores use the cache
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kNodeBlock) void lbm_stream_kernel(T* pop, T* dst, 
 }
 
 // The odd free-streaming step row-aligned, on the shapes where the odd step runs
-// row-aligned (ring_shape; every lane active).
+// row-aligned (ring_whole, ring_part; every lane active).
 template <int QF, int QG, typename T, bool PART, bool CACHED>
 __global__ __launch_bounds__(256) void lbm_stream_ring_kernel(T* pop, Geometry geo) {
   constexpr bool NL = !CACHED && (!PART || STGV_RING_PART_NT_XLOAD), NS = !CACHED && (!PART || STGV_RING_PART_NT_XSTORE);

@@ -68,7 +68,6 @@ __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ the
     P->b2[t] = v2;
     P->b3[t] = t < N_OUT ? v3 : 0.f;
     P->y_scale[t] = t < N_OUT ? ys : 0.f;
-    P->zero[t] = 0.f;
     if (t < K_IN) {
       P->x_mean[t] = t < N_IN ? xm : 0.f;
       P->x_iscale[t] = t < N_IN ? xi : 0.f;
@@ -688,7 +687,7 @@ __global__ __launch_bounds__(64) void norm_kernel(const float* __restrict__ x, c
 // with 128 lanes, which spill, 48.7.
 //
 // 256^3 -> 64^3, FP32: 3480 us for the per-node stencil, 816 in this form with loads that
-// bypass the caches, 725 with cached ones (four rows in sixteen are read by two blocks), 712
+// bypass the caches, 725 with cached ones (of sixteen rows nine are read once, six twice and one four times), 712
 // with a run of (Y, Z) per XCD, 659 with tiles of them and both sweeps opposed; 500 us is one
 // read of the state.
 // ---------------------------------------------------------------------------

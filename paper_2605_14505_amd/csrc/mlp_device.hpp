@@ -255,7 +255,6 @@ struct Packed {
   uint16_t w3t[N_HID * M_OUT];      // W3^T: [hidden][output], outputs >= 41 zero
   float b1[N_HID], b2[N_HID], b3[M_OUT];
   float x_mean[K_IN], x_iscale[K_IN], y_scale[M_OUT];
-  float zero[M_OUT];                // a zero bias for the backward products
   // the fused step's copies: rows at perm_row(logical row), W3 and b3 times y_scale
   alignas(16) uint16_t w1p[64 * K_IN];
   alignas(16) uint16_t w2p[64 * N_HID];
