@@ -19,13 +19,15 @@ namespace {
 
 constexpr int kShellBlocks = 1024;           // at most, a component
 constexpr int kShellThreads = 256;
-// Components that one transform and one binning launch take: all three up to the size where the
-// three half spectra and rocFFT's work space outgrow the last-level cache, then one.  Below, the
-// time is launches (16^3 33.9 -> 16.1 us, 64^3 53.4 -> 30.1) and the tail of each (128^3 191 -> 140,
-// 160^3 329 -> 260); the results are the same.  The line, one by one / at once: odd boxes, whose
-// rows are transformed at full length, 181^3 1100 / 1040, 199^3 1458 / 1467, 225^3 1313 / 1430;
-// even ones 216^3 667 / 595, 240^3 917 / 842, 250^3 1101 / 1170; rows of whole 64-byte pieces
-// 224^3 750 / 688, 256^3 1101 / 1048, 288^3 1559 / 1582, 320^3 2116 / 2232.
+// Components that one transform and one binning launch take: all three up to a size, beyond it one.
+// Below, the time is launches (16^3 33.9 -> 16.1 us, 64^3 53.4 -> 30.1) and the tail of each (128^3
+// 191 -> 140, 160^3 329 -> 260), and the results are the same; towards the line the gain fades as
+// three half spectra and their work space leave the caches.  The line is a table of measurements, not
+// a count of bytes: rocFFT takes rows of whole 64-byte pieces without work space, other even boxes
+// with one half spectrum of it a component, and odd ones, whose rows it transforms at full length,
+// with four.  One by one / at once, us: odd 181^3 1230 / 1135, 191^3 1356 / 1299, 199^3 1551 / 1537
+// and, on another day, 1458 / 1467, 225^3 1313 / 1430; even 230^3 1405 / 1350, 238^3 1087 / 1093, 246^3
+// 1615 / 1618, 250^3 1156 / 1204; multiples of 16 240^3 978 / 934, 256^3 1119 / 1083, 272^3 1472 / 1529.
 inline int components_at_once(int n) {
   const int up_to = n % 16 == 0 ? 256 : (n % 2 == 0 ? 240 : 181);
   return n <= up_to ? 3 : 1;
@@ -43,8 +45,8 @@ size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 // (kx, ky, kz) along by adding the stride's own digits, so no element needs a division, and
 // the shell is taken in FP32: |k|^2 is an integer below 2^20, and the values next to a shell's
 // edge, (s - 1/2)^2 -+ 1/4 and 3/4, are 1e-4 or more away from it in |k|, twice the rounding.
-// Bound by reading c: 256^3 30 -> 20 us a component.  blockIdx.y is the component of a batch; partial is [shell][block], so that
-// the reduction reads a shell's partials contiguously.
+// Bound by reading c: 256^3 30 -> 20 us a component.  blockIdx.y is the component of a batch; partial
+// is [shell][block], so that the reduction reads a shell's partials contiguously.
 struct Digits {
   int kx, ky, kz;
 };
