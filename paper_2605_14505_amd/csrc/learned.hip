@@ -543,7 +543,7 @@ __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, fl
 // rounding residue that came out positive for about half of all constants at 262 144 rows, and
 // 1 / std of it some 1e8), and a mean far from zero costs no digits: a row is at most sqrt(rows)
 // standard deviations from the mean, so the variance loses no more than the factor `rows` of FP64's
-// 1e-16.
+// 1e-16.  The subtraction costs 0.6 us of 65 at 1 048 576 rows.
 //
 // One pass over the rows, HBM-bound (369 MB at 1 048 576 rows).  V rows of C columns are a
 // run of C pieces of V floats; C neighbouring threads take one piece each, so a thread's V
@@ -566,16 +566,21 @@ constexpr int inverse_mod(int V, int C) {
   return 1;
 }
 
-// What column c of the features is taken relative to: its first row, unless that is infinite or NaN.
-__device__ __forceinline__ double shift_of(const float* __restrict__ x, int c) {
-  return isfinite(x[c]) ? (double)x[c] : 0.0;
+// What a column of the features is taken relative to: its first row, unless that is infinite or NaN.
+__device__ __forceinline__ double shift_of(float first) { return isfinite(first) ? (double)first : 0.0; }
+
+// The first row's values of the V columns that a thread sums in a [rows][C] table.
+template <int C, int V>
+__device__ __forceinline__ void first_row(const float* __restrict__ t, float (&first)[V]) {
+#pragma unroll
+  for (int j = 0; j < V; ++j) first[j] = t[(V * (int)(threadIdx.x % C) + j) % C];
 }
 
 // Column sums of a [rows][C] table: runs [u0, u1) of V rows by this block's threads, the
-// per-thread sums left in LDS as [piece element][thread].  FIRST: sums of t - shift_of and squares
-// of that, else squares of t alone.
+// per-thread sums left in LDS as [piece element][thread].  FIRST: sums of t - shift_of(first) and
+// squares of that, else squares of t alone.
 template <int C, int V, bool FIRST>
-__device__ __forceinline__ void column_sums(const float* __restrict__ t, int64_t u0, int64_t u1,
+__device__ __forceinline__ void column_sums(const float* __restrict__ t, int64_t u0, int64_t u1, const float (&first)[V],
                                             double (*sum)[kStatsThreads], double (*sq)[kStatsThreads]) {
   using Piece = typename FloatPiece<V>::type;
   constexpr int G = kStatsThreads / C;
@@ -585,7 +590,7 @@ __device__ __forceinline__ void column_sums(const float* __restrict__ t, int64_t
   for (int j = 0; j < V; ++j) {
     s[j] = 0.0;
     s2[j] = 0.0;
-    shift[j] = FIRST ? shift_of(t, (V * i + j) % C) : 0.0;
+    shift[j] = FIRST ? shift_of(first[j]) : 0.0;
   }
   if (g < G) {
     const Piece* p = reinterpret_cast<const Piece*>(t);
@@ -628,8 +633,10 @@ __global__ __launch_bounds__(kStatsThreads) void stats_kernel(const float* __res
   __shared__ double sx[V][kStatsThreads], sx2[V][kStatsThreads], sy2[V][kStatsThreads];
   const int64_t b = blockIdx.x, nb = gridDim.x, runs = rows / V;
   const int64_t u0 = runs * b / nb, u1 = runs * (b + 1) / nb;
-  column_sums<N_IN, V, true>(x, u0, u1, sx, sx2);
-  column_sums<N_OUT, V, false>(y, u0, u1, nullptr, sy2);
+  float first[V];       // on its way while the targets are summed
+  first_row<N_IN, V>(x, first);
+  column_sums<N_OUT, V, false>(y, u0, u1, first, nullptr, sy2);
+  column_sums<N_IN, V, true>(x, u0, u1, first, sx, sx2);
   __syncthreads();
   // one wavefront per statistic; the last block also takes the rows past the last whole run
   const int c = threadIdx.x & 63, which = threadIdx.x >> 6;
@@ -638,7 +645,7 @@ __global__ __launch_bounds__(kStatsThreads) void stats_kernel(const float* __res
                         : (which == 1 ? column_total<N_IN, V>(sx2, c) : column_total<N_OUT, V>(sy2, c));
   if (b == nb - 1)
     for (int64_t r = runs * V; r < rows; ++r) {
-      const double d = which < 2 ? (double)x[r * N_IN + c] - shift_of(x, c) : (double)y[r * N_OUT + c];
+      const double d = which < 2 ? (double)x[r * N_IN + c] - shift_of(x[c]) : (double)y[r * N_OUT + c];
       s += which == 0 ? d : d * d;
     }
   part[(which * N_IN + c) * nb + b] = s;
@@ -648,6 +655,7 @@ __global__ __launch_bounds__(kStatsThreads) void stats_kernel(const float* __res
 __global__ __launch_bounds__(64) void norm_kernel(const float* __restrict__ x, const double* __restrict__ part,
                                                   int nblocks, int64_t rows, float* __restrict__ norm) {
   const int c = blockIdx.x, lane = threadIdx.x;
+  const float first = x[c < N_IN ? c : 0];
   auto total = [&](int stat) {
     double s = 0.0;
 #pragma unroll 4
@@ -659,7 +667,7 @@ __global__ __launch_bounds__(64) void norm_kernel(const float* __restrict__ x, c
     const double mean = s / rows;
     const double var = s2 / rows - mean * mean;
     if (lane == 63) {
-      norm[c] = (float)(shift_of(x, c) + mean);
+      norm[c] = (float)(shift_of(first) + mean);
       norm[N_IN + c] = var > 1e-300 ? (float)(1.0 / sqrt(var)) : 0.f;
     }
   } else {
