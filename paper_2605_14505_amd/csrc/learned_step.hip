@@ -439,7 +439,8 @@ __global__ __launch_bounds__(256, DIAG ? 1 : 4) void learned_step_kernel(float* 
     uint32_t o0 = 0, o1 = 0;
     if (p0 >= 0) address_of<MODE, false>(p0, ixs, a0, o0);
     if (p1 >= 0) address_of<MODE, false>(p1, ixs, a1, o1);
-    // through the caches: 64^3 32.5 -> 30.1 us against stores that bypass them, 128^3 258.7 -> 256.8
+    // through the caches, against stores that bypass them: 64^3 35.6 -> 33.3 us, 128^3 219.2 -> 221, 192^3
+    // 692 -> 688, 256^3 1643 -> 1636; A-B 128^3 244 -> 218, 256^3 2090 -> 1929
     if ((h ? p1 : p0) >= 0) store_as<false>(slot_address(dst, p0, p1, a0, a1, h ? o1 : o0), v[s]);
   }
 
