@@ -105,7 +105,7 @@ def main():
     ap.add_argument("--pmc", action="append", default=[],
                     help="further --pmc folders of the same command: their counters per kernel "
                          "go to profiles/KEY_pmc.txt")
-    ap.add_argument("--match", default="", help="only kernels whose name contains this in KEY_pmc.txt")
+    ap.add_argument("--match", default="", help="only kernels whose name this pattern finds in KEY_kernel_stats.txt and KEY_pmc.txt")
     a = ap.parse_args()
     os.makedirs(PROFILES, exist_ok=True)
     if a.trace:
@@ -117,6 +117,8 @@ def main():
                 fh.write(f"# {a.note}\n")
             fh.write(f"{'calls':>6} {'avg_us':>10} {'min_us':>10} {'max_us':>10} {'pct':>6}  kernel\n")
             for name, calls, avg, mn, mx, pct in kernel_stats(a.trace):
+                if not re.search(a.match, name):
+                    continue
                 fh.write(f"{calls:6d} {avg:10.2f} {mn:10.2f} {mx:10.2f} {pct:6.2f}  {name[:150]}\n")
         print("wrote", path)
     if a.fetch and a.write:
@@ -160,7 +162,7 @@ def main():
             if a.note:
                 fh.write(f"# {a.note}\n")
             for k in sorted(table):
-                if a.match and a.match not in k:
+                if not re.search(a.match, k):
                     continue
                 fh.write(f"{k[:150]}\n")
                 for c in sorted(table[k]):
